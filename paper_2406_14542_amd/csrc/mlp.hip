@@ -33,232 +33,359 @@ constexpr int oW4 = oB3 + kHid;
 constexpr int oB4 = oW4 + kHid;
 constexpr int kParams = oB4 + 1;
 
-constexpr int kTileP = 64;        // points per tile (one per lane)
-constexpr int kLd = kHid + 1;     // padded LDS row: lanes read different rows without conflicts
-constexpr int kQ = kHid / 4;      // outputs per wave (4 waves split a layer's 128 outputs)
+constexpr int kTileP = 64;        // points per tile
+constexpr int kLd = kHid + 4;     // LDS row of a point's activations (see Tile)
+constexpr int kLdX = 20;          // LDS row of a point's inputs: 12 features, 1, zeros up to 16
+constexpr int kUB = kHid / 16;    // blocks of 16 units
+
+typedef float f4 __attribute__((ext_vector_type(4)));
 
 __device__ inline float softplus(float z) { return z > 20.f ? z : log1pf(expf(z)); }
 __device__ inline float sigmoid(float z) { return 1.f / (1.f + expf(-z)); }
 
-__device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
-
-// out[p][32 q .. 32 q + 31] = tanh(W^T in[p] + b) for the tile's 64 points; the weights of
-// this wave's quarter are wave-uniform (scalar loads).
-template <int NIN, int LDI>
-__device__ inline void dense_tanh(const float* __restrict__ Wt, const float* __restrict__ b,
-                                  const float* in, float* out)
+// The network's layers are matrix products, run on v_mfma_f32_16x16x4_f32 (FP32 inputs and sums:
+// 157 TFLOP/s, twice the unpacked FP32 VALU).  Operands, with c = lane % 16 and g = lane / 16:
+// A[row c][k g], B[k g][column c], D[row 4 g + r][column c] in register r.
+//
+// Rows are units, columns are points: a wave owns the 16 units u0 .. u0 + 15 of a layer for some of
+// the tile's points, holds its slice of the layer's weights in 32 registers (fetched per tile: the
+// 270 KB of parameters stay in L2), and reads the points' activations from LDS.  The k index
+// of MFMA (t, i) in lane group g is 16 t + 4 g + i, so that a lane's operands of four consecutive
+// MFMAs are 16 consecutive bytes of its point's row; D holds four consecutive units of a point, which
+// go back with one 16-byte store.  Rows of 132 floats put the 16 points of such an access on 16
+// different groups of four banks.
+__device__ inline void load_w_fwd(const float* __restrict__ Wt, int u0, int c, int g, float (&w)[32])
 {
-    const int q = wave_id();
-    const int lane = threadIdx.x & 63;
-    float acc[kQ];
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) acc[i] = b[q * kQ + i];
-    for (int k = 0; k < NIN; ++k) {
-        const float a = in[lane * LDI + k];
-        const float* wr = Wt + k * kHid + q * kQ;
+    for (int t = 0; t < kUB; ++t)
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) acc[i] = fmaf(wr[i], a, acc[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) out[lane * kLd + q * kQ + i] = tanhf(acc[i]);
+        for (int i = 0; i < 4; ++i) w[4 * t + i] = Wt[(16 * t + 4 * g + i) * kHid + u0 + c];
 }
 
-struct TileBufs {
-    float x0[kTileP * kIn];
-    float a1[kTileP * kLd];
-    float a2[kTileP * kLd];
-    float a3[kTileP * kLd];
-    float z4[kTileP];
-};
+// the transposed product's slice: rows are the layer's inputs, k its outputs
+__device__ inline void load_w_bwd(const float* __restrict__ Wt, int u0, int c, int g, float (&w)[32])
+{
+    // four-byte alignment only: the blocks of the parameter array start at multiples of 4 bytes
+    const float* row = Wt + (u0 + c) * kHid + 4 * g;
+#pragma unroll
+    for (int t = 0; t < kUB; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[4 * t + i] = row[16 * t + i];
+}
 
-// forward pass of one tile into the LDS buffers (256 threads)
+// acc[pb] += (weight slice) x (act rows pbase + 16 pb ..)
+template <int NPB>
+__device__ inline void mm_units(const float (&w)[32], const float* act, int pbase, int c, int g,
+                                f4 (&acc)[NPB])
+{
+#pragma unroll
+    for (int t = 0; t < kUB; ++t) {
+        f4 b[NPB];
+#pragma unroll
+        for (int pb = 0; pb < NPB; ++pb)
+            b[pb] = *reinterpret_cast<const f4*>(act + (pbase + 16 * pb + c) * kLd + 16 * t + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int pb = 0; pb < NPB; ++pb)
+                acc[pb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[4 * t + i], b[pb][i], acc[pb], 0, 0, 0);
+    }
+}
+
+// D[NK] (rows: 16 units of `a` per block from k0 on, columns: units j0 .. j0 + 15 of `d`), the sum
+// over the tile's points of a[p][k] d[p][j].  Lane group g takes point 16 S + 4 g + s, whose row is
+// 16 banks from the next group's.
+template <int NK, int LDA>
+__device__ inline void mm_points(const float* a, int k0, const float* d, int j0, int c, int g,
+                                 f4 (&out)[NK])
+{
+#pragma unroll
+    for (int kb = 0; kb < NK; ++kb) out[kb] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int q = 0; q < kTileP / 4; ++q) {
+        const int p = (q >> 2) * 16 + 4 * g + (q & 3);
+        const float b = d[p * kLd + j0 + c];
+#pragma unroll
+        for (int kb = 0; kb < NK; ++kb)
+            out[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[p * LDA + k0 + 16 * kb + c], b, out[kb], 0,
+                                                           0, 0);
+    }
+}
+
+__device__ inline f4 tanh4(f4 v)
+{
+    f4 o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[r] = tanhf(v[r]);
+    return o;
+}
+
+// b[0 .. 3] of an array aligned to 4 bytes
+__device__ inline f4 load4(const float* __restrict__ b)
+{
+    return f4{b[0], b[1], b[2], b[3]};
+}
+
+// Forward pass of one tile by the whole block: a1 and a2 into LDS, the wave's own a3 (units
+// u0 + 4 g + r of points pbase + 16 pb + c) into a3, its share of the output layer's sum into zp.
+// Ends with a barrier.
+template <int NPB>
 __device__ inline void tile_forward(const float* __restrict__ prm, const float* __restrict__ feat,
-                                    int64_t p0, int64_t npts, TileBufs& s)
+                                    int64_t p0, int64_t npts, int ub, int pbase, int c, int g,
+                                    float* x0, float* A1, float* A2, float (*zp)[kTileP],
+                                    f4 (&a3)[NPB])
 {
-    for (int e = threadIdx.x; e < kTileP * kIn; e += blockDim.x) {
-        const int64_t p = p0 + e / kIn;
-        s.x0[e] = p < npts ? feat[p0 * kIn + e] : 0.f;
+    const int u0 = 16 * ub;
+    float w[32];
+    for (int e = threadIdx.x; e < kTileP * 16; e += blockDim.x) {
+        const int p = e >> 4, k = e & 15;
+        float v = k == kIn ? 1.f : 0.f;  // the row of ones carries db1
+        if (k < kIn && p0 + p < npts) v = feat[(p0 + p) * kIn + k];
+        x0[p * kLdX + k] = v;
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int k = 4 * g + i;
+        w[i] = k < kIn ? prm[oW1 + (k < kIn ? k : 0) * kHid + u0 + c] : 0.f;
+    }
+    f4 acc[NPB], bias = load4(prm + oB1 + u0 + 4 * g);
     __syncthreads();
-    dense_tanh<kIn, kIn>(prm + oW1, prm + oB1, s.x0, s.a1);
+#pragma unroll
+    for (int pb = 0; pb < NPB; ++pb) {
+        acc[pb] = bias;
+        const f4 b = *reinterpret_cast<const f4*>(x0 + (pbase + 16 * pb + c) * kLdX + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            acc[pb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i], b[i], acc[pb], 0, 0, 0);
+    }
+#pragma unroll
+    for (int pb = 0; pb < NPB; ++pb)
+        *reinterpret_cast<f4*>(A1 + (pbase + 16 * pb + c) * kLd + u0 + 4 * g) = tanh4(acc[pb]);
+    load_w_fwd(prm + oW2, u0, c, g, w);
+    bias = load4(prm + oB2 + u0 + 4 * g);
     __syncthreads();
-    dense_tanh<kHid, kLd>(prm + oW2, prm + oB2, s.a1, s.a2);
+#pragma unroll
+    for (int pb = 0; pb < NPB; ++pb) acc[pb] = bias;
+    mm_units<NPB>(w, A1, pbase, c, g, acc);
+#pragma unroll
+    for (int pb = 0; pb < NPB; ++pb)
+        *reinterpret_cast<f4*>(A2 + (pbase + 16 * pb + c) * kLd + u0 + 4 * g) = tanh4(acc[pb]);
+    load_w_fwd(prm + oW3, u0, c, g, w);
+    bias = load4(prm + oB3 + u0 + 4 * g);
     __syncthreads();
-    dense_tanh<kHid, kLd>(prm + oW3, prm + oB3, s.a2, s.a3);
-    __syncthreads();
-    if (threadIdx.x < kTileP) {
-        const int lane = threadIdx.x;
-        float z = prm[oB4];
-        for (int k = 0; k < kHid; ++k) z = fmaf(prm[oW4 + k], s.a3[lane * kLd + k], z);
-        s.z4[lane] = z;
+#pragma unroll
+    for (int pb = 0; pb < NPB; ++pb) acc[pb] = bias;
+    mm_units<NPB>(w, A2, pbase, c, g, acc);
+    const f4 w4 = load4(prm + oW4 + u0 + 4 * g);
+#pragma unroll
+    for (int pb = 0; pb < NPB; ++pb) {
+        a3[pb] = tanh4(acc[pb]);
+        float z = a3[pb][0] * w4[0] + a3[pb][1] * w4[1] + a3[pb][2] * w4[2] + a3[pb][3] * w4[3];
+        z += __shfl_xor(z, 16);
+        z += __shfl_xor(z, 32);
+        if (g == 0) zp[ub][pbase + 16 * pb + c] = z;
     }
     __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ prm,
-                                                     const float* __restrict__ feat, int64_t npts,
-                                                     float scale, float* __restrict__ w)
+// the output unit of point p from the blocks' shares
+__device__ inline float out_unit(const float* __restrict__ prm, const float (*zp)[kTileP], int p)
 {
-    __shared__ TileBufs s;
+    float z = prm[oB4];
+#pragma unroll
+    for (int u = 0; u < kUB; ++u) z += zp[u][p];
+    return z;
+}
+
+// Forward: one block of 8 waves per tile, wave u owns units 16 u .. of all 64 points; two blocks
+// per CU (75 KB of LDS each), so that one's tanh and barriers run beside the other's MFMAs.  Bound by
+// the FP32 MFMAs (70 kflop a point; 0.90 ms at their peak for 2 M points): 1.49 ms, 94 TFLOP/s,
+// against 17.96 ms with one lane per point on the VALU (102 KB of LDS, one block of 4 waves per CU).
+__global__ __launch_bounds__(512, 4) void k_mlp_forward(const float* __restrict__ prm,
+                                                        const float* __restrict__ feat,
+                                                        int64_t npts, float scale,
+                                                        float* __restrict__ w)
+{
+    __shared__ __align__(16) float x0[kTileP * kLdX];
+    __shared__ __align__(16) float A1[kTileP * kLd];
+    __shared__ __align__(16) float A2[kTileP * kLd];
+    __shared__ float zp[kUB][kTileP];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t p0 = (int64_t)blockIdx.x * kTileP;
-    tile_forward(prm, feat, p0, npts, s);
+    f4 a3[4];
+    tile_forward<4>(prm, feat, p0, npts, wave, 0, lane & 15, lane >> 4, x0, A1, A2, zp, a3);
     if (threadIdx.x < kTileP && p0 + threadIdx.x < npts)
-        w[p0 + threadIdx.x] = softplus(s.z4[threadIdx.x]) * scale;
+        w[p0 + threadIdx.x] = softplus(out_unit(prm, zp, threadIdx.x)) * scale;
 }
 
-// Backward: grid-stride over tiles; every block accumulates the parameter gradient of its
-// tiles in registers (thread t owns output unit j = t % 128 of W2t/W3t for input rows
-// k in [64 (t / 128), +64)), then writes one partial vector; k_mlp_reduce sums the partials
-// in block order.
-__global__ __launch_bounds__(256) void k_mlp_backward(const float* __restrict__ prm,
-                                                      const float* __restrict__ feat,
-                                                      const float* __restrict__ gw, int64_t npts,
-                                                      float scale, float* __restrict__ partial)
+// Backward: grid-stride over tiles by blocks of 16 waves (four per SIMD).  Wave (ub, ph) owns units
+// 16 ub .. of points 32 ph .. in the products over units, and the gradient blocks of rows 64 ph ..,
+// columns 16 ub .. of W2 and W3 (32 registers) in the products over points.  A tile's gradient is
+// summed from zero and then added to the block's running sum, so that the sums' rounding grows
+// with the number of tiles, not of points.  Every block writes one partial vector, which
+// k_mlp_reduce sums in block order.  Bound by the FP32 MFMAs (208 kflop a point; 2.65 ms at their
+// peak for 2 M points) and the barriers between the layers: 6.03 ms against 85.4 ms on the VALU
+// (135 KB of LDS, one block of 4 waves per CU; strided scalar weight loads in the delta products).
+__global__ __launch_bounds__(1024) void k_mlp_backward(const float* __restrict__ params,
+                                                       const float* __restrict__ feat,
+                                                       const float* __restrict__ gw, int64_t npts,
+                                                       float scale, float* __restrict__ partial)
 {
-    __shared__ TileBufs s;
-    __shared__ float g4[kTileP];
-    __shared__ float dl[kTileP * kLd];  // delta of the current layer
-    const int t = threadIdx.x;
-    const int j = t & (kHid - 1);
-    const int kh = __builtin_amdgcn_readfirstlane(t >> 7);  // which half of the input rows
-    float dW2[64], dW3[64];
-    float dW1[kIn / 2], db1 = 0.f, db2 = 0.f, db3 = 0.f, dw4 = 0.f, db4 = 0.f;
+    __shared__ __align__(16) float x0[kTileP * kLdX];
+    __shared__ __align__(16) float A1[kTileP * kLd];
+    __shared__ __align__(16) float A2[kTileP * kLd];
+    __shared__ __align__(16) float dl[kTileP * kLd];  // delta of the current layer
+    __shared__ float zp[kUB][kTileP];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int ub = wave & (kUB - 1), ph = wave / kUB, u0 = 16 * ub;
+    const int c = lane & 15, g = lane >> 4;
+    const int pbase = 32 * ph;
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 dW2[4], dW3[4], dW1 = zero, db2 = zero, db3 = zero, dw4 = zero;
+    float db4 = 0.f;
 #pragma unroll
-    for (int k = 0; k < 64; ++k) dW2[k] = dW3[k] = 0.f;
-#pragma unroll
-    for (int k = 0; k < kIn / 2; ++k) dW1[k] = 0.f;
+    for (int k = 0; k < 4; ++k) dW2[k] = dW3[k] = zero;
 
     const int64_t ntiles = (npts + kTileP - 1) / kTileP;
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const int64_t p0 = tile * kTileP;
-        tile_forward(prm, feat, p0, npts, s);
-        // output layer: g4 = dL/dz4 = dL/dw * scale * sigmoid(z4)
-        if (t < kTileP) {
-            const int64_t p = p0 + t;
-            g4[t] = p < npts ? gw[p] * scale * sigmoid(s.z4[t]) : 0.f;
-        }
-        __syncthreads();
-        // dw4, db4 and delta3 = g4 w4 (1 - a3^2); threads 0..127 own unit j
-        if (t < kHid) {
-            float acc = 0.f, accb = 0.f;
-            for (int p = 0; p < kTileP; ++p) {
-                acc = fmaf(g4[p], s.a3[p * kLd + j], acc);
-                accb += g4[p];
-            }
-            dw4 += acc;
-            if (t == 0) db4 += accb;
-        }
-        for (int e = t; e < kTileP * kHid; e += blockDim.x) {
-            const int p = e / kHid, u = e % kHid;
-            const float a = s.a3[p * kLd + u];
-            dl[p * kLd + u] = g4[p] * prm[oW4 + u] * (1.f - a * a);
-        }
-        __syncthreads();
-        // dW3t[k][j] += sum_p a2[p][k] delta3[p][j];  db3[j] += sum_p delta3[p][j]
-        for (int p = 0; p < kTileP; ++p) {
-            const float d = dl[p * kLd + j];
-            const float* ar = s.a2 + p * kLd + 64 * kh;
-#pragma unroll
-            for (int k = 0; k < 64; ++k) dW3[k] = fmaf(ar[k], d, dW3[k]);
-            if (kh == 0) db3 += d;
-        }
-        // delta2[p][k] = (sum_j W3t[k][j] delta3[p][j]) (1 - a2^2): thread -> (p = t % 64,
-        // k block of 32 = t / 64); computed into registers, then stored over delta3
-        float d2[kQ];
+        f4 a3[2];
+        // the parameters are fetched anew for every tile: held across tiles, they (and the
+        // addresses of their loads) spill
+        const float* prm = params;
+        int ln = lane;
+        asm volatile("" : "+s"(prm), "+v"(ln));
+        const int c = ln & 15, g = ln >> 4;
+        tile_forward<2>(prm, feat, p0, npts, ub, pbase, c, g, x0, A1, A2, zp, a3);
+        // output layer: g4 = dL/dz4 = dL/dw scale sigmoid(z4); delta3 = g4 w4 (1 - a3^2)
         {
-            const int p = t & 63;
-            const int kb = wave_id();
+            const f4 w4 = load4(prm + oW4 + u0 + 4 * g);
+            f4 s4 = zero, s3 = zero;
 #pragma unroll
-            for (int i = 0; i < kQ; ++i) d2[i] = 0.f;
-            for (int jj = 0; jj < kHid; ++jj) {
-                const float dv = dl[p * kLd + jj];
-#pragma unroll
-                for (int i = 0; i < kQ; ++i)
-                    d2[i] = fmaf(prm[oW3 + (kb * kQ + i) * kHid + jj], dv, d2[i]);
+            for (int pb = 0; pb < 2; ++pb) {
+                const int p = pbase + 16 * pb + c;
+                const float g4 =
+                    p0 + p < npts ? gw[p0 + p] * scale * sigmoid(out_unit(prm, zp, p)) : 0.f;
+                const f4 d = g4 * w4 * (1.f - a3[pb] * a3[pb]);
+                s4 += g4 * a3[pb];
+                s3 += d;
+                db4 += g4;
+                *reinterpret_cast<f4*>(dl + p * kLd + u0 + 4 * g) = d;
             }
+            dw4 += s4;
+            db3 += s3;
+        }
+        float w[32];
+        f4 t[4], acc[2];
+        load_w_bwd(prm + oW3, u0, c, g, w);
+        __syncthreads();
+        // dW3t[k][j] += sum_p a2[p][k] delta3[p][j];  delta2 = (W3t delta3) (1 - a2^2)
+        mm_points<4, kLd>(A2, 64 * ph, dl, u0, c, g, t);
 #pragma unroll
-            for (int i = 0; i < kQ; ++i) {
-                const float a = s.a2[p * kLd + kb * kQ + i];
-                d2[i] *= (1.f - a * a);
-            }
+        for (int k = 0; k < 4; ++k) dW3[k] += t[k];
+        acc[0] = acc[1] = zero;
+        mm_units<2>(w, dl, pbase, c, g, acc);
+        load_w_bwd(prm + oW2, u0, c, g, w);
+        __syncthreads();  // delta3 has been read
+#pragma unroll
+        for (int pb = 0; pb < 2; ++pb) {
+            const int o = (pbase + 16 * pb + c) * kLd + u0 + 4 * g;
+            const f4 a = *reinterpret_cast<const f4*>(A2 + o);
+            acc[pb] *= 1.f - a * a;
+            *reinterpret_cast<f4*>(dl + o) = acc[pb];
+        }
+        db2 += acc[0] + acc[1];
+        __syncthreads();
+        // the same for layer 2
+        mm_points<4, kLd>(A1, 64 * ph, dl, u0, c, g, t);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dW2[k] += t[k];
+        acc[0] = acc[1] = zero;
+        mm_units<2>(w, dl, pbase, c, g, acc);
+        __syncthreads();  // delta2 has been read
+#pragma unroll
+        for (int pb = 0; pb < 2; ++pb) {
+            const int o = (pbase + 16 * pb + c) * kLd + u0 + 4 * g;
+            const f4 a = *reinterpret_cast<const f4*>(A1 + o);
+            *reinterpret_cast<f4*>(dl + o) = acc[pb] * (1.f - a * a);
         }
         __syncthreads();
-        {
-            const int p = t & 63;
-            const int kb = wave_id();
-#pragma unroll
-            for (int i = 0; i < kQ; ++i) dl[p * kLd + kb * kQ + i] = d2[i];
-        }
-        __syncthreads();
-        // dW2t[k][j] += sum_p a1[p][k] delta2[p][j]
-        for (int p = 0; p < kTileP; ++p) {
-            const float d = dl[p * kLd + j];
-            const float* ar = s.a1 + p * kLd + 64 * kh;
-#pragma unroll
-            for (int k = 0; k < 64; ++k) dW2[k] = fmaf(ar[k], d, dW2[k]);
-            if (kh == 0) db2 += d;
-        }
-        // delta1 = (W2t delta2) (1 - a1^2)
-        {
-            const int p = t & 63;
-            const int kb = wave_id();
-#pragma unroll
-            for (int i = 0; i < kQ; ++i) d2[i] = 0.f;
-            for (int jj = 0; jj < kHid; ++jj) {
-                const float dv = dl[p * kLd + jj];
-#pragma unroll
-                for (int i = 0; i < kQ; ++i)
-                    d2[i] = fmaf(prm[oW2 + (kb * kQ + i) * kHid + jj], dv, d2[i]);
-            }
-#pragma unroll
-            for (int i = 0; i < kQ; ++i) {
-                const float a = s.a1[p * kLd + kb * kQ + i];
-                d2[i] *= (1.f - a * a);
-            }
-        }
-        __syncthreads();
-        {
-            const int p = t & 63;
-            const int kb = wave_id();
-#pragma unroll
-            for (int i = 0; i < kQ; ++i) dl[p * kLd + kb * kQ + i] = d2[i];
-        }
-        __syncthreads();
-        // dW1t[k][j] += sum_p x0[p][k] delta1[p][j] (k in this thread's half of the 12 inputs)
-        for (int p = 0; p < kTileP; ++p) {
-            const float d = dl[p * kLd + j];
-#pragma unroll
-            for (int k = 0; k < kIn / 2; ++k)
-                dW1[k] = fmaf(s.x0[p * kIn + kh * (kIn / 2) + k], d, dW1[k]);
-            if (kh == 0) db1 += d;
+        // dW1t and db1 (input row 12 is one)
+        if (ph == 0) {
+            f4 t1[1];
+            mm_points<1, kLdX>(x0, 0, dl, u0, c, g, t1);
+            dW1 += t1[0];
         }
         __syncthreads();
     }
+    // sums over points held by lanes c (and by the two waves of a unit block): first over the lanes
+    float* red = A1;  // [ph][3][kHid], then db4 of the two waves
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            dw4[r] += __shfl_xor(dw4[r], o);
+            db3[r] += __shfl_xor(db3[r], o);
+            db2[r] += __shfl_xor(db2[r], o);
+        }
+        db4 += __shfl_xor(db4, o);
+    }
+    if (c == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            red[(3 * ph + 0) * kHid + u0 + 4 * g + r] = dw4[r];
+            red[(3 * ph + 1) * kHid + u0 + 4 * g + r] = db3[r];
+            red[(3 * ph + 2) * kHid + u0 + 4 * g + r] = db2[r];
+        }
+        if (ub == 0 && g == 0) red[6 * kHid + ph] = db4;
+    }
+    __syncthreads();
     float* out = partial + (int64_t)blockIdx.x * kParams;
 #pragma unroll
-    for (int k = 0; k < 64; ++k) {
-        out[oW2 + (64 * kh + k) * kHid + j] = dW2[k];
-        out[oW3 + (64 * kh + k) * kHid + j] = dW3[k];
-    }
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-    for (int k = 0; k < kIn / 2; ++k) out[oW1 + (kh * (kIn / 2) + k) * kHid + j] = dW1[k];
-    if (kh == 0) {
-        out[oB1 + j] = db1;
-        out[oB2 + j] = db2;
-        out[oB3 + j] = db3;
-        out[oW4 + j] = dw4;
-        if (j == 0) out[oB4] = db4;
+        for (int r = 0; r < 4; ++r) {
+            const int row = 64 * ph + 16 * k + 4 * g + r;
+            out[oW2 + row * kHid + u0 + c] = dW2[k][r];
+            out[oW3 + row * kHid + u0 + c] = dW3[k][r];
+        }
+    if (ph == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 4 * g + r;
+            if (row < kIn) out[oW1 + row * kHid + u0 + c] = dW1[r];
+            if (row == kIn) out[oB1 + u0 + c] = dW1[r];
+        }
+    }
+    const int e = threadIdx.x;
+    if (e < kHid) {
+        out[oW4 + e] = red[e] + red[3 * kHid + e];
+        out[oB3 + e] = red[kHid + e] + red[4 * kHid + e];
+        out[oB2 + e] = red[2 * kHid + e] + red[5 * kHid + e];
+        if (e == 0) out[oB4] = red[6 * kHid] + red[6 * kHid + 1];
     }
 }
 
-__global__ void k_mlp_reduce(const float* __restrict__ partial, int nblocks,
-                             float* __restrict__ grad)
+// grad[i] = sum of the partial vectors: 16 threads of a parameter each sum every 16th vector in
+// order, then their sums are added in order
+constexpr int kRedRows = 16;
+__global__ __launch_bounds__(1024) void k_mlp_reduce(const float* __restrict__ partial, int nblocks,
+                                                     float* __restrict__ grad)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kParams) return;
+    __shared__ float sh[kRedRows][64];
+    const int x = threadIdx.x & 63, yy = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + x;
     float s = 0.f;
-    for (int b = 0; b < nblocks; ++b) s += partial[(int64_t)b * kParams + i];
-    grad[i] = s;
+    if (i < kParams)
+        for (int b = yy; b < nblocks; b += kRedRows) s += partial[(int64_t)b * kParams + i];
+    sh[yy][x] = s;
+    __syncthreads();
+    if (yy == 0 && i < kParams) {
+        float v = 0.f;
+#pragma unroll
+        for (int k = 0; k < kRedRows; ++k) v += sh[k][x];
+        grad[i] = v;
+    }
 }
 
 __global__ void k_adam(float* __restrict__ prm, const float* __restrict__ g, float* __restrict__ m,
@@ -405,6 +532,9 @@ __global__ void k_weight_grad(const double* __restrict__ d, const double* __rest
     if (i < n) g[i] = (float)(2.0 * d[i] * q[i] / *den);
 }
 
+// blocks of the backward pass: one per CU (106 KB of LDS, 16 waves)
+constexpr int kBwdBlocks = 256;
+
 inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
@@ -516,7 +646,7 @@ int nusht_mlp_forward(const float* params, const float* features, int64_t npts, 
     if (!params || !features || !weights || npts < 1) return NUSHT_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int64_t tiles = (npts + kTileP - 1) / kTileP;
-    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)tiles), dim3(256), 0, s, params, features,
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)tiles), dim3(512), 0, s, params, features,
                        npts, scale, weights);
     NUSHT_HIP(hipGetLastError());
     return NUSHT_OK;
@@ -528,12 +658,12 @@ int nusht_mlp_backward(const float* params, const float* features, const float* 
     if (!params || !features || !grad_weights || !grad_params || npts < 1) return NUSHT_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int64_t tiles = (npts + kTileP - 1) / kTileP;
-    const int blocks = (int)(tiles < 512 ? tiles : 512);
+    const int blocks = (int)(tiles < kBwdBlocks ? tiles : kBwdBlocks);
     float* partial = nullptr;
     NUSHT_HIP(hipMallocAsync((void**)&partial, (size_t)blocks * kParams * sizeof(float), s));
-    hipLaunchKernelGGL(k_mlp_backward, dim3(blocks), dim3(256), 0, s, params, features,
+    hipLaunchKernelGGL(k_mlp_backward, dim3(blocks), dim3(1024), 0, s, params, features,
                        grad_weights, npts, scale, partial);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((kParams + 255) / 256), dim3(256), 0, s, partial, blocks,
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((kParams + 63) / 64), dim3(1024), 0, s, partial, blocks,
                        grad_params);
     NUSHT_HIP(hipGetLastError());
     NUSHT_HIP(hipFreeAsync(partial, s));
