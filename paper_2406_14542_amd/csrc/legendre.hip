@@ -18,6 +18,9 @@
 //    below 2^-200 are dropped (they cannot reach the FP64 result).
 #include "internal.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace nusht {
 namespace {
 
@@ -782,6 +785,256 @@ __global__ __launch_bounds__(kAdjWaves * 64, DET ? 3 : 4) void k_legendre_adj(
     asm volatile("s_waitcnt vmcnt(0)" ::"v"(pf_keep) : "memory");
 }
 
+// ------------------------------------------------------------------------------------
+// Adjoint of one map.  The 4x4x4 products above compute four maps whatever the batch, behind an
+// LDS round trip of every lam value; for one map the products with the ring data cost less than that
+// on the VALU.  So every lane sums lam times its data over its R ring pairs (two FMAs per pair and
+// l) and only the sum over the wave's lanes is a matrix
+// product: v_mfma_f64_4x4x4_4b with A_b[i][k] = [i = l mod 4] takes the lane values as they lie (B_b[k][j]
+// in lane j + 4 b + 16 k) and adds those of the four lanes x, x + 16, x + 32, x + 48 into row i of D
+// (lane x + 16 i), so four MFMAs of four consecutive l leave 16 partial sums of each in one
+// register; these are summed within the rows of 16 lanes by DPP (wave_rows).  No LDS, no
+// barriers, no waits between waves: a wave is on its own and adds its sums into the zeroed output
+// with FP64 atomics (or writes them to its partial array, see part_stride).
+//
+// Work split: the live pairs (from jlive[m] on) are cut into sub-blocks of 64 neighbours, counted from
+// the equator; the fewest waves that hold them at R per wave take them in turn, so that the waves
+// of a block (one m) are equally long: waves of unlike length, or blocks of unlike weight in a fixed
+// order, leave SIMDs and shader engines idle (the same work in blocks of 4 waves and 1 wave by turns
+// took 1.24 instead of 0.8 ms at lmax 2047, one map).  A sub-block runs in the cheapest of three
+// forms: every pair scaled (the recurrence only), some scaled (each value times 1 or 0), none.  The
+// rescale test is made once per chunk: eight steps grow a value by less than 2^56, so a scaled value
+// stays below 2^112 and is dropped below 2^-144.
+//
+// Bound by the FP64 VALU: 5 R instructions per l and wave, and about 10 for the sums.  One map at
+// lmax 2047 / 4095: 0.62 / 5.4 ms against 1.13 / 7.2 ms of the kernel above.  (The same for two
+// maps, 7 R instructions and four MFMAs per l, took 1.21 / 10.4 against 1.12 / 7.3 ms.)
+// ------------------------------------------------------------------------------------
+
+// the double of the lane that DPP control CTRL names (within rows of 16 lanes)
+template <int CTRL>
+__device__ inline double dpp_f64(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+constexpr int kDppXor1 = 0xB1;  // quad_perm [1, 0, 3, 2]
+constexpr int kDppXor2 = 0x4E;  // quad_perm [2, 3, 0, 1]
+constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;
+
+// the sum of q[x & 3] over the row's 16 lanes, in lane x of each row
+__device__ inline double wave_rows(const double (&q)[4], int x)
+{
+    const bool o1 = x & 1, o2 = x & 2;
+    const double a = (o1 ? q[1] : q[0]) + dpp_f64<kDppXor1>(o1 ? q[0] : q[1]);
+    const double b = (o1 ? q[3] : q[2]) + dpp_f64<kDppXor1>(o1 ? q[2] : q[3]);
+    double v = (o2 ? b : a) + dpp_f64<kDppXor2>(o2 ? a : b);
+    v += dpp_f64<kDppRor4>(v);
+    v += dpp_f64<kDppRor8>(v);
+    return v;
+}
+
+constexpr int kOneWaves = 8;  // most waves per block
+
+template <int R, bool FUSED, typename InT>
+__global__ __launch_bounds__(64 * kOneWaves) void k_legendre_adj_one(
+    const InT* __restrict__ in, int64_t in_row_stride, double* __restrict__ alm, int64_t part_stride,
+    int nbx, int lmax, int mmax,
+    const double2* __restrict__ rec, const double* __restrict__ cm_mant,
+    const int* __restrict__ cm_exp, const int* __restrict__ jlive, int nr, int nt)
+{
+    constexpr int LC = 8;  // l values between two flushes: 2 LC / 4 = 4 registers of sums
+    __shared__ float pf_sink[kOneWaves][64];
+    int m, rb;
+    xcd_block(blockIdx.x, nbx, m, rb);
+    if (m > mmax) return;
+    const int npairs = (nr + 1) / 2;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int pc = rb * (blockDim.x >> 6) + wave;
+    const int jl = jlive[m];
+    const int nsub = (npairs - jl + 63) >> 6, nwm = (nsub + R - 1) / R;
+    if (pc >= nwm) return;
+    const int64_t moff = (int64_t)m * (2 * lmax + 1 - m) / 2;
+    const double msgn = (m & 1) ? -1.0 : 1.0;
+    const double cm = cm_mant[m];
+    const int ce = cm_exp[m];
+
+    // per pair: data of the even and odd combinations (N + S, N - S) and the recurrence, which starts
+    // one step early: the step (0, -1) into l = m gives lam_mm from vp = lam_mm, vc = 0
+    double H[R][2][2], y[R], vc[R], vp[R];
+    int k[R];
+    enum { kNone, kDead, kMixed, kPlain };  // no pairs; all, some, none of them scaled
+    int form[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int sub = pc + r * nwm;
+        const int jraw = npairs - 1 - 64 * sub - lane;
+        const bool valid = jraw >= jl;
+        const int j = max(jraw, jl), js = nr - 1 - j;
+        double2 n, s2 = make_double2(0.0, 0.0);
+        if (FUSED) {
+            // folded: G'(j) = Tp(j) + [1 <= j <= N_r - 2] (-1)^m Tp(N_t - j), likewise for js
+            const InT* col = in + (int64_t)m * in_row_stride;
+            n = load_c(col + j);
+            if (j >= 1 && j <= nr - 2) {
+                const double2 w = load_c(col + (nt - j));
+                n.x = fma(msgn, w.x, n.x);
+                n.y = fma(msgn, w.y, n.y);
+            }
+            if (js != j) {
+                s2 = load_c(col + js);
+                if (js >= 1 && js <= nr - 2) {
+                    const double2 w = load_c(col + (nt - js));
+                    s2.x = fma(msgn, w.x, s2.x);
+                    s2.y = fma(msgn, w.y, s2.y);
+                }
+            }
+        } else {
+            n = load_c(in + (int64_t)j * in_row_stride + m);
+            if (js != j) s2 = load_c(in + (int64_t)js * in_row_stride + m);
+        }
+        H[r][0][0] = valid ? n.x + s2.x : 0.0;
+        H[r][0][1] = valid ? n.y + s2.y : 0.0;
+        H[r][1][0] = valid ? n.x - s2.x : 0.0;
+        H[r][1][1] = valid ? n.y - s2.y : 0.0;
+        double s;
+        ring_geom(j, nr, s, y[r]);
+        vc[r] = 0.0;
+        lambda_mm_scaled(cm, ce, s, m, vp[r], k[r]);
+        if (!valid) {
+            vp[r] = 0.0;
+            k[r] = 0;
+        }
+        form[r] = sub >= nsub                          ? kNone
+                  : !__any(k[r] > 0)                   ? kPlain
+                  : __any(valid && k[r] == 0)          ? kMixed
+                                                       : kDead;
+    }
+    // selector rows: sel[i] is 1 in the lanes of row i of the A operand
+    double sel[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sel[i] = (lane & 3) == i ? 1.0 : 0.0;
+    const int x = lane & 15;
+    // lane x < 4 of row i writes component x & 1 of l = chunk + i + 4 (x >> 1)
+    const int out_l = (lane >> 4) + 4 * ((x >> 1) & 1);
+    const bool out_lane = x < 4 && !(part_stride == 0 && m == 0 && (x & 1));
+    double* out = alm + (int64_t)pc * part_stride + (moff + out_l) * 2 + (x & 1);
+    const __attribute__((address_space(4))) double* crec =
+        (const __attribute__((address_space(4))) double*)rec;
+    unsigned pf_keep = 0;
+    const unsigned lds_sink = __builtin_amdgcn_readfirstlane(
+        (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)pf_sink[wave]);
+    int pf_at = m;
+
+    // a chunk's coefficients are fetched while the chunk before runs; the table is padded past its
+    // end, and steps past lmax run on whatever follows (finite coefficients; their sums are not
+    // written)
+    double2 cn[LC];
+    auto fetch = [&](int l0) {
+#pragma unroll
+        for (int i = 0; i < LC; ++i)
+            cn[i] = make_double2(crec[2 * (moff + l0 + i)], crec[2 * (moff + l0 + i) + 1]);
+    };
+    fetch(m);
+    cn[0] = make_double2(0.0, -1.0);
+    int l0 = m;
+    // The sub-blocks come into range in order (the equator first): one loop per number NP of
+    // sub-blocks in range, left when the next one is.
+    auto phase = [&](auto np) {
+        constexpr int NP = decltype(np)::value;
+        for (; l0 <= lmax; l0 += LC) {
+            if (l0 >= pf_at) {
+                pf_keep ^=
+                    prefetch_coeffs<0>(rec, nullptr, 0, moff, lmax, l0 + kPfStep, lane, lds_sink);
+                pf_at = l0 + kPfStep;
+            }
+            double2 cc[LC];
+#pragma unroll
+            for (int i = 0; i < LC; ++i) cc[i] = cn[i];
+            fetch(min(l0 + LC, lmax));
+            double t[LC][2];
+            bool any = NP > 0;
+            auto step = [&](int r, int i) {
+                const double vn = rec_step(cc[i], y[r], vc[r], vp[r]);
+                vp[r] = vc[r];
+                vc[r] = vn;
+                return vn;
+            };
+#pragma unroll
+            for (int i = 0; i < LC; ++i) {
+#pragma unroll
+                for (int e = 0; e < 2; ++e) t[i][e] = 0.0;
+#pragma unroll
+                for (int r = 0; r < NP; ++r) {
+                    const double v = step(r, i);
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+                        t[i][e] = r == 0 ? v * H[0][i & 1][e] : fma(v, H[r][i & 1][e], t[i][e]);
+                }
+            }
+#pragma unroll
+            for (int r = NP; r < R; ++r) {
+                if (form[r] == kNone) continue;
+                if (form[r] == kDead) {
+#pragma unroll
+                    for (int i = 0; i < LC; ++i) step(r, i);
+                } else {
+                    const double f = k[r] == 0 ? 1.0 : 0.0;
+#pragma unroll
+                    for (int i = 0; i < LC; ++i) {
+                        const double v = step(r, i) * f;
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) t[i][e] = fma(v, H[r][i & 1][e], t[i][e]);
+                    }
+                    any = true;
+                }
+                const bool big = (k[r] > 0) && fmax(fabs(vc[r]), fabs(vp[r])) >= kBig;
+                const double sc = big ? kUnit : 1.0;
+                vp[r] *= sc;
+                vc[r] *= sc;
+                k[r] -= big ? 1 : 0;
+                form[r] = !__any(k[r] > 0)                      ? kPlain
+                          : __any(k[r] == 0 && vc[r] != 0.0)    ? kMixed
+                                                                : kDead;
+            }
+            if (any || part_stride != 0) {
+                double q[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int i = 0; i < LC; ++i)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        double& d = q[2 * (i >> 2) + e];
+                        d = __builtin_amdgcn_mfma_f64_4x4x4f64(sel[i & 3], t[i][e], d, 0, 0, 0);
+                    }
+                const double v = wave_rows(q, x);
+                if (out_lane && l0 + out_l <= lmax) {
+                    double* o = out + 2 * (int64_t)l0;
+                    if (part_stride != 0)
+                        *o = (m == 0 && (x & 1)) ? 0.0 : v;
+                    else if (v != 0.0)
+                        unsafeAtomicAdd(o, v);
+                }
+            }
+            if (NP < R && form[NP < R ? NP : 0] == kPlain) {
+                l0 += LC;
+                break;
+            }
+        }
+    };
+    if (form[0] != kPlain) phase(std::integral_constant<int, 0>());
+    if constexpr (R > 1) if (form[1] != kPlain) phase(std::integral_constant<int, 1>());
+    if constexpr (R > 2) if (form[2] != kPlain) phase(std::integral_constant<int, 2>());
+    if constexpr (R > 3) if (form[3] != kPlain) phase(std::integral_constant<int, 3>());
+    if constexpr (R > 4) if (form[4] != kPlain) phase(std::integral_constant<int, 4>());
+    if constexpr (R > 5) if (form[5] != kPlain) phase(std::integral_constant<int, 5>());
+    phase(std::integral_constant<int, R>());
+    // no LDS-DMA write may be in flight when the workgroup's LDS is released
+    asm volatile("s_waitcnt vmcnt(0)" ::"v"(pf_keep) : "memory");
+}
+
 __global__ void k_fill_zero(double* __restrict__ a, int64_t n)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -789,11 +1042,11 @@ __global__ void k_fill_zero(double* __restrict__ a, int64_t n)
 }
 
 // Deterministic adjoint: alm[b][i] = sum over the pair-chunks pc of part[pc][b][i], in pc order.
-// Pair-chunks that wrote nothing for the element's m (all their ring pairs below the live-ring
-// bound jlive[m], or past the last pair) are skipped.
+// Pair-chunks that wrote nothing for the element's m are skipped: those whose ring pairs all lie
+// below the live-ring bound jlive[m], or past the last pair (packed: chunk 0 starts at jlive[m]).
 __global__ void k_adj_reduce(const double2* __restrict__ part, int npc, int nmaps, int64_t nalm,
                              int lmax, int mmax, const int* __restrict__ jlive, int ppb,
-                             int npairs, double2* __restrict__ alm)
+                             int npairs, int packed, double2* __restrict__ alm)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nalm) return;
@@ -806,10 +1059,11 @@ __global__ void k_adj_reduce(const double2* __restrict__ part, int npc, int nmap
     int m = (int)fmin(fmax(floor(0.5 * (bq - sqrt(disc))), 0.0), (double)mmax);
     while (m > 0 && (int64_t)m * (2 * lmax + 3 - m) / 2 > i) --m;
     while (m < mmax && (int64_t)(m + 1) * (2 * lmax + 2 - m) / 2 <= i) ++m;
-    const int pc0 = jlive[m] / ppb;
+    const int pc0 = packed ? 0 : jlive[m] / ppb;
+    const int left = packed ? npairs - jlive[m] : npairs;
     for (int b = 0; b < nmaps; ++b) {
         double2 acc = make_double2(0.0, 0.0);
-        for (int pc = pc0; pc < npc && pc * ppb < npairs; ++pc) {
+        for (int pc = pc0; pc < npc && pc * ppb < left; ++pc) {
             const double2 v = part[((int64_t)pc * nmaps + b) * nalm + i];
             acc.x += v.x;
             acc.y += v.y;
@@ -909,16 +1163,80 @@ int launch_legendre_synth(const nusht_plan_s* p, const double* alm, void* out, i
     return NUSHT_OK;
 }
 
+namespace {
+
+// Ring pairs per lane of the one-map adjoint: more of them share a wave's sums and coefficient
+// loads, fewer make more waves.  At 257 pairs (lmax 511) R = 1 / 2 / 4 took 55 / 50 / 60 us, at 513
+// 205 / 142 / 167, at 769 563 / 384 / 339, at 1025 (R = 2 / 4 / 6) 976 / 634 / 625, at 2049 (5327) /
+// 6222 / 5401: with R = 4 the 9 waves need two blocks per m.
+int one_map_pairs_per_lane(int npairs)
+{
+    return npairs <= 128 ? 1 : npairs <= 640 ? 2 : npairs <= 1024 ? 4 : 6;
+}
+
+// room for the partial sums of deterministic plans
+int ensure_partials(nusht_plan_s* p, size_t need, hipStream_t s)
+{
+    if (need <= p->adj_part_bytes) return NUSHT_OK;
+    NUSHT_HIP(hipStreamSynchronize(s));
+    if (p->adj_part) hipFree(p->adj_part);
+    p->adj_part = nullptr;
+    p->adj_part_bytes = 0;
+    NUSHT_HIP(hipMalloc((void**)&p->adj_part, need));
+    p->adj_part_bytes = need;
+    return NUSHT_OK;
+}
+
+// the adjoint of one map into alm (zeroed, or, deterministic, written)
+template <bool FUSED, typename InT>
+int launch_adj_one(nusht_plan_s* p, const void* in, double* alm, int64_t row_stride,
+                   hipStream_t s)
+{
+    const nusht_geometry& g = p->g;
+    const int npairs = (g.nrings + 1) / 2;
+    const int R = one_map_pairs_per_lane(npairs);
+    const int nw = (npairs + 64 * R - 1) / (64 * R);  // most waves of one m
+    // blocks of equal weight: one block per m up to kOneWaves waves, else the fewest equal ones
+    const int nbx = (nw + kOneWaves - 1) / kOneWaves;
+    const int wpb = (nw + nbx - 1) / nbx;
+    const int mpad = (g.mmax + 1 + 7) / 8 * 8;
+    double* target = alm;
+    int64_t part_stride = 0;
+    if (p->deterministic) {
+        part_stride = g.nalm * 2;
+        NUSHT_TRY(ensure_partials(p, (size_t)nw * part_stride * sizeof(double), s));
+        target = p->adj_part;
+    }
+#define ONE(RV)                                                                                  \
+    hipLaunchKernelGGL((k_legendre_adj_one<RV, FUSED, InT>), dim3(nbx * mpad), dim3(64 * wpb), 0, \
+                       s, reinterpret_cast<const InT*>(in), row_stride, target, part_stride, nbx, \
+                       g.lmax, g.mmax, p->rec, p->cm_mant, p->cm_exp, p->jlive, g.nrings,        \
+                       g.ntorus)
+    if (R == 1)
+        ONE(1);
+    else if (R == 2)
+        ONE(2);
+    else if (R == 4)
+        ONE(4);
+    else
+        ONE(6);
+#undef ONE
+    NUSHT_HIP(hipGetLastError());
+    if (p->deterministic) {
+        hipLaunchKernelGGL(k_adj_reduce, dim3((unsigned)((g.nalm + 255) / 256)), dim3(256), 0, s,
+                           reinterpret_cast<const double2*>(target), nw, 1, g.nalm, g.lmax, g.mmax,
+                           p->jlive, 64 * R, npairs, 1, reinterpret_cast<double2*>(alm));
+        NUSHT_HIP(hipGetLastError());
+    }
+    return NUSHT_OK;
+}
+
+}  // namespace
+
 int launch_legendre_adjoint(nusht_plan_s* p, const void* in, double* alm, int nmaps,
                             int fused, int in_f32, hipStream_t s)
 {
     const nusht_geometry& g = p->g;
-    const int npairs = (g.nrings + 1) / 2;
-    const int npc = (npairs + kAdjWaves * 64 - 1) / (kAdjWaves * 64);
-    int ppb = (npairs + npc - 1) / npc;
-    ppb = ((ppb + 63) / 64) * 64;
-    const int threads = ppb < 128 ? 128 : ppb;
-    const int groups = (nmaps + 3) / 4;
     int64_t map_stride, row_stride;
     if (fused) {
         row_stride = g.ntorus;
@@ -927,24 +1245,44 @@ int launch_legendre_adjoint(nusht_plan_s* p, const void* in, double* alm, int nm
         row_stride = g.nphi / 2 + 1;
         map_stride = (int64_t)g.nrings * row_stride;
     }
+    if (!p->deterministic) {
+        // the workgroups of one m add their sums into the zeroed output with FP64 atomics, which
+        // resolve in the L2 of the XCD those workgroups share
+        const int64_t nz = (int64_t)nmaps * g.nalm * 2;
+        hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, s, alm,
+                           nz);
+    }
+    // one map left over after the groups of four has its own kernel; two or three fill a group of
+    // the other well enough
+    const int one = nmaps % 4 == 1 ? 1 : 0, many = nmaps - one;
+    if (one) {
+        const int64_t esz = in_f32 ? sizeof(float2) : sizeof(double2);
+        const char* lin = reinterpret_cast<const char*>(in) + many * map_stride * esz;
+        double* lout = alm + many * g.nalm * 2;
+        if (fused && in_f32)
+            NUSHT_TRY((launch_adj_one<true, float2>(p, lin, lout, row_stride, s)));
+        else if (fused)
+            NUSHT_TRY((launch_adj_one<true, double2>(p, lin, lout, row_stride, s)));
+        else
+            NUSHT_TRY((launch_adj_one<false, double2>(p, lin, lout, row_stride, s)));
+    }
+    if (!many) return NUSHT_OK;
+    const int npairs = (g.nrings + 1) / 2;
+    const int npc = (npairs + kAdjWaves * 64 - 1) / (kAdjWaves * 64);
+    int ppb = (npairs + npc - 1) / npc;
+    ppb = ((ppb + 63) / 64) * 64;
+    const int threads = ppb < 128 ? 128 : ppb;
+    const int groups = (many + 3) / 4;
     const int mpad = (g.mmax + 1 + 7) / 8 * 8;
     dim3 grid(npc * mpad, groups);
 #define ADJ(F, IT, D, OUT)                                                                      \
     hipLaunchKernelGGL((k_legendre_adj<F, IT, D>), grid, dim3(threads), 0, s,                    \
-                       reinterpret_cast<const IT*>(in), map_stride, row_stride, nmaps, OUT, npc,  \
+                       reinterpret_cast<const IT*>(in), map_stride, row_stride, many, OUT, npc,   \
                        g.nalm, g.lmax, p->rec, p->cm_mant, p->cm_exp, p->jlive, g.nrings,        \
                        g.ntorus, ppb, g.mmax, p->dstatus)
     if (p->deterministic) {
         // every pair-chunk writes its own partial sums; one pass adds them in pair-chunk order
-        const size_t need = (size_t)npc * nmaps * g.nalm * 2 * sizeof(double);
-        if (need > p->adj_part_bytes) {
-            NUSHT_HIP(hipStreamSynchronize(s));
-            if (p->adj_part) hipFree(p->adj_part);
-            p->adj_part = nullptr;
-            p->adj_part_bytes = 0;
-            NUSHT_HIP(hipMalloc((void**)&p->adj_part, need));
-            p->adj_part_bytes = need;
-        }
+        NUSHT_TRY(ensure_partials(p, (size_t)npc * many * g.nalm * 2 * sizeof(double), s));
         double* part = p->adj_part;
         if (fused && in_f32) {
             ADJ(true, float2, true, part);
@@ -955,14 +1293,9 @@ int launch_legendre_adjoint(nusht_plan_s* p, const void* in, double* alm, int nm
         }
         NUSHT_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_adj_reduce, dim3((unsigned)((g.nalm + 255) / 256)), dim3(256), 0, s,
-                           reinterpret_cast<const double2*>(part), npc, nmaps, g.nalm, g.lmax,
-                           g.mmax, p->jlive, ppb, npairs, reinterpret_cast<double2*>(alm));
+                           reinterpret_cast<const double2*>(part), npc, many, g.nalm, g.lmax,
+                           g.mmax, p->jlive, ppb, npairs, 0, reinterpret_cast<double2*>(alm));
     } else {
-        // the pair-chunk workgroups of one m add their sums into the zeroed output with FP64
-        // atomics, which resolve in the L2 of the XCD those workgroups share
-        const int64_t nz = (int64_t)nmaps * g.nalm * 2;
-        hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, s, alm,
-                           nz);
         if (fused && in_f32) {
             ADJ(true, float2, false, alm);
         } else if (fused) {

@@ -48,3 +48,35 @@ def test_mlp_tiles(P, oracle_mod, n):
     assert rel(g, gw) <= 2e-5, rel(g, gw)
     # every point counts once: the output bias's gradient is the sum of the points' terms alone
     assert abs(g[-1] - gw[-1]) <= 2e-5 * abs(gw[-1])
+
+
+def mrel(a, b, lmax, mmax):
+    """relative L2 distance in the <.,.>_m norm"""
+    _, ms = inputs.ell_of_index(lmax, mmax)
+    w = np.where(ms == 0, 1.0, 2.0)
+    return float(np.sqrt((w * np.abs(a - b) ** 2).sum() / (w * np.abs(b) ** 2).sum()))
+
+
+@pytest.mark.parametrize("lmax,mmax,mode,det", [
+    (5, 5, "fused", False), (125, 125, "paper", False), (126, 60, "fused", True),
+    (253, 253, "fused", False), (254, 254, "paper", True), (700, 699, "fused", False),
+    (1279, 1279, "fused", False), (1300, 700, "fused", True), (2049, 2049, "fused", False)])
+def test_one_map_adjoint(P, oracle_mod, lmax, mmax, mode, det):
+    """The adjoint of one map at the edges of its ring-pair splits (64 pairs per sub-block; 1, 2, 4
+    and 6 pairs per lane from 1, 129, 641 and 1025 pairs on), and the same map as the fifth of a
+    batch: within the plan's eps = 1e-12 times the margin of the other FP64 tests."""
+    print(f"[one map lmax={lmax} mmax={mmax} {mode} det={det}]", flush=True)
+    rng = np.random.default_rng(lmax)
+    th, ph = inputs.uniform_points(rng, 61)
+    d = rng.standard_normal((5, th.size))
+    ref = oracle_mod.adjoint(lmax, mmax, th, ph, d[4:])
+    p = P.Plan(lmax, mmax, dev(th), dev(ph), 1e-12, dfs_mode=mode, deterministic=det)
+    one = p.adjoint(dev(d[4:])).cpu().numpy()
+    assert mrel(one, ref, lmax, mmax) <= 1e-11
+    assert np.all(one[0, :lmax + 1].imag == 0.0)
+    five = p.adjoint(dev(d)).cpu().numpy()
+    assert mrel(five[4:], ref, lmax, mmax) <= 1e-11
+    if det:
+        assert np.array_equal(p.adjoint(dev(d[4:])).cpu().numpy(), one)
+        assert np.array_equal(five[4], one[0])
+    p.status()
