@@ -85,17 +85,12 @@ struct nusht_plan_s {
     double eps = 0;
     int device = 0;
     hipStream_t plan_stream = nullptr;
-    // Second stream of the Legendre synthesis (default priority): its plain-range instance runs
-    // there beside the scaled-range instance on the call's stream; fork / join events.
-    hipStream_t side = nullptr;
-    hipEvent_t fork_ev = nullptr, join_ev = nullptr;
 
     // Legendre tables (host-computed, FP64).
     double2* rec = nullptr;      // [nalm]: (a_lm, a_lm * b_lm) of the recurrence, l >= m+1
     double* cm_mant = nullptr;   // [mmax+1]: lam_mm prefactor mantissa, sign (-1)^m included
     int* cm_exp = nullptr;       // [mmax+1]: its power-of-two exponent
     int* jlive = nullptr;        // [mmax+1]: first ring pair with any lam_lm above 2^-300
-    int* jscale = nullptr;       // [mmax+1]: first ring pair with lam_mm above 2^-190
     std::vector<int> jlive_host;
 
     // Wigner-d tables of the spin-weighted Legendre step (spin.hip), for spin spin_s (0: none):
@@ -248,9 +243,6 @@ void stage_end(nusht_plan_s* p, Stage st, hipStream_t s);
 // ring FFT's input); FUSED writes the doubled column Gt[b][m][t], t < N_t.
 int launch_legendre_synth(const nusht_plan_s* p, const double* alm, void* out, int nmaps,
                           int fused, int out_f32, hipStream_t s);
-// ring pairs per lane of the synthesis' plain instance
-int synth_pairs_per_lane(int npairs);
-int synth_scaled_pairs_per_lane(int npairs);
 // adjoint into alm [nmaps][nalm] (complex128), which it zeroes and then accumulates into
 int launch_legendre_adjoint(nusht_plan_s* p, const void* in, double* alm, int nmaps,
                             int fused, int in_f32, hipStream_t s);

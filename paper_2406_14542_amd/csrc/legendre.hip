@@ -15,7 +15,8 @@
 //  * exponent range: lam_mm underflows FP64 for m of a few thousand near the poles.  Each
 //    lane carries a count k of 2^256 factors; while any lane of the wave has k > 0 the wave
 //    runs a rescaling step, afterwards the plain recurrence.  Terms whose true magnitude is
-//    below 2^-200 are dropped (they cannot reach the FP64 result).
+//    below 2^-200 (below 2^-144 where the test is made once per eight steps) are dropped: they
+//    cannot reach the FP64 result.
 #include "internal.h"
 
 #include <algorithm>
@@ -95,18 +96,6 @@ __device__ inline double rec_step(double2 c, double y, double vc, double vp)
     return fma(c.x, xv, -(c.y * vp));
 }
 
-template <int MB>
-__device__ inline void accum(double (&acc)[MB][2], const double2* __restrict__ alm, int64_t nalm,
-                             int64_t idx, double lam)
-{
-#pragma unroll
-    for (int b = 0; b < MB; ++b) {
-        double2 a = alm[b * nalm + idx];
-        acc[b][0] = fma(a.x, lam, acc[b][0]);
-        acc[b][1] = fma(a.y, lam, acc[b][1]);
-    }
-}
-
 // The coefficient stream of one m (recurrence table and MB coefficient rows) is read through
 // the scalar cache, one l at a time, by every wave of that m; a miss costs a trip to HBM that
 // the few resident waves cannot hide.  Every kPfStep values of l the wave therefore touches
@@ -135,17 +124,23 @@ __device__ inline unsigned lds_dma_touch(const void* src, unsigned lds_sink)
     return saved;
 }
 
+// the lane's line of the MB + 1 streams (rec, then MB rows of alm): first coefficient, null if none
 template <int MB>
-__device__ inline unsigned prefetch_coeffs(const double2* __restrict__ rec,
-                                           const double2* __restrict__ alm, int64_t nalm,
-                                           int64_t moff, int lmax, int lp, int lane,
-                                           unsigned lds_sink)
+__device__ inline const double2* touch_line(const double2* __restrict__ rec,
+                                            const double2* __restrict__ alm, int64_t nalm,
+                                            int64_t moff, int lane, int& off)
 {
-    const int stream = lane / kPfLines, line = lane - stream * kPfLines;
-    if (stream > MB || lp > lmax) return 0u;
-    const int64_t idx = moff + min(lp + 8 * line, lmax);
-    const double2* src = (stream == 0 ? rec : alm + (int64_t)(stream - 1) * nalm) + idx;
-    return lds_dma_touch(src, lds_sink);
+    const int stream = lane / kPfLines;
+    off = 8 * (lane - stream * kPfLines);
+    if (stream > MB) return nullptr;
+    return (stream == 0 ? rec : alm + (int64_t)(stream - 1) * nalm) + moff;
+}
+
+__device__ inline unsigned touch_coeffs(const double2* line, int off, int lp, int lmax,
+                                        unsigned lds_sink)
+{
+    if (!line || lp > lmax) return 0u;
+    return lds_dma_touch(line + min(lp + off, lmax), lds_sink);
 }
 
 // ------------------------------------------------------------------------------------
@@ -174,215 +169,281 @@ __device__ inline void xcd_block(int b, int nbx, int& m, int& rb)
     rb = q % nbx;
 }
 
-// Each lane owns R ring pairs j = base + lane + 64 r; a wave therefore covers 64 R
-// consecutive pairs and loads every coefficient once for all of them.
+// Work split, for each m: the live pairs (from jlive[m] on) are cut into sub-blocks of 64 neighbours,
+// counted from the equator; the fewest waves that hold them at R per wave take them in turn, so that
+// every wave has pairs of all latitudes and the waves of one m are equally long: waves of unlike
+// length, or blocks of unlike weight in a fixed order, leave SIMDs and shader engines idle (the one-map
+// adjoint in blocks of 4 waves and 1 wave by turns took 1.24 instead of 0.82 ms at lmax 2047).  A lane
+// runs the recurrence of its R pairs, one of each sub-block, and reads every coefficient once for all
+// of them.
 //
-// The kernel comes in two instances.  Ring pairs j >= jscale[m] have lam_mm above 2^-190,
-// so none of their lam_lm ever needs the power-of-two scale; their waves run the
-// SCALED = false instance, which has no scaled step at all (the scaled step's extra live
-// registers would otherwise cost the whole kernel almost half of its occupancy).  The pairs
-// below jscale[m] (a multiple of 64 R of both instances, so that their waves partition the
-// pairs) run SCALED = true.
-template <int MB, int R, bool FUSED, typename OutT, bool SCALED>
-__global__ __launch_bounds__(256) void k_legendre_synth(
-    const double2* __restrict__ alm, int64_t nalm, int lmax, int mmax, int nbx,
-    const double2* __restrict__ rec, const double* __restrict__ cm_mant,
-    const int* __restrict__ cm_exp, const int* __restrict__ jlive,
-    const int* __restrict__ jscale, int nr, int nt, OutT* __restrict__ out,
-    int64_t out_map_stride, int64_t out_row_stride)
+// Exponent range: a sub-block runs in the cheapest of three forms: every pair scaled (the
+// recurrence only), some scaled (each value times 1 or 0), none.  Sub-blocks come into range in
+// order, the equator first; each state (how many are in range, how many have a pair in range) has a
+// loop of its own, straight-line code without copies of the sums.  The rescale test is made once
+// per chunk of eight steps, which grow a value by less than 2^56: a scaled value stays below 2^112 and is
+// dropped below 2^-144.
+//
+// Bound by the FP64 VALU: (3 + 2 MB) R instructions per l and wave, and by the coefficients' scalar
+// loads.  One map at lmax 127 / 1023 / 1535 / 2047 / 4095: 12 / 84 / 225 / 432 / 2573 us against 43 / 149 /
+// 522 / 603 / 3132 us of two kernels (scaled and unscaled rings) on forked streams with contiguous rings
+// per wave and coefficients loaded when used; four maps 18 / 173 / 488 / 937 / 6401 against 42 / 250 / 878 /
+// 1162 / 7035 us.
+constexpr int kSynLC = 8;               // l values per chunk of the synthesis
+
+constexpr int kSubWaves = 8;  // most waves per block
+
+// Blocks of the kernels that split one m's live pairs over waves of R sub-blocks.  For m > 0 the
+// pole's pair is never live, so that 2^k + 1 pairs (lmax = 2^k' - 1) leave no sub-block of one pair: the
+// launch has waves for npairs - 1 pairs, and m = 0 gets one more block, in front, where it needs it
+// (grid: 8 ids, of which one is used, so that the others keep their XCD).  Wave w of block rb is
+// the m's wave w nbx + rb: blocks of equal weight.
+struct SubGrid {
+    int nbx, wpb, extra;
+    __host__ __device__ SubGrid(int npairs, int R)
+    {
+        const int nw = (npairs + 64 * R - 2) / (64 * R), nw0 = (npairs + 64 * R - 1) / (64 * R);
+        const int n = nw > 0 ? nw : 1;
+        nbx = (n + kSubWaves - 1) / kSubWaves;
+        wpb = (n + nbx - 1) / nbx;
+        extra = nw0 > nbx * wpb ? 8 : 0;
+    }
+    // column m and wave pc of this wave; m > mmax: none
+    __device__ void place(int block, int wave, int mmax, int& m, int& pc) const
+    {
+        if (block < extra) {
+            m = block == 0 ? 0 : mmax + 1;
+            pc = nbx * wpb + wave;
+            return;
+        }
+        int rb;
+        xcd_block(block - extra, nbx, m, rb);
+        pc = wave * nbx + rb;
+    }
+};
+
+// State of a wave's R sub-blocks: the first np have no scaled pair, those from nm on no unscaled
+// one; kept as np * 8 + nm with nm one of np, np + 1 and R, each of which has its own loop.
+// Sub-blocks from np0 on are looked at: k their scale counts, v whether a lane has a value at all.
+template <int R>
+__device__ inline int sub_state(int np0, const int (&k)[R], const bool (&v)[R])
 {
-    int m, rb;
-    xcd_block(blockIdx.x, nbx, m, rb);
-    if (m > mmax) return;
+    int np = np0, nm = np0;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r >= np0) {
+            if (np == r && !__any(k[r] > 0)) np = r + 1;
+            if (__any(k[r] == 0 && v[r])) nm = r + 1;
+        }
+    if (nm < np) nm = np;
+    return np * 8 + (nm > np + 1 ? R : nm);
+}
+
+// the rescale test at a chunk's end (powers of two: exact)
+__device__ inline void rescale(double& vc, double& vp, int& k)
+{
+    const bool big = (k > 0) && fmax(fabs(vc), fabs(vp)) >= kBig;
+    const double sc = big ? kUnit : 1.0;
+    vp *= sc;
+    vc *= sc;
+    k -= big ? 1 : 0;
+}
+
+// Runs f(np, nm), the loop of state np * 8 + nm, for each state in ascending order if it is the
+// current one: sub-blocks only ever come into range, so states only ever grow.
+template <int R, int NP = 0, typename F>
+__device__ inline void run_states(int& st, F&& f)
+{
+    using np = std::integral_constant<int, NP>;
+    if (st == NP * 9) f(np(), np());
+    if constexpr (NP + 1 < R)
+        if (st == NP * 9 + 1) f(np(), std::integral_constant<int, NP + 1>());
+    if constexpr (NP < R) {
+        if (st == NP * 8 + R) f(np(), std::integral_constant<int, R>());
+        run_states<R, NP + 1>(st, f);
+    }
+}
+
+template <int MB, int R, bool FUSED, typename OutT>
+__global__ __launch_bounds__(64 * kSubWaves) void k_legendre_synth(
+    const double2* __restrict__ alm, int64_t nalm, int lmax, int mmax,
+    const double2* __restrict__ rec, const double* __restrict__ cm_mant,
+    const int* __restrict__ cm_exp, const int* __restrict__ jlive, int nr, int nt,
+    OutT* __restrict__ out, int64_t out_map_stride, int64_t out_row_stride)
+{
+    constexpr int LC = kSynLC;
+    __shared__ float pf_sink[kSubWaves][64];
     const int npairs = (nr + 1) / 2;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int wbase = (rb * (blockDim.x >> 6) + wave) * 64 * R;
-    if (wbase >= npairs) return;
-    if (SCALED != (wbase < jscale[m])) return;  // the other instance owns this wave
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const SubGrid sg(npairs, R);
+    int m, pc;
+    sg.place(blockIdx.x, wave, mmax, m, pc);
+    if (m > mmax) return;
+    const int jl = jlive[m];
+    const int nsub = (npairs - jl + 63) >> 6, nwm = (nsub + R - 1) / R;
     alm += (int64_t)blockIdx.y * MB * nalm;
     out += (int64_t)blockIdx.y * MB * out_map_stride;
     const int64_t moff = (int64_t)m * (2 * lmax + 1 - m) / 2;  // index(l, m) = moff + l
-    const bool wave_dead = wbase + 64 * R <= jlive[m];
-    __shared__ float pf_sink[4][64];
-
-    double E[R][MB][2], O[R][MB][2];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int b = 0; b < MB; ++b) E[r][b][0] = E[r][b][1] = O[r][b][0] = O[r][b][1] = 0.0;
-
-    if (!wave_dead) {
-        double y[R], vc[R], vp[R];
-        int k[R];
-        bool any_scaled = false;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int j = min(wbase + lane + 64 * r, npairs - 1);
-            double s;
-            ring_geom(j, nr, s, y[r]);
-            vp[r] = 0.0;
-            lambda_mm_scaled(cm_mant[m], cm_exp[m], s, m, vc[r], k[r]);
-            if (!SCALED && k[r] != 0) {
-                // cannot happen above jscale (10 bits of margin); drop rather than misuse
-                vc[r] = 0.0;
-                k[r] = 0;
-            }
-            if (k[r] == 0) accum<MB>(E[r], alm, nalm, moff + m, vc[r]);
-            any_scaled |= k[r] > 0;
-        }
-        // Steps run in (even, odd) pairs of l - m after the first (odd) one, so that the
-        // accumulator of every step is static.  While some lane of the wave still carries a
-        // 2^256 factor the wave takes the scaled step; the branch is wave-uniform and both
-        // sides update the same accumulators in place.
-        auto scaled_step = [&](const double2 c, int64_t idx, double (&A)[R][MB][2]) {
-            any_scaled = false;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double vn = rec_step(c, y[r], vc[r], vp[r]);
-                vp[r] = vc[r];
-                vc[r] = vn;
-                const bool big = (k[r] > 0) && (fabs(vc[r]) >= kBig);
-                const double sc = big ? kUnit : 1.0;
-                vc[r] *= sc;
-                vp[r] *= sc;
-                k[r] -= big ? 1 : 0;
-                any_scaled |= k[r] > 0;
-                accum<MB>(A[r], alm, nalm, idx, (k[r] == 0) ? vc[r] : 0.0);
-            }
-        };
-        auto plain_step = [&](const double2 c, int64_t idx, double (&A)[R][MB][2]) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double vn = rec_step(c, y[r], vc[r], vp[r]);
-                vp[r] = vc[r];
-                vc[r] = vn;
-                accum<MB>(A[r], alm, nalm, idx, vc[r]);
-            }
-        };
-        int l = m + 1;
-        if (l <= lmax) {
-            if (SCALED && __any(any_scaled))
-                scaled_step(rec[moff + l], moff + l, O);
-            else
-                plain_step(rec[moff + l], moff + l, O);
-            ++l;
-        }
-        int pf_at = l;
-        unsigned pf_keep = 0;
-        const unsigned lds_sink = __builtin_amdgcn_readfirstlane(
-            (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)pf_sink[wave]);
-        auto prefetch = [&]() {
-            if (l >= pf_at) {
-                pf_keep ^= prefetch_coeffs<MB>(rec, alm, nalm, moff, lmax, l + kPfStep, lane,
-                                               lds_sink);
-                pf_at = l + kPfStep;
-            }
-        };
-        if (SCALED) {
-            // Phase 1: no lane has reached the accumulation range (every accumulator is still
-            // zero), so the steps run the recurrence and its rescaling only.  The rescale test
-            // is made once per pair: one step grows a value by less than 2^7, far from the
-            // FP64 range above kBig.  The pair in which some lane reaches k = 0 accumulates
-            // both of its values for those lanes (a value one step before k reached 0 is
-            // below 2^-200 times its coefficient: kept, not dropped).
-            bool reached = false;
-#pragma unroll
-            for (int r = 0; r < R; ++r) reached |= k[r] == 0;
-            if (!__any(reached)) {
-                for (; l + 1 <= lmax; l += 2) {
-                    const double2 c0 = rec[moff + l], c1 = rec[moff + l + 1];
-                    reached = false;
-#pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        const double v0 = rec_step(c0, y[r], vc[r], vp[r]);
-                        const double v1 = rec_step(c1, y[r], v0, vc[r]);
-                        const bool big = fmax(fabs(v0), fabs(v1)) >= kBig;
-                        const double sc = big ? kUnit : 1.0;
-                        vp[r] = v0 * sc;
-                        vc[r] = v1 * sc;
-                        k[r] -= big ? 1 : 0;
-                        reached |= k[r] == 0;
-                    }
-                    if (__any(reached)) {
-                        prefetch();
-                        any_scaled = false;
-#pragma unroll
-                        for (int r = 0; r < R; ++r) {
-                            const bool live = k[r] == 0;
-                            any_scaled |= !live;
-                            accum<MB>(E[r], alm, nalm, moff + l, live ? vp[r] : 0.0);
-                            accum<MB>(O[r], alm, nalm, moff + l + 1, live ? vc[r] : 0.0);
-                        }
-                        l += 2;
-                        break;
-                    }
-                }
-            }
-            // Phase 2: some lane still carries a scale factor: the rescale test once per pair
-            // of steps, as in phase 1, and the pair's two values accumulated for the lanes
-            // whose count is zero after it (scaling by 2^-256 is exact, so the values are the
-            // ones a per-step test would give).
-            for (; l + 1 <= lmax && __any(any_scaled); l += 2) {
-                prefetch();
-                const double2 c0 = rec[moff + l], c1 = rec[moff + l + 1];
-                any_scaled = false;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const double v0 = rec_step(c0, y[r], vc[r], vp[r]);
-                    const double v1 = rec_step(c1, y[r], v0, vc[r]);
-                    const bool big = (k[r] > 0) && fmax(fabs(v0), fabs(v1)) >= kBig;
-                    const double sc = big ? kUnit : 1.0;
-                    vp[r] = v0 * sc;
-                    vc[r] = v1 * sc;
-                    k[r] -= big ? 1 : 0;
-                    const bool live = k[r] == 0;
-                    any_scaled |= !live;
-                    accum<MB>(E[r], alm, nalm, moff + l, live ? vp[r] : 0.0);
-                    accum<MB>(O[r], alm, nalm, moff + l + 1, live ? vc[r] : 0.0);
-                }
-            }
-        }
-        // Phase 3: every lane is in plain FP64 range.
-        for (; l + 1 <= lmax; l += 2) {
-            prefetch();
-            const double2 c0 = rec[moff + l], c1 = rec[moff + l + 1];
-            plain_step(c0, moff + l, E);
-            plain_step(c1, moff + l + 1, O);
-        }
-        if (l <= lmax) {
-            if (SCALED && __any(any_scaled))
-                scaled_step(rec[moff + l], moff + l, E);
-            else
-                plain_step(rec[moff + l], moff + l, E);
-        }
-        // no LDS-DMA write may be in flight when the workgroup's LDS is released
-        asm volatile("s_waitcnt vmcnt(0)" ::"v"(pf_keep) : "memory");
-    }
-
     const double sgn = (m & 1) ? -1.0 : 1.0;
+    // values of pair j: the rings j (n) and N_r - 1 - j (s) of map b
+    auto put = [&](int b, int j, double nre, double nim, double sre, double sim) {
+        const int js = nr - 1 - j;
+        OutT* o = out + b * out_map_stride;
+        if (FUSED) {
+            OutT* col = o + (int64_t)m * out_row_stride;
+            col[j] = make_out<OutT>(nre, nim);
+            if (j >= 1 && j <= nr - 2) col[nt - j] = make_out<OutT>(sgn * nre, sgn * nim);
+            if (js != j) {
+                col[js] = make_out<OutT>(sre, sim);
+                if (js >= 1 && js <= nr - 2) col[nt - js] = make_out<OutT>(sgn * sre, sgn * sim);
+            }
+        } else {
+            o[(int64_t)j * out_row_stride + m] = make_out<OutT>(nre, nim);
+            if (js != j) o[(int64_t)js * out_row_stride + m] = make_out<OutT>(sre, sim);
+        }
+    };
+    // pairs below the live bound are zero
+    for (int j = pc * 64 + lane; j < jl; j += sg.nbx * sg.wpb * 64)
+#pragma unroll
+        for (int b = 0; b < MB; ++b) put(b, j, 0.0, 0.0, 0.0, 0.0);
+    if (pc >= nwm) return;
+
+    // the recurrence starts one step early: the step (0, -1) into l = m gives lam_mm from
+    // vp = lam_mm, vc = 0
+    double E[R][MB][2], O[R][MB][2], y[R], vc[R], vp[R];
+    int k[R];
+    bool has[R];
+    const double cm = cm_mant[m];
+    const int ce = cm_exp[m];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int j = wbase + lane + 64 * r;
-        if (j >= npairs) continue;
-        const int js = nr - 1 - j;
+#pragma unroll
+        for (int b = 0; b < MB; ++b) E[r][b][0] = E[r][b][1] = O[r][b][0] = O[r][b][1] = 0.0;
+        const int sub = pc + r * nwm;
+        const int jraw = npairs - 1 - 64 * sub - lane;
+        const bool valid = jraw >= jl;
+        double s;
+        ring_geom(max(jraw, jl), nr, s, y[r]);
+        vc[r] = 0.0;
+        lambda_mm_scaled(cm, ce, s, m, vp[r], k[r]);
+        if (!valid) {
+            vp[r] = 0.0;
+            k[r] = 0;
+        }
+        has[r] = vp[r] != 0.0;
+    }
+    int st = sub_state<R>(0, k, has);
+    auto step = [&](int r, double2 c) {
+        const double vn = rec_step(c, y[r], vc[r], vp[r]);
+        vp[r] = vc[r];
+        vc[r] = vn;
+        return vn;
+    };
+    auto add = [&](double (&A)[MB][2], const double2 (&a)[MB], double v) {
+#pragma unroll
+        for (int b = 0; b < MB; ++b) {
+            A[b][0] = fma(a[b].x, v, A[b][0]);
+            A[b][1] = fma(a[b].y, v, A[b][1]);
+        }
+    };
+    // Coefficients through the constant address space: wave-uniform scalar loads.  Those of the next
+    // PL values of l are fetched while the current ones are used: as many as fit the scalar
+    // registers twice (a load takes several hundred cycles where no other wave has brought the line
+    // into the scalar cache).
+    using cptr = const __attribute__((address_space(4))) double*;
+    cptr crec = (cptr)(rec + moff), calm = (cptr)(alm + moff);
+    auto fetch = [&](auto& cn, auto& an, int l) {
+        constexpr int PL = sizeof(cn) / sizeof(cn[0]);
+#pragma unroll
+        for (int i = 0; i < PL; ++i) {
+            cn[i] = make_double2(crec[2 * (l + i)], crec[2 * (l + i) + 1]);
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+                an[i][b] = make_double2(calm[2 * (b * nalm + l + i)], calm[2 * (b * nalm + l + i) + 1]);
+        }
+    };
+    int l0 = m, pf_at = m, pf_off;
+    unsigned pf_keep = 0;
+    const double2* pf_line = touch_line<MB>(rec, alm, nalm, moff, lane, pf_off);
+    const unsigned lds_sink = __builtin_amdgcn_readfirstlane(
+        (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)pf_sink[wave]);
+    auto loop = [&](auto np, auto nm) {
+        constexpr int NP = decltype(np)::value, NM = decltype(nm)::value;
+        constexpr int PL = (NP == R ? 8 : 4) / (MB == 1 ? 2 : MB);
+        double2 cn[PL], an[PL][MB];
+        if (l0 + LC - 1 <= lmax) {
+            fetch(cn, an, l0);
+            if (l0 == m) cn[0] = make_double2(0.0, -1.0);
+        }
+        for (; l0 + LC - 1 <= lmax; l0 += LC) {
+            if (l0 >= pf_at) {
+                pf_keep ^= touch_coeffs(pf_line, pf_off, l0 + kPfStep, lmax, lds_sink);
+                pf_at = l0 + kPfStep;
+            }
+            double f[R];
+#pragma unroll
+            for (int r = NP; r < NM; ++r) f[r] = k[r] == 0 ? 1.0 : 0.0;
+#pragma unroll
+            for (int h = 0; h < LC; h += PL) {
+                double2 c[PL], a[PL][MB];
+#pragma unroll
+                for (int i = 0; i < PL; ++i) {
+                    c[i] = cn[i];
+#pragma unroll
+                    for (int b = 0; b < MB; ++b) a[i][b] = an[i][b];
+                }
+                fetch(cn, an, min(l0 + h + PL, lmax + 1 - PL));
+#pragma unroll
+                for (int i = 0; i < PL; ++i)
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const double v = step(r, c[i]);
+                        if (r < NM) add((h + i) & 1 ? O[r] : E[r], a[i], r < NP ? v : v * f[r]);
+                    }
+            }
+            if constexpr (NP < R) {
+#pragma unroll
+                for (int r = NP; r < R; ++r) {
+                    rescale(vc[r], vp[r], k[r]);
+                    has[r] = vc[r] != 0.0 || vp[r] != 0.0;
+                }
+                const int now = sub_state<R>(NP, k, has);
+                if (now > NP * 8 + NM) {
+                    st = now;
+                    l0 += LC;
+                    break;
+                }
+            }
+        }
+    };
+    run_states<R>(st, loop);
+    // the last l values, fewer than a chunk (l0 - m is even)
+    for (int i = 0; l0 + i <= lmax; ++i) {
+        const int l = l0 + i;
+        const double2 c = l == m ? make_double2(0.0, -1.0) : make_double2(crec[2 * l], crec[2 * l + 1]);
+        double2 a[MB];
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+            a[b] = make_double2(calm[2 * (b * nalm + l)], calm[2 * (b * nalm + l) + 1]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double v = k[r] == 0 ? step(r, c) : (step(r, c), 0.0);
+            add(i & 1 ? O[r] : E[r], a, v);
+        }
+    }
+    // no LDS-DMA write may be in flight when the workgroup's LDS is released
+    asm volatile("s_waitcnt vmcnt(0)" ::"v"(pf_keep) : "memory");
+
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int j = npairs - 1 - 64 * (pc + r * nwm) - lane;
+        if (j < jl) continue;
 #pragma unroll
         for (int b = 0; b < MB; ++b) {
             double nre = E[r][b][0] + O[r][b][0], nim = E[r][b][1] + O[r][b][1];
             double sre = E[r][b][0] - O[r][b][0], sim = E[r][b][1] - O[r][b][1];
             if (m == 0) nim = sim = 0.0;  // Im a_l0 is ignored
-            OutT* o = out + b * out_map_stride;
-            if (FUSED) {
-                OutT* col = o + (int64_t)m * out_row_stride;
-                col[j] = make_out<OutT>(nre, nim);
-                if (j >= 1 && j <= nr - 2) col[nt - j] = make_out<OutT>(sgn * nre, sgn * nim);
-                if (js != j) {
-                    col[js] = make_out<OutT>(sre, sim);
-                    if (js >= 1 && js <= nr - 2) col[nt - js] = make_out<OutT>(sgn * sre, sgn * sim);
-                }
-            } else {
-                o[(int64_t)j * out_row_stride + m] = make_out<OutT>(nre, nim);
-                if (js != j) o[(int64_t)js * out_row_stride + m] = make_out<OutT>(sre, sim);
-            }
+            put(b, j, nre, nim, sre, sim);
         }
     }
 }
@@ -797,18 +858,11 @@ __global__ __launch_bounds__(kAdjWaves * 64, DET ? 3 : 4) void k_legendre_adj(
 // barriers, no waits between waves: a wave is on its own and adds its sums into the zeroed output
 // with FP64 atomics (or writes them to its partial array, see part_stride).
 //
-// Work split: the live pairs (from jlive[m] on) are cut into sub-blocks of 64 neighbours, counted from
-// the equator; the fewest waves that hold them at R per wave take them in turn, so that the waves
-// of a block (one m) are equally long: waves of unlike length, or blocks of unlike weight in a fixed
-// order, leave SIMDs and shader engines idle (the same work in blocks of 4 waves and 1 wave by turns
-// took 1.24 instead of 0.8 ms at lmax 2047, one map).  A sub-block runs in the cheapest of three
-// forms: every pair scaled (the recurrence only), some scaled (each value times 1 or 0), none.  The
-// rescale test is made once per chunk: eight steps grow a value by less than 2^56, so a scaled value
-// stays below 2^112 and is dropped below 2^-144.
+// Work split, exponent range and loops as in the synthesis (a chunk is 8 values of l here too).
 //
-// Bound by the FP64 VALU: 5 R instructions per l and wave, and about 10 for the sums.  One map at
-// lmax 2047 / 4095: 0.62 / 5.4 ms against 1.13 / 7.2 ms of the kernel above.  (The same for two
-// maps, 7 R instructions and four MFMAs per l, took 1.21 / 10.4 against 1.12 / 7.3 ms.)
+// Bound by the FP64 VALU: 5 R instructions per l and wave, and about 6 for the sums.  One map at
+// lmax 1023 / 2047 / 4095: 0.13 / 0.60 / 3.75 ms against 0.20 / 1.13 / 7.2 ms of the kernel above.  (The
+// same for two maps, 7 R instructions and four MFMAs per l, was slower than that kernel.)
 // ------------------------------------------------------------------------------------
 
 // the double of the lane that DPP control CTRL names (within rows of 16 lanes)
@@ -837,23 +891,21 @@ __device__ inline double wave_rows(const double (&q)[4], int x)
     return v;
 }
 
-constexpr int kOneWaves = 8;  // most waves per block
-
 template <int R, bool FUSED, typename InT>
-__global__ __launch_bounds__(64 * kOneWaves) void k_legendre_adj_one(
+__global__ __launch_bounds__(64 * kSubWaves) void k_legendre_adj_one(
     const InT* __restrict__ in, int64_t in_row_stride, double* __restrict__ alm, int64_t part_stride,
-    int nbx, int lmax, int mmax,
+    int lmax, int mmax,
     const double2* __restrict__ rec, const double* __restrict__ cm_mant,
     const int* __restrict__ cm_exp, const int* __restrict__ jlive, int nr, int nt)
 {
     constexpr int LC = 8;  // l values between two flushes: 2 LC / 4 = 4 registers of sums
-    __shared__ float pf_sink[kOneWaves][64];
-    int m, rb;
-    xcd_block(blockIdx.x, nbx, m, rb);
-    if (m > mmax) return;
+    __shared__ float pf_sink[kSubWaves][64];
     const int npairs = (nr + 1) / 2;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int pc = rb * (blockDim.x >> 6) + wave;
+    const SubGrid sg(npairs, R);
+    int m, pc;
+    sg.place(blockIdx.x, wave, mmax, m, pc);
+    if (m > mmax) return;
     const int jl = jlive[m];
     const int nsub = (npairs - jl + 63) >> 6, nwm = (nsub + R - 1) / R;
     if (pc >= nwm) return;
@@ -866,8 +918,7 @@ __global__ __launch_bounds__(64 * kOneWaves) void k_legendre_adj_one(
     // one step early: the step (0, -1) into l = m gives lam_mm from vp = lam_mm, vc = 0
     double H[R][2][2], y[R], vc[R], vp[R];
     int k[R];
-    enum { kNone, kDead, kMixed, kPlain };  // no pairs; all, some, none of them scaled
-    int form[R];
+    bool has[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int sub = pc + r * nwm;
@@ -908,11 +959,9 @@ __global__ __launch_bounds__(64 * kOneWaves) void k_legendre_adj_one(
             vp[r] = 0.0;
             k[r] = 0;
         }
-        form[r] = sub >= nsub                          ? kNone
-                  : !__any(k[r] > 0)                   ? kPlain
-                  : __any(valid && k[r] == 0)          ? kMixed
-                                                       : kDead;
+        has[r] = vp[r] != 0.0;
     }
+    int st = sub_state<R>(0, k, has);
     // selector rows: sel[i] is 1 in the lanes of row i of the A operand
     double sel[4];
 #pragma unroll
@@ -927,80 +976,51 @@ __global__ __launch_bounds__(64 * kOneWaves) void k_legendre_adj_one(
     unsigned pf_keep = 0;
     const unsigned lds_sink = __builtin_amdgcn_readfirstlane(
         (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)pf_sink[wave]);
-    int pf_at = m;
+    int pf_at = m, pf_off;
+    const double2* pf_line = touch_line<0>(rec, nullptr, 0, moff, lane, pf_off);
 
     // a chunk's coefficients are fetched while the chunk before runs; the table is padded past its
     // end, and steps past lmax run on whatever follows (finite coefficients; their sums are not
     // written)
-    double2 cn[LC];
-    auto fetch = [&](int l0) {
+    auto fetch = [&](double2 (&cn)[LC], int l0) {
 #pragma unroll
         for (int i = 0; i < LC; ++i)
             cn[i] = make_double2(crec[2 * (moff + l0 + i)], crec[2 * (moff + l0 + i) + 1]);
     };
-    fetch(m);
-    cn[0] = make_double2(0.0, -1.0);
     int l0 = m;
-    // The sub-blocks come into range in order (the equator first): one loop per number NP of
-    // sub-blocks in range, left when the next one is.
-    auto phase = [&](auto np) {
-        constexpr int NP = decltype(np)::value;
+    auto loop = [&](auto np, auto nm) {
+        constexpr int NP = decltype(np)::value, NM = decltype(nm)::value;
+        double2 cn[LC];
+        fetch(cn, min(l0, lmax));
+        if (l0 == m) cn[0] = make_double2(0.0, -1.0);
         for (; l0 <= lmax; l0 += LC) {
             if (l0 >= pf_at) {
-                pf_keep ^=
-                    prefetch_coeffs<0>(rec, nullptr, 0, moff, lmax, l0 + kPfStep, lane, lds_sink);
+                pf_keep ^= touch_coeffs(pf_line, pf_off, l0 + kPfStep, lmax, lds_sink);
                 pf_at = l0 + kPfStep;
             }
             double2 cc[LC];
 #pragma unroll
             for (int i = 0; i < LC; ++i) cc[i] = cn[i];
-            fetch(min(l0 + LC, lmax));
-            double t[LC][2];
-            bool any = NP > 0;
-            auto step = [&](int r, int i) {
-                const double vn = rec_step(cc[i], y[r], vc[r], vp[r]);
-                vp[r] = vc[r];
-                vc[r] = vn;
-                return vn;
-            };
+            fetch(cn, min(l0 + LC, lmax));
+            double t[LC][2], f[R];
+#pragma unroll
+            for (int r = NP; r < NM; ++r) f[r] = k[r] == 0 ? 1.0 : 0.0;
 #pragma unroll
             for (int i = 0; i < LC; ++i) {
+                t[i][0] = t[i][1] = 0.0;
 #pragma unroll
-                for (int e = 0; e < 2; ++e) t[i][e] = 0.0;
-#pragma unroll
-                for (int r = 0; r < NP; ++r) {
-                    const double v = step(r, i);
+                for (int r = 0; r < R; ++r) {
+                    const double vn = rec_step(cc[i], y[r], vc[r], vp[r]);
+                    vp[r] = vc[r];
+                    vc[r] = vn;
+                    if (r >= NM) continue;
+                    const double v = r < NP ? vn : vn * f[r];
 #pragma unroll
                     for (int e = 0; e < 2; ++e)
                         t[i][e] = r == 0 ? v * H[0][i & 1][e] : fma(v, H[r][i & 1][e], t[i][e]);
                 }
             }
-#pragma unroll
-            for (int r = NP; r < R; ++r) {
-                if (form[r] == kNone) continue;
-                if (form[r] == kDead) {
-#pragma unroll
-                    for (int i = 0; i < LC; ++i) step(r, i);
-                } else {
-                    const double f = k[r] == 0 ? 1.0 : 0.0;
-#pragma unroll
-                    for (int i = 0; i < LC; ++i) {
-                        const double v = step(r, i) * f;
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) t[i][e] = fma(v, H[r][i & 1][e], t[i][e]);
-                    }
-                    any = true;
-                }
-                const bool big = (k[r] > 0) && fmax(fabs(vc[r]), fabs(vp[r])) >= kBig;
-                const double sc = big ? kUnit : 1.0;
-                vp[r] *= sc;
-                vc[r] *= sc;
-                k[r] -= big ? 1 : 0;
-                form[r] = !__any(k[r] > 0)                      ? kPlain
-                          : __any(k[r] == 0 && vc[r] != 0.0)    ? kMixed
-                                                                : kDead;
-            }
-            if (any || part_stride != 0) {
+            if (NM > 0 || part_stride != 0) {
                 double q[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                 for (int i = 0; i < LC; ++i)
@@ -1018,19 +1038,22 @@ __global__ __launch_bounds__(64 * kOneWaves) void k_legendre_adj_one(
                         unsafeAtomicAdd(o, v);
                 }
             }
-            if (NP < R && form[NP < R ? NP : 0] == kPlain) {
-                l0 += LC;
-                break;
+            if constexpr (NP < R) {
+#pragma unroll
+                for (int r = NP; r < R; ++r) {
+                    rescale(vc[r], vp[r], k[r]);
+                    has[r] = vc[r] != 0.0 || vp[r] != 0.0;
+                }
+                const int now = sub_state<R>(NP, k, has);
+                if (now > NP * 8 + NM) {
+                    st = now;
+                    l0 += LC;
+                    break;
+                }
             }
         }
     };
-    if (form[0] != kPlain) phase(std::integral_constant<int, 0>());
-    if constexpr (R > 1) if (form[1] != kPlain) phase(std::integral_constant<int, 1>());
-    if constexpr (R > 2) if (form[2] != kPlain) phase(std::integral_constant<int, 2>());
-    if constexpr (R > 3) if (form[3] != kPlain) phase(std::integral_constant<int, 3>());
-    if constexpr (R > 4) if (form[4] != kPlain) phase(std::integral_constant<int, 4>());
-    if constexpr (R > 5) if (form[5] != kPlain) phase(std::integral_constant<int, 5>());
-    phase(std::integral_constant<int, R>());
+    run_states<R>(st, loop);
     // no LDS-DMA write may be in flight when the workgroup's LDS is released
     asm volatile("s_waitcnt vmcnt(0)" ::"v"(pf_keep) : "memory");
 }
@@ -1074,105 +1097,88 @@ __global__ void k_adj_reduce(const double2* __restrict__ part, int npc, int nmap
 
 }  // namespace
 
-int synth_pairs_per_lane(int npairs) { return npairs >= 1024 ? 2 : 1; }
-int synth_scaled_pairs_per_lane(int npairs) { return synth_pairs_per_lane(npairs); }
+namespace {
+
+// Two sub-blocks per wave share its coefficient loads and loop, one makes twice the waves and leaves
+// the scalar registers to longer fetches.  R = 1 / 2 in us: four maps at 65 pairs (lmax 127) 18 / 25, at
+// 129 34 / 36, at 257 80 / 67, at 2049 7485 / 6401; one map at 257 31 / 36, at 513 84 / 85, at 1025
+// 470 / 432, at 2049 2950 / 2573; two maps at 513 108 / 128, at 1025 555 / 599, at 2049 3875 / 3934.
+// (More than two per wave: spilled scalar registers.)
+int synth_pairs_per_lane(int npairs, int mb)
+{
+    if (mb == 2) return 1;
+    return npairs <= (mb == 4 ? 160 : 640) ? 1 : 2;
+}
+
+template <int MB, int R, bool FUSED, typename OutT>
+int launch_synth(const nusht_plan_s* p, const double2* alm, OutT* out, int groups,
+                 int64_t map_stride, int64_t row_stride, hipStream_t s)
+{
+    const nusht_geometry& g = p->g;
+    const int npairs = (g.nrings + 1) / 2;
+    const SubGrid sg(npairs, R);
+    const int mpad = (g.mmax + 1 + 7) / 8 * 8;
+    hipLaunchKernelGGL((k_legendre_synth<MB, R, FUSED, OutT>), dim3(sg.extra + sg.nbx * mpad, groups),
+                       dim3(64 * sg.wpb), 0, s, alm, g.nalm, g.lmax, g.mmax, p->rec, p->cm_mant,
+                       p->cm_exp, p->jlive, g.nrings, g.ntorus, out, map_stride, row_stride);
+    NUSHT_HIP(hipGetLastError());
+    return NUSHT_OK;
+}
+
+template <int MB, bool FUSED, typename OutT>
+int launch_synth_r(const nusht_plan_s* p, const double2* alm, OutT* out, int groups,
+                   int64_t map_stride, int64_t row_stride, hipStream_t s)
+{
+    if constexpr (MB != 2)
+        if (synth_pairs_per_lane((p->g.nrings + 1) / 2, MB) == 2)
+            return launch_synth<MB, 2, FUSED, OutT>(p, alm, out, groups, map_stride, row_stride, s);
+    return launch_synth<MB, 1, FUSED, OutT>(p, alm, out, groups, map_stride, row_stride, s);
+}
+
+template <bool FUSED, typename OutT>
+int launch_synth_maps(const nusht_plan_s* p, const double2* alm, OutT* out, int nmaps,
+                      int64_t map_stride, int64_t row_stride, hipStream_t s)
+{
+    // groups of four maps, then of two, then one
+    for (int b = 0; b < nmaps;) {
+        const int left = nmaps - b, mb = left >= 4 ? 4 : (left >= 2 ? 2 : 1), groups = left / mb;
+        const double2* a = alm + (int64_t)b * p->g.nalm;
+        OutT* o = out + (int64_t)b * map_stride;
+        if (mb == 4)
+            NUSHT_TRY((launch_synth_r<4, FUSED, OutT>(p, a, o, groups, map_stride, row_stride, s)));
+        else if (mb == 2)
+            NUSHT_TRY((launch_synth_r<2, FUSED, OutT>(p, a, o, groups, map_stride, row_stride, s)));
+        else
+            NUSHT_TRY((launch_synth_r<1, FUSED, OutT>(p, a, o, groups, map_stride, row_stride, s)));
+        b += groups * mb;
+    }
+    return NUSHT_OK;
+}
+
+}  // namespace
 
 int launch_legendre_synth(const nusht_plan_s* p, const double* alm, void* out, int nmaps,
                           int fused, int out_f32, hipStream_t s)
 {
     const nusht_geometry& g = p->g;
-    const int npairs = (g.nrings + 1) / 2;
-    // both instances take two ring pairs per lane once there are enough pairs to fill the
-    // waves (one pair per lane in the scaled instance, which halves the spread of the scaled
-    // phases' lengths across a wave, measured slower at C3: 7.41 against 7.07 ms)
-    const int R = synth_pairs_per_lane(npairs);
-    const int RS = synth_scaled_pairs_per_lane(npairs);
-    auto shape = [&](int r, int& bx, int& threads) {
-        const int waves_needed = (npairs + 64 * r - 1) / (64 * r);
-        const int wpb = waves_needed >= 4 ? 4 : waves_needed;
-        threads = 64 * wpb;
-        bx = (waves_needed + wpb - 1) / wpb;
-    };
-    int bxp, thp, bxs, ths;
-    shape(R, bxp, thp);
-    shape(RS, bxs, ths);
-    const int64_t nalm = g.nalm;
     const double2* a = reinterpret_cast<const double2*>(alm);
-    int64_t map_stride, row_stride;
     if (fused) {
-        row_stride = g.ntorus;
-        map_stride = (int64_t)(g.mmax + 1) * g.ntorus;
-    } else {
-        row_stride = g.nphi / 2 + 1;
-        map_stride = (int64_t)g.nrings * row_stride;
+        const int64_t row = g.ntorus, map = (int64_t)(g.mmax + 1) * g.ntorus;
+        if (out_f32)
+            return launch_synth_maps<true>(p, a, reinterpret_cast<float2*>(out), nmaps, map, row, s);
+        return launch_synth_maps<true>(p, a, reinterpret_cast<double2*>(out), nmaps, map, row, s);
     }
-    const int mpad = (g.mmax + 1 + 7) / 8 * 8;
-    // the two instances write disjoint ring pairs: the plain one runs on the plan's side
-    // stream, forked from and joined back into the call's stream, so that each fills the
-    // other's tail
-    hipStream_t sp = p->side ? p->side : s;
-    if (sp != s) {
-        NUSHT_HIP(hipEventRecord(p->fork_ev, s));
-        NUSHT_HIP(hipStreamWaitEvent(sp, p->fork_ev, 0));
-    }
-    int b = 0;
-    while (b < nmaps) {
-        const int left = nmaps - b;
-        const int mb = left >= 4 ? 4 : (left >= 2 ? 2 : 1);
-        const int groups = left / mb;
-        const double2* ab = a + (int64_t)b * nalm;
-#define SYN1(MBV, RV, F, OT, SC, BX, TH)                                                         \
-    hipLaunchKernelGGL((k_legendre_synth<MBV, RV, F, OT, SC>), dim3(BX * mpad, groups),          \
-                       dim3(TH), 0, SC ? s : sp, ab, nalm, g.lmax, g.mmax, BX, p->rec, p->cm_mant, \
-                       p->cm_exp, p->jlive, p->jscale, g.nrings, g.ntorus,                        \
-                       reinterpret_cast<OT*>(out) + (int64_t)b * map_stride, map_stride,          \
-                       row_stride)
-#define SYNR(MBV, F, OT)                              \
-    if (R == 2) {                                     \
-        SYN1(MBV, 2, F, OT, false, bxp, thp);         \
-    } else {                                          \
-        SYN1(MBV, 1, F, OT, false, bxp, thp);         \
-    }                                                 \
-    if (RS == 2) {                                    \
-        SYN1(MBV, 2, F, OT, true, bxs, ths);          \
-    } else {                                          \
-        SYN1(MBV, 1, F, OT, true, bxs, ths);          \
-    }
-        if (fused && out_f32) {
-            if (mb == 4) { SYNR(4, true, float2) }
-            else if (mb == 2) { SYNR(2, true, float2) }
-            else { SYNR(1, true, float2) }
-        } else if (fused) {
-            if (mb == 4) { SYNR(4, true, double2) }
-            else if (mb == 2) { SYNR(2, true, double2) }
-            else { SYNR(1, true, double2) }
-        } else {
-            if (mb == 4) { SYNR(4, false, double2) }
-            else if (mb == 2) { SYNR(2, false, double2) }
-            else { SYNR(1, false, double2) }
-        }
-#undef SYNR
-#undef SYN1
-        NUSHT_HIP(hipGetLastError());
-        b += groups * mb;
-    }
-    if (sp != s) {
-        NUSHT_HIP(hipEventRecord(p->join_ev, sp));
-        NUSHT_HIP(hipStreamWaitEvent(s, p->join_ev, 0));
-    }
-    return NUSHT_OK;
+    const int64_t row = g.nphi / 2 + 1, map = (int64_t)g.nrings * row;
+    return launch_synth_maps<false>(p, a, reinterpret_cast<double2*>(out), nmaps, map, row, s);
 }
 
 namespace {
 
 // Ring pairs per lane of the one-map adjoint: more of them share a wave's sums and coefficient
-// loads, fewer make more waves.  At 257 pairs (lmax 511) R = 1 / 2 / 4 took 55 / 50 / 60 us, at 513
-// 205 / 142 / 167, at 769 563 / 384 / 339, at 1025 (R = 2 / 4 / 6) 976 / 634 / 625, at 2049 (5327) /
-// 6222 / 5401: with R = 4 the 9 waves need two blocks per m.
-int one_map_pairs_per_lane(int npairs)
-{
-    return npairs <= 128 ? 1 : npairs <= 640 ? 2 : npairs <= 1024 ? 4 : 6;
-}
+// loads, fewer make more waves.  R = 1 / 2 / 4 / 6 in us: at 257 pairs (lmax 511) 39 / 47 / 54 / 68, at 513
+// 169 / 132 / 140 / 174, at 769 478 / 396 / 324 / 305, at 1025 952 / 726 / 598 / 595, at 2049 6432 / 4737 /
+// 3748 / 3997.
+int one_map_pairs_per_lane(int npairs) { return npairs <= 320 ? 1 : npairs <= 640 ? 2 : 4; }
 
 // room for the partial sums of deterministic plans
 int ensure_partials(nusht_plan_s* p, size_t need, hipStream_t s)
@@ -1196,9 +1202,7 @@ int launch_adj_one(nusht_plan_s* p, const void* in, double* alm, int64_t row_str
     const int npairs = (g.nrings + 1) / 2;
     const int R = one_map_pairs_per_lane(npairs);
     const int nw = (npairs + 64 * R - 1) / (64 * R);  // most waves of one m
-    // blocks of equal weight: one block per m up to kOneWaves waves, else the fewest equal ones
-    const int nbx = (nw + kOneWaves - 1) / kOneWaves;
-    const int wpb = (nw + nbx - 1) / nbx;
+    const SubGrid sg(npairs, R);
     const int mpad = (g.mmax + 1 + 7) / 8 * 8;
     double* target = alm;
     int64_t part_stride = 0;
@@ -1208,18 +1212,16 @@ int launch_adj_one(nusht_plan_s* p, const void* in, double* alm, int64_t row_str
         target = p->adj_part;
     }
 #define ONE(RV)                                                                                  \
-    hipLaunchKernelGGL((k_legendre_adj_one<RV, FUSED, InT>), dim3(nbx * mpad), dim3(64 * wpb), 0, \
-                       s, reinterpret_cast<const InT*>(in), row_stride, target, part_stride, nbx, \
-                       g.lmax, g.mmax, p->rec, p->cm_mant, p->cm_exp, p->jlive, g.nrings,        \
+    hipLaunchKernelGGL((k_legendre_adj_one<RV, FUSED, InT>), dim3(sg.extra + sg.nbx * mpad),         \
+                       dim3(64 * sg.wpb), 0, s, reinterpret_cast<const InT*>(in), row_stride,     \
+                       target, part_stride, g.lmax, g.mmax, p->rec, p->cm_mant, p->cm_exp, p->jlive, g.nrings,        \
                        g.ntorus)
     if (R == 1)
         ONE(1);
     else if (R == 2)
         ONE(2);
-    else if (R == 4)
-        ONE(4);
     else
-        ONE(6);
+        ONE(4);
 #undef ONE
     NUSHT_HIP(hipGetLastError());
     if (p->deterministic) {

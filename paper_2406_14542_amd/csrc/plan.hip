@@ -720,36 +720,6 @@ static int build_tables(nusht_plan_s* p)
             });
         for (auto& th : pool) th.join();
     }
-    // first ring pair whose lam_mm = c_m sin^m(theta_j) is at least 2^-190 (sin theta_j grows
-    // with j up to the equator); no lam_lm of such a pair needs the power-of-two scale
-    std::vector<int> jsc(M + 1, 0);
-    {
-        const int npairs = (g.nrings + 1) / 2;
-        for (int m = 0; m <= M; ++m) {
-            const double lc = (double)ce[m] + std::log2(std::fabs(cm[m]));
-            int j = 0;
-            if (m > 0) {
-                // bisection on the monotone log2 lam_mm(theta_j) >= -190
-                int lo = 0, hi = npairs;
-                while (lo < hi) {
-                    const int mid = (lo + hi) / 2;
-                    const double sth = std::sin(M_PI * (double)mid / (double)(g.nrings - 1));
-                    const bool ok = sth > 0.0 && lc + m * std::log2(sth) >= -190.0;
-                    if (ok)
-                        hi = mid;
-                    else
-                        lo = mid + 1;
-                }
-                j = lo;
-            }
-            if (j < jl[m]) j = jl[m];
-            // the synthesis splits its waves at jsc: a multiple of the spans of both of its
-            // instances' waves (powers of two)
-            const int span = 64 * std::max(synth_pairs_per_lane(npairs),
-                                            synth_scaled_pairs_per_lane(npairs));
-            jsc[m] = (j + span - 1) / span * span;
-        }
-    }
     // deconvolution: h / psi^(k) = 2 / (w I(k)), with the 1/N_t of the theta transform
     std::vector<double> i1, i2;
     es_fourier(g.beta, g.width * M_PI / g.n1, L, i1);
@@ -790,8 +760,6 @@ static int build_tables(nusht_plan_s* p)
     NUSHT_TRY(dmalloc(&p->dec1f, L + 1));
     NUSHT_TRY(dmalloc(&p->dec2f, M + 1));
     NUSHT_TRY(dmalloc(&p->jlive, M + 1));
-    NUSHT_TRY(dmalloc(&p->jscale, M + 1));
-    NUSHT_HIP(hipMemcpy(p->jscale, jsc.data(), jsc.size() * sizeof(int), hipMemcpyHostToDevice));
     NUSHT_HIP(hipMemcpy(p->jlive, jl.data(), jl.size() * sizeof(int), hipMemcpyHostToDevice));
     p->jlive_host = jl;
     NUSHT_HIP(hipMemcpy(p->rec, rec.data(), rec.size() * sizeof(double), hipMemcpyHostToDevice));
@@ -876,7 +844,7 @@ void nusht_destroy(nusht_plan_t p)
                     p->slot_off,  p->slot_tile,
                     p->tile_slot, p->boff, p->brec, p->dflag, p->dstatus, p->X,     p->Y,         p->W,   p->Z,
                     p->fftwork,   p->rowtw, p->thetatw,
-                    p->red,      p->jlive,  p->jscale, p->adj_part, p->es_coef, p->es_coeff,
+                    p->red,      p->jlive,  p->adj_part, p->es_coef, p->es_coeff,
                     p->spin_rec, p->spin_km, p->spin_ke, p->spin_jlive};
     for (void* b : bufs)
         if (b) hipFree(b);
@@ -885,9 +853,6 @@ void nusht_destroy(nusht_plan_t p)
             if (p->ev[c][i][0]) hipEventDestroy(p->ev[c][i][0]);
             if (p->ev[c][i][1]) hipEventDestroy(p->ev[c][i][1]);
         }
-    if (p->fork_ev) hipEventDestroy(p->fork_ev);
-    if (p->join_ev) hipEventDestroy(p->join_ev);
-    if (p->side) hipStreamDestroy(p->side);
     hipSetDevice(cur);
     delete p;
 }
@@ -921,12 +886,6 @@ int nusht_plan_ex(int lmax, int mmax, int64_t npts, const double* theta, const d
         if ((rc = build_band_records(p, s))) break;
         p->g.ntiles_used = p->nslots;
         if ((rc = create_fft_plans(p))) break;
-        if (hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking) != hipSuccess ||
-            hipEventCreateWithFlags(&p->fork_ev, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&p->join_ev, hipEventDisableTiming) != hipSuccess) {
-            rc = NUSHT_EDEVICE;
-            break;
-        }
         if (p->timing) {
             for (int c = 0; c < nusht_plan_s::kTimingSlots && rc == NUSHT_OK; ++c)
                 for (int i = 0; i < ST_COUNT; ++i) {

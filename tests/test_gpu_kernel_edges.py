@@ -80,3 +80,23 @@ def test_one_map_adjoint(P, oracle_mod, lmax, mmax, mode, det):
         assert np.array_equal(p.adjoint(dev(d[4:])).cpu().numpy(), one)
         assert np.array_equal(five[4], one[0])
     p.status()
+
+
+@pytest.mark.parametrize("lmax,mmax,B,mode", [
+    (0, 0, 1, "fused"), (1, 1, 1, "fused"), (6, 6, 3, "paper"), (7, 3, 7, "fused"),
+    (8, 8, 4, "fused"), (126, 126, 2, "paper"), (127, 127, 4, "fused"), (319, 300, 4, "fused"),
+    (1279, 1279, 1, "fused"), (1280, 1280, 1, "fused"), (1280, 1279, 6, "fused"),
+    (2050, 2050, 4, "fused")])
+def test_synthesis_splits(P, oracle_mod, lmax, mmax, B, mode):
+    """The Legendre synthesis at the edges of its splits: fewer degrees than a chunk of 8, columns
+    of one degree, 64 pairs per sub-block, one and two sub-blocks per wave (up to 160 / 641 pairs),
+    batches that split into 4 + 2 + 1 maps; points down to 1e-4 from the poles.  Bound: the plan's
+    eps = 1e-12 times the margin of the other FP64 tests."""
+    print(f"[synthesis lmax={lmax} mmax={mmax} B={B} {mode}]", flush=True)
+    rng = np.random.default_rng(7 * lmax + B)
+    th, ph = inputs.uniform_points(rng, 53)
+    th[:2] = [1e-4, np.pi - 1e-4]
+    alm = inputs.red_alm(rng, lmax, mmax, B)
+    p = P.Plan(lmax, mmax, dev(th), dev(ph), 1e-12, dfs_mode=mode)
+    f = p.synthesis(dev(alm)).cpu().numpy()
+    assert rel(f, oracle_mod.synthesis(lmax, mmax, th, ph, alm)) <= 1e-11
