@@ -176,14 +176,18 @@ struct nusht_plan_s {
     nusht::FftPlan fine_rowa_c2r, fine_rowa_r2c;  // 1D over n2, batch fine_ra
     nusht::FftPlan fine_rowb_c2r, fine_rowb_r2c;  // 1D over n2, batch fine_rb (may be empty)
     int fine_ra = 0, fine_rb = 0;
-    // n2 / 2 = 2^K or 5 2^K: the phi pass runs in the library's own row kernels (rowfft.hip),
+    // n2 / 2 that fits in LDS: the phi pass runs in the library's own row kernels (rowfft.hip for
+    // 2^K and 5 2^K, mixfft.hip for every other length),
     // on row spectra of width mmax + 1 (no zero columns), instead of the rocFFT row plans.
     bool row_custom = false;
     void* rowtw = nullptr;  // [n2] e^{2 pi i k / n2} in the plan's FFT precision
-    // Fused mode with n1 = 2^K or 5 2^K up to 16384: the theta pass and the deconvolution run
-    // as one kernel per direction (rowfft.hip) instead of the rocFFT column plans and the pad /
-    // truncate kernels.
+    // Fused mode with n1 that fits in LDS (or 2^14): the theta pass and the deconvolution run
+    // as one kernel per direction (rowfft.hip, mixfft.hip) instead of the rocFFT column plans and
+    // the pad / truncate kernels.  theta_torus: that kernel holds the DFT over the doubled circle
+    // (F) as well.
     bool theta_custom = false;
+    bool theta_torus = false;
+    void* torustw = nullptr;  // [2 N_t] e^{2 pi i k / (2 N_t)} (theta_torus)
     void* thetatw = nullptr;  // [2 n1] e^{2 pi i k / (2 n1)} in the plan's FFT precision
 
     // Timing.
@@ -278,7 +282,7 @@ int launch_band_to_rows(const nusht_plan_s* p, const void* band, void* rows, int
 int launch_rows_to_band(const nusht_plan_s* p, const void* rows, int rw, void* band,
                         hipStream_t s, bool window_only = false);
 
-// ---- fine-grid row transforms for n2 / 2 = 2^K or 5 2^K (rowfft.hip) ----
+// ---- fine-grid row transforms (rowfft.hip: 2^K and 5 2^K, mixfft.hip: other lengths) ----
 bool rowfft_supported(const nusht_geometry& g);
 // window rows of one map: rows [n1][rw] (columns 0 .. mmax) <-> real fine grid [n1][n2]
 int launch_row_c2r(const nusht_plan_s* p, const void* rows, int64_t rw, void* fine, hipStream_t s);
@@ -286,6 +290,20 @@ int launch_row_r2c(const nusht_plan_s* p, const void* fine, void* rows, int64_t 
 // theta pass fused with the deconvolution, maps [0, nmaps): torus spectrum cs [b][mmax+1][N_t]
 // <-> band spectrum [b][mmax+1][n1] (window rows only)
 bool thetafft_supported(const nusht_geometry& g);
+// A length and its radices, four bits each, first pass lowest.
+struct MixLen {
+    int n, np;
+    unsigned long long code;
+    __host__ __device__ int radix(int p) const { return (int)(code >> (4 * p)) & 15; }
+};
+// the fused theta pass of this geometry also holds the DFT over the doubled circle
+bool thetafft_with_torus(const nusht_geometry& g);
+bool mixrow_supported(const nusht_geometry& g);
+bool mixtheta_supported(const nusht_geometry& g);
+int launch_mix_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, bool c2r,
+                   hipStream_t s);
+int launch_mix_theta(const nusht_plan_s* p, const void* in, void* out, int nmaps, bool inv,
+                     hipStream_t s);
 int launch_theta_inv(const nusht_plan_s* p, const void* cs, void* band, int nmaps, hipStream_t s);
 int launch_theta_fwd(const nusht_plan_s* p, const void* band, void* cs, int nmaps, hipStream_t s);
 

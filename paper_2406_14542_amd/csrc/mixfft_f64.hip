@@ -1,0 +1,18 @@
+// Row and column transforms of general lengths in FP64.
+#include "mixfft_impl.h"
+
+namespace nusht {
+
+int mix_row_f64(const nusht_plan_s* p, const MixLen& m, const void* in, void* out, int64_t rw,
+                bool c2r, hipStream_t s)
+{
+    return mix_row<double>(p, m, in, out, rw, c2r, s);
+}
+
+int mix_theta_f64(const nusht_plan_s* p, const MixLen& mt, const MixLen& mn, const void* in, void* out,
+                  int nmaps, bool inv, hipStream_t s)
+{
+    return mix_theta<double>(p, mt, mn, in, out, nmaps, inv, s);
+}
+
+}  // namespace nusht

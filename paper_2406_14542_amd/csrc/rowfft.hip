@@ -22,134 +22,11 @@
 // 16), reading the row straight from HBM in the first pass and writing it in the last: one
 // read and one write of each row, and only the M + 1 band columns of the spectrum are read
 // (C2R) or written (R2C).
+#include "fft_core.h"
 #include "internal.h"
 
 namespace nusht {
 namespace {
-
-template <typename T>
-struct Cx;
-template <>
-struct Cx<float> {
-    using type = float2;
-};
-template <>
-struct Cx<double> {
-    using type = double2;
-};
-
-template <typename C>
-__device__ inline C cmk(decltype(C::x) re, decltype(C::x) im)
-{
-    C r;
-    r.x = re;
-    r.y = im;
-    return r;
-}
-template <typename C>
-__device__ inline C cadd(C a, C b)
-{
-    return cmk<C>(a.x + b.x, a.y + b.y);
-}
-template <typename C>
-__device__ inline C csub(C a, C b)
-{
-    return cmk<C>(a.x - b.x, a.y - b.y);
-}
-template <typename C>
-__device__ inline C cmul(C a, C b)
-{
-    return cmk<C>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-// a * (DIR i)
-template <int DIR, typename C>
-__device__ inline C cmul_i(C a)
-{
-    return DIR > 0 ? cmk<C>(-a.y, a.x) : cmk<C>(a.y, -a.x);
-}
-
-// cos and sin of 2 pi e / 16
-__device__ constexpr double kCos16[16] = {
-    1.0, 0.92387953251128675613, 0.70710678118654752440, 0.38268343236508977173,
-    0.0, -0.38268343236508977173, -0.70710678118654752440, -0.92387953251128675613,
-    -1.0, -0.92387953251128675613, -0.70710678118654752440, -0.38268343236508977173,
-    0.0, 0.38268343236508977173, 0.70710678118654752440, 0.92387953251128675613};
-__device__ constexpr double kSin16[16] = {
-    0.0, 0.38268343236508977173, 0.70710678118654752440, 0.92387953251128675613,
-    1.0, 0.92387953251128675613, 0.70710678118654752440, 0.38268343236508977173,
-    0.0, -0.38268343236508977173, -0.70710678118654752440, -0.92387953251128675613,
-    -1.0, -0.92387953251128675613, -0.70710678118654752440, -0.38268343236508977173};
-
-// a * e^{DIR 2 pi i e / 16}; e is a constant once the callers' loops are unrolled, so the
-// branches and the table lookups fold away
-template <int DIR, typename C>
-__device__ __forceinline__ C rot16(C a, int e)
-{
-    using T = decltype(C::x);
-    e &= 15;
-    if (e == 0) return a;
-    if (e == 4) return cmul_i<DIR>(a);
-    if (e == 8) return cmk<C>(-a.x, -a.y);
-    if (e == 12) return cmul_i<-DIR>(a);
-    return cmul(a, cmk<C>((T)kCos16[e], (T)(DIR * kSin16[e])));
-}
-
-// in-place DFT of R = 1, 2, 4, 5, 8 or 16 values, natural order in and out:
-// V[k] = sum_n v[n] e^{DIR 2 pi i n k / R}
-template <int R, int DIR, typename C>
-__device__ inline void dft(C (&v)[R])
-{
-    if constexpr (R == 2) {
-        const C a = v[0];
-        v[0] = cadd(a, v[1]);
-        v[1] = csub(a, v[1]);
-    } else if constexpr (R == 4) {
-        const C a0 = cadd(v[0], v[2]), a1 = csub(v[0], v[2]);
-        const C a2 = cadd(v[1], v[3]), a3 = cmul_i<DIR>(csub(v[1], v[3]));
-        v[0] = cadd(a0, a2);
-        v[2] = csub(a0, a2);
-        v[1] = cadd(a1, a3);
-        v[3] = csub(a1, a3);
-    } else if constexpr (R == 5) {
-        // V[k] = sum_n v[n] w^(n k), w = e^{DIR 2 pi i / 5}: pairs (1, 4) and (2, 3) share
-        // cos(2 pi / 5), cos(4 pi / 5) and sin(2 pi / 5), sin(4 pi / 5)
-        using T = decltype(C::x);
-        const T c1 = (T)0.30901699437494742410, c2 = (T)-0.80901699437494742410;
-        const T s1 = (T)0.95105651629515357212, s2 = (T)0.58778525229247312917;
-        const C t1 = cadd(v[1], v[4]), t2 = cadd(v[2], v[3]);
-        const C t3 = csub(v[1], v[4]), t4 = csub(v[2], v[3]);
-        const C a1 = cmk<C>(v[0].x + c1 * t1.x + c2 * t2.x, v[0].y + c1 * t1.y + c2 * t2.y);
-        const C a2 = cmk<C>(v[0].x + c2 * t1.x + c1 * t2.x, v[0].y + c2 * t1.y + c1 * t2.y);
-        const C b1 = cmul_i<DIR>(cmk<C>(s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y));
-        const C b2 = cmul_i<DIR>(cmk<C>(s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y));
-        v[0] = cadd(v[0], cadd(t1, t2));
-        v[1] = cadd(a1, b1);
-        v[4] = csub(a1, b1);
-        v[2] = cadd(a2, b2);
-        v[3] = csub(a2, b2);
-    } else if constexpr (R == 8 || R == 16) {
-        // R = 4 Q: n = Q n1 + n2, k = k1 + 4 k2; DFT_4 over n1, twiddle e^{DIR 2 pi i n2 k1 / R},
-        // DFT_Q over n2
-        constexpr int Q = R / 4;
-        C u[4][Q];
-#pragma unroll
-        for (int n2 = 0; n2 < Q; ++n2) {
-            C w[4] = {v[n2], v[Q + n2], v[2 * Q + n2], v[3 * Q + n2]};
-            dft<4, DIR>(w);
-#pragma unroll
-            for (int k1 = 0; k1 < 4; ++k1) u[k1][n2] = rot16<DIR>(w[k1], n2 * k1 * (16 / R));
-        }
-#pragma unroll
-        for (int k1 = 0; k1 < 4; ++k1) {
-            dft<Q, DIR>(u[k1]);
-#pragma unroll
-            for (int k2 = 0; k2 < Q; ++k2) v[k1 + 4 * k2] = u[k1][k2];
-        }
-    }
-}
-
-// LDS index with one pad slot per 16 entries (stride-16 accesses stay off one bank)
-__device__ inline int pad16(int i) { return i + (i >> 4); }
 
 // Transform length N = F 2^K, F = 1 or 5.  Passes: radix R0 (from HBM), for F = 5 a radix
 // R1 = 2^(K mod 4) pass when K mod 4 > 0, then NPASS16 radix-16 passes (the last one to HBM).
@@ -196,14 +73,6 @@ __device__ inline void load_twiddles(C (&w)[R], int j, int Ns, int N, const C* _
 #pragma unroll
         for (int r = 1; r < R; ++r) w[r].y = -w[r].y;
     }
-}
-
-// tw[k] read through the constant address space: for a wave-uniform k this is a scalar load
-template <typename T>
-__device__ inline typename Cx<T>::type tw_uniform(const typename Cx<T>::type* tw, int k)
-{
-    const __attribute__((address_space(4))) T* p = (const __attribute__((address_space(4))) T*)tw;
-    return cmk<typename Cx<T>::type>(p[2 * k], p[2 * k + 1]);
 }
 
 template <int R, typename C>
@@ -413,8 +282,6 @@ __global__ __launch_bounds__((RowShape<K, F>::NT)) void k_row_r2c(
 
 
 // ---- theta pass (band columns, complex, length n1 = 2^K) ----------------------------------
-
-__device__ inline int kappa_of(int i, int n) { return i <= n / 2 ? i : i - n; }
 
 // synthesis: torus spectrum cs[b][mu][t] (t < nt) -> band[b][mu][i], window rows only
 template <typename T, int K, int F>
@@ -723,20 +590,14 @@ static bool split_len(int n, int& K, int& F)
     return true;
 }
 
-// one transform of N complex values held in LDS (with the pad slots)
-template <typename T>
-constexpr bool lds_fits(int N)
-{
-    return (size_t)(N + N / 16) * 2 * sizeof(T) <= 150 * 1024;
-}
-
 // lengths the kernels are built for: 2^K (K = 5 .. 14) and 5 2^K (K = 4 .. 11)
 static bool len_supported(int K, int F)
 {
     return F == 1 ? (K >= 5 && K <= 14) : (K >= 4 && K <= 11);
 }
 
-bool rowfft_supported(const nusht_geometry& g)
+// rows of 2^K or 5 2^K: the kernels of this file; other lengths: mixfft.hip
+static bool row_pow2(const nusht_geometry& g)
 {
     const int n2 = g.n2;
     int K, F;
@@ -746,6 +607,8 @@ bool rowfft_supported(const nusht_geometry& g)
     if (!(g.dtype == NUSHT_MIXED ? lds_fits<float>(N) : lds_fits<double>(N))) return false;
     return g.mmax + 1 <= N;
 }
+
+bool rowfft_supported(const nusht_geometry& g) { return row_pow2(g) || mixrow_supported(g); }
 
 #define NUSHT_FK_CASE(FF, KK, ...) \
     case (FF) * 100 + (KK): { constexpr int FV = FF, KV = KK; __VA_ARGS__; } break;
@@ -801,11 +664,13 @@ int launch_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, hip
 
 int launch_row_c2r(const nusht_plan_s* p, const void* rows, int64_t rw, void* fine, hipStream_t s)
 {
+    if (!row_pow2(p->g)) return launch_mix_row(p, rows, fine, rw, true, s);
     return launch_row<true>(p, rows, fine, rw, s);
 }
 
 int launch_row_r2c(const nusht_plan_s* p, const void* fine, void* rows, int64_t rw, hipStream_t s)
 {
+    if (!row_pow2(p->g)) return launch_mix_row(p, fine, rows, rw, false, s);
     return launch_row<false>(p, fine, rows, rw, s);
 }
 
@@ -818,6 +683,11 @@ bool thetafft_supported(const nusht_geometry& g)
     // a complex column in LDS, or (FP64, 16384) real and imaginary parts in turn
     if (g.dtype == NUSHT_MIXED) return lds_fits<float>(n1);
     return lds_fits<double>(n1) || (F == 1 && K == 14);
+}
+
+bool thetafft_with_torus(const nusht_geometry& g)
+{
+    return rowfft_supported(g) && !thetafft_supported(g) && mixtheta_supported(g);
 }
 
 // columns whose complex values exceed the LDS (FP64, 16384) take the register-resident kernels
@@ -878,11 +748,13 @@ int launch_theta(const nusht_plan_s* p, const void* in, void* out, int nmaps, hi
 
 int launch_theta_inv(const nusht_plan_s* p, const void* cs, void* band, int nmaps, hipStream_t s)
 {
+    if (p->theta_torus) return launch_mix_theta(p, cs, band, nmaps, true, s);
     return launch_theta<true>(p, cs, band, nmaps, s);
 }
 
 int launch_theta_fwd(const nusht_plan_s* p, const void* band, void* cs, int nmaps, hipStream_t s)
 {
+    if (p->theta_torus) return launch_mix_theta(p, band, cs, nmaps, false, s);
     return launch_theta<false>(p, band, cs, nmaps, s);
 }
 

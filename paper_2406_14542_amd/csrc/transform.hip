@@ -91,6 +91,32 @@ void free_fft(FftPlan& f)
 
 int ensure_ring_plans(nusht_plan_s* p);
 
+// [n] e^{2 pi i k / n} on the device in the plan's FFT precision, rounded once from long double
+int make_twiddles(int n, bool f32, void** out)
+{
+    std::vector<double> tw(f32 ? 0 : 2 * (size_t)n);
+    std::vector<float> twf(f32 ? 2 * (size_t)n : 0);
+    for (int k = 0; k < n; ++k) {
+        const long double a = 2.0L * 3.14159265358979323846264338327950288L * k / n;
+        const long double c = cosl(a), s = sinl(a);
+        if (f32) {
+            twf[2 * k] = (float)c;
+            twf[2 * k + 1] = (float)s;
+        } else {
+            tw[2 * k] = (double)c;
+            tw[2 * k + 1] = (double)s;
+        }
+    }
+    const size_t tb = 2 * (size_t)n * (f32 ? sizeof(float) : sizeof(double));
+    if (hipMalloc(out, tb) != hipSuccess) {
+        set_last_error("nusht_plan", "device allocation failed");
+        return NUSHT_ENOMEM;
+    }
+    NUSHT_HIP(hipMemcpy(*out, f32 ? (const void*)twf.data() : (const void*)tw.data(), tb,
+                        hipMemcpyHostToDevice));
+    return NUSHT_OK;
+}
+
 }  // namespace
 
 int create_fft_plans(nusht_plan_s* p)
@@ -132,28 +158,12 @@ int create_fft_plans(nusht_plan_s* p)
     const size_t fw = (size_t)g.n2 / 2 + 1;
     const size_t ncol = (size_t)g.mmax + 1;
     p->row_custom = rowfft_supported(g);
-    p->theta_custom = thetafft_supported(g);
+    p->theta_torus = thetafft_with_torus(g);
+    p->theta_custom = p->theta_torus || thetafft_supported(g);
     if (p->theta_custom) {
-        // twiddles of the fused theta pass: [2 n1] e^{2 pi i k / (2 n1)}, rounded once from
-        // long double (the row kernels' table convention for an n1-point transform)
-        const int n = 2 * g.n1;
-        const bool f32 = g.dtype == NUSHT_MIXED;
-        std::vector<double> tw(2 * (size_t)n);
-        std::vector<float> twf(2 * (size_t)n);
-        for (int k = 0; k < n; ++k) {
-            const long double a = 2.0L * 3.14159265358979323846264338327950288L * k / n;
-            tw[2 * k] = (double)cosl(a);
-            tw[2 * k + 1] = (double)sinl(a);
-            twf[2 * k] = (float)cosl(a);
-            twf[2 * k + 1] = (float)sinl(a);
-        }
-        const size_t tb = 2 * (size_t)n * (f32 ? sizeof(float) : sizeof(double));
-        if (hipMalloc(&p->thetatw, tb) != hipSuccess) {
-            set_last_error("nusht_plan", "device allocation failed");
-            return NUSHT_ENOMEM;
-        }
-        NUSHT_HIP(hipMemcpy(p->thetatw, f32 ? (const void*)twf.data() : (const void*)tw.data(),
-                            tb, hipMemcpyHostToDevice));
+        NUSHT_TRY(make_twiddles(2 * g.n1, g.dtype == NUSHT_MIXED, &p->thetatw));
+        if (p->theta_torus)
+            NUSHT_TRY(make_twiddles(2 * g.ntorus, g.dtype == NUSHT_MIXED, &p->torustw));
     } else {
         NUSHT_TRY(make_fft_1d(p->fine_col_inv, rocfft_transform_type_complex_inverse, prec, g.n1,
                               ncol, 1, g.n1, 1, g.n1, rocfft_placement_inplace));
@@ -161,25 +171,7 @@ int create_fft_plans(nusht_plan_s* p)
                               ncol, 1, g.n1, 1, g.n1, rocfft_placement_inplace));
     }
     if (p->row_custom) {
-        // twiddle table of the row kernels, rounded once from long double
-        const int n2 = g.n2;
-        const bool f32 = g.dtype == NUSHT_MIXED;
-        std::vector<double> tw(2 * (size_t)n2);
-        std::vector<float> twf(2 * (size_t)n2);
-        for (int k = 0; k < n2; ++k) {
-            const long double a = 2.0L * 3.14159265358979323846264338327950288L * k / n2;
-            tw[2 * k] = (double)cosl(a);
-            tw[2 * k + 1] = (double)sinl(a);
-            twf[2 * k] = (float)cosl(a);
-            twf[2 * k + 1] = (float)sinl(a);
-        }
-        const size_t tb = 2 * (size_t)n2 * (f32 ? sizeof(float) : sizeof(double));
-        if (hipMalloc(&p->rowtw, tb) != hipSuccess) {
-            set_last_error("nusht_plan", "device allocation failed");
-            return NUSHT_ENOMEM;
-        }
-        NUSHT_HIP(hipMemcpy(p->rowtw, f32 ? (const void*)twf.data() : (const void*)tw.data(), tb,
-                            hipMemcpyHostToDevice));
+        NUSHT_TRY(make_twiddles(g.n2, g.dtype == NUSHT_MIXED, &p->rowtw));
     } else {
         NUSHT_TRY(make_fft_1d(p->fine_rowa_c2r, rocfft_transform_type_real_inverse, prec, g.n2,
                               p->fine_ra, 1, fw, 1, g.n2, rocfft_placement_notinplace));
@@ -192,7 +184,9 @@ int create_fft_plans(nusht_plan_s* p)
         NUSHT_TRY(make_fft_1d(p->fine_rowb_r2c, rocfft_transform_type_real_forward, prec, g.n2,
                               p->fine_rb, 1, g.n2, 1, fw, rocfft_placement_notinplace));
     }
-    if (g.dfs_mode == NUSHT_DFS_FUSED) {
+    if (p->theta_torus) {
+        // F is part of the theta kernels
+    } else if (g.dfs_mode == NUSHT_DFS_FUSED) {
         const size_t len = (size_t)g.ntorus;
         NUSHT_TRY(make_fft(p->theta_fwd, rocfft_transform_type_complex_forward, prec, 1, &len,
                            (size_t)g.mmax + 1, rocfft_placement_inplace));
@@ -406,7 +400,7 @@ int synthesis_to_fine(nusht_plan_s* p, const double* alm, int nmaps, hipStream_t
         stage_end(p, ST_LEGENDRE, s);
         stage_begin(p, ST_TORUS_FFT, s);
         const size_t cstride = (size_t)(g.mmax + 1) * g.ntorus * 2 * e;
-        for (int b = 0; b < nmaps; ++b)
+        for (int b = 0; b < nmaps && !p->theta_torus; ++b)
             NUSHT_TRY(fft_exec(p, p->theta_fwd, bytes(p->X) + b * cstride, nullptr, s));
         stage_end(p, ST_TORUS_FFT, s);
         stage_begin(p, ST_DECONV, s);
@@ -592,7 +586,7 @@ int adjoint_impl(nusht_plan_s* p, const double* map, double* alm, int nmaps, hip
         stage_end(p, ST_DECONV, s);
         stage_begin(p, ST_TORUS_FFT, s);
         const size_t cstride = (size_t)(g.mmax + 1) * g.ntorus * 2 * e;
-        for (int b = 0; b < nmaps; ++b)
+        for (int b = 0; b < nmaps && !p->theta_torus; ++b)
             NUSHT_TRY(fft_exec(p, p->theta_bwd, bytes(p->X) + b * cstride, nullptr, s));
         stage_end(p, ST_TORUS_FFT, s);
         stage_begin(p, ST_LEGENDRE, s);

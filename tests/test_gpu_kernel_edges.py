@@ -100,3 +100,29 @@ def test_synthesis_splits(P, oracle_mod, lmax, mmax, B, mode):
     p = P.Plan(lmax, mmax, dev(th), dev(ph), 1e-12, dfs_mode=mode)
     f = p.synthesis(dev(alm)).cpu().numpy()
     assert rel(f, oracle_mod.synthesis(lmax, mmax, th, ph, alm)) <= 1e-11
+
+
+@pytest.mark.parametrize("lmax,mmax,B,dtype,mode", [
+    (14, 14, 1, "f64", "fused"), (17, 3, 2, "f64", "fused"), (23, 23, 1, "mixed", "paper"),
+    (40, 37, 3, "f64", "fused"), (55, 41, 5, "f64", "paper"), (78, 78, 1, "mixed", "fused"),
+    (100, 90, 2, "f64", "fused"), (134, 134, 1, "f64", "fused"), (190, 167, 4, "mixed", "fused"),
+    (223, 223, 1, "f64", "fused"), (311, 300, 1, "f64", "fused"), (438, 400, 1, "f64", "fused"),
+    (540, 540, 2, "mixed", "fused"), (1000, 900, 1, "f64", "fused"), (1500, 1500, 1, "f64", "fused"),
+    (2100, 1050, 1, "f64", "fused"), (2300, 800, 1, "f64", "fused"), (2120, 2120, 1, "mixed", "fused"),
+    (4320, 700, 1, "mixed", "fused")])
+def test_general_lengths(P, oracle_mod, lmax, mmax, B, dtype, mode):
+    """Fine-grid transforms of lengths other than 2^K and 5 2^K, both directions: all radices, one
+    and several butterflies per thread, lengths just below and above 8192 and the LDS limit.
+    Bounds: eps times the margin of the other tests (1e-11 FP64, 1e-5 mixed)."""
+    eps = 1e-12 if dtype == "f64" else 1e-5
+    tol = 1e-11 if dtype == "f64" else 1e-5
+    rng = np.random.default_rng(11 * lmax + mmax)
+    th, ph = inputs.uniform_points(rng, 61)
+    p = P.Plan(lmax, mmax, dev(th), dev(ph), eps, dtype=dtype, dfs_mode=mode)
+    print(f"[lengths lmax={lmax} mmax={mmax} B={B} {dtype} {mode}]", flush=True)
+    alm = inputs.red_alm(rng, lmax, mmax, B)
+    f = p.synthesis(dev(alm)).cpu().numpy()
+    assert rel(f, oracle_mod.synthesis(lmax, mmax, th, ph, alm)) <= tol
+    d = rng.standard_normal((B, th.size))
+    c = p.adjoint(dev(d)).cpu().numpy()
+    assert mrel(c, oracle_mod.adjoint(lmax, mmax, th, ph, d), lmax, mmax) <= tol
