@@ -21,6 +21,8 @@ constexpr int kMaxWidth = 16;
 // zero entries after the recurrence table, so that a chunk of l values can be loaded whole
 constexpr int kRecPad = 64;
 constexpr int kMinWidth = 2;
+// columns of a row of the spreading subgrids (kTile + w - 1 <= 47, in blocks of 16)
+constexpr int kSubCols = 48;
 // bits of a plan's device error word
 constexpr int kErrAdjWait = 1;  // a Legendre-adjoint slot wait reached its bound
 
@@ -222,7 +224,7 @@ struct BandRec {
 inline int group_width(int nmaps, int b) { return (nmaps - b) >= 4 ? 4 : 1; }
 
 // Spreading strategy: the band sweep for every FP32 (mixed-precision) kernel, for FP64 kernels
-// of width <= 8 and for deterministic plans; tile subgrids with LDS atomics and a halo pass for
+// of width <= 8 and for deterministic plans; tile subgrids (matrix cores) and a halo pass for
 // wider FP64 kernels (whose band sweep runs one map per pass).
 inline bool spread_uses_tiles(const nusht_plan_s* p)
 {

@@ -13,8 +13,8 @@
 //    column bands row by row and keep the rows a point can reach in registers
 //    (k_spread_band): every fine cell is written once, with its points summed in a fixed
 //    order, and no atomics or partial grids are involved;
-//  * spreading, FP64 windows of w > 8: tile subgrids accumulated with LDS atomics
-//    (k_spread_lds) and a halo pass that sums, for every fine cell, the subgrids of the
+//  * spreading, FP64 windows of w > 8: tile subgrids formed on the matrix cores
+//    (k_spread_tile) and a halo pass that sums, for every fine cell, the subgrids of the
 //    windows covering it (k_halo).
 // Offsets are formed in FP64 from FP64 coordinates before any cast to the kernel's type T.
 #pragma once
@@ -370,147 +370,226 @@ __global__ __launch_bounds__(256) void k_interp_deriv(const double* __restrict__
     }
 }
 
-// Spreading of wide FP64 kernels (w > 8), not deterministic: tile subgrids with LDS atomics
-// and a halo pass.  (The band sweep below does only 64 / 16 = 4 points per wave step once
-// w > 8 and runs FP64 maps one per pass; for FP64 its per-point work then outweighs the
-// atomics this kernel pays.)
-// Batched: the block stages up to NB of the slot's points (tap
-// offsets, first cells relative to the tile, values) in LDS, then every wave takes
-// PPW = 64 / LPP points at a time with LPP lanes per point, lane = column tap: each lane forms
-// its column tap psi2[col] and the row tap psi1[col], the row taps of the point are exchanged
-// through a per-wave LDS row, and lane (point, col) adds f psi1[a] psi2[col] into window
-// rows r + a, a < W, of its column.  The window is planar (map-major), so the lanes of one
-// point add into consecutive words of one row.  Values come in packed, [point][MB], in the
-// caller's order, and are fetched through the permutation.  The window sums in FP64; the order of the additions into a cell is not fixed, so results can
-// differ between runs by FP64 rounding (~1e-16 relative) before the cast to T.
-template <typename T, int MB>
-struct SpreadPoint {
-    T d1, d2;  // offsets of the first taps, grid units
-    int r, c;  // first tap cell relative to the tile
-    T f[MB];
-};
+// Spreading of wide FP64 kernels (w > 8), not deterministic: tile subgrids on the matrix cores
+// and a halo pass.
+//
+// A subgrid is sum_p f_p psi1_p psi2_p^T, a product contracted over points: K = 4 points per
+// v_mfma_f64_16x16x4.  The tile's points are dealt to the block's four waves by the 16 x 16
+// quadrant of their first cell, so the taps of all points of a wave lie in one 32 x 32 window
+// (15 + w <= 31): 2 x 2 accumulator blocks in registers, which no other wave touches.  Lane
+// (k, j) forms tap j of point k (one polynomial per axis, its coefficient column in registers);
+// the shift to window cells is a rotation within the 16 lanes of the point, and the lanes that
+// wrap belong to the second block.  Points of a batch are taken with a stride over the tile, so
+// that every quadrant has its share of each batch.  The waves then put their windows into LDS,
+// one map after the other, and the block writes their sum as the subgrid.  Every order is fixed.
+//
+// What bounds it: the matrix cores (4 x 64 cycles per 4 points and map, (w / 32)^2 of whose products
+// are used) and FP64 vector work (2 (w + 1) FMAs of taps and the shifts), which share the FP64
+// units: 226 and 290 us of the 620 us at 8.4 M points, w = 12, one map.  One FP64 LDS atomic add
+// per tap and point, with taps from exp and sqrt, took 765 us there; with four maps of 2.1 M
+// points, w = 14, 562 -> 448 us.  The subgrids' sum 242 -> 153 us.  Tiles of a few points
+// (26, w = 14) are bound by the subgrid's write and no faster than before (149 -> 186 us for
+// four maps, the sum 157 -> 200 us).
+typedef double d4 __attribute__((ext_vector_type(4)));
 
-template <typename T, int W, int MB>
-__global__ __launch_bounds__(256) void k_spread_lds(const T* __restrict__ vals, PointBins pb,
-                                                    T beta, T* __restrict__ sub)
+template <int W, int MB>
+__global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const double* __restrict__ vals, PointBins pb,
+                                                     double beta, const double* __restrict__ coef,
+                                                     double* __restrict__ sub)
 {
     constexpr int P = kTile + W - 1;
-    constexpr int LPP = W <= 8 ? 8 : 16;
-    constexpr int PPW = 64 / LPP;
-    constexpr int NB = 128;  // points staged per batch (64 for FP64 measured 0.6 ms slower)
-    static_assert(W <= 16, "one lane per column tap");
-    // the window accumulates in FP64 for either T: LDS atomic adds of FP64 measured fast on
-    // gfx950, those of FP32 an order of magnitude slower than the whole kernel
-    __shared__ double win[MB * P * P];
-    __shared__ SpreadPoint<T, MB> s_pt[NB];
-    __shared__ T s_p1[4][PPW][LPP];
+    constexpr int NB = 256;  // points per batch, one per thread
+    static_assert(W <= 16 && P < kSubCols, "a lane per tap, two blocks per quadrant");
+    __shared__ double win[4][32 * 32];  // the waves' windows of one map
+    __shared__ double s_s1[NB], s_s2[NB], s_f[NB][MB];
+    __shared__ int s_rc[NB], s_cnt[4][4];
     const int slot = blockIdx.x;
     const int tile = pb.slot_tile[slot];
     const int r0 = (tile / pb.nt2) * kTile;
     const int c0 = (tile % pb.nt2) * kTile;
-    const int t = threadIdx.x;
-    for (int e = t; e < MB * P * P; e += blockDim.x) win[e] = 0.0;
-    const int wave = t >> 6, lane = t & 63;
-    const int grp = lane / LPP, col = lane - grp * LPP;
-    const int p0 = pb.slot_off[slot], p1 = pb.slot_off[slot + 1];
-    const T cw = T(2) / T(W);
-    T* p1row = s_p1[wave][grp];
-    for (int base = p0; base < p1; base += NB) {
-        const int nb = min(NB, p1 - base);
-        __syncthreads();  // window cleared, or the previous batch consumed
-        if (t < nb) {
-            const int p = base + t;
-            double d1, d2;
-            const int l1 = first_tap(pb.sth[p], pb.s1, W, d1);
-            const int l2 = first_tap(pb.sph[p], pb.s2, W, d2);
-            int r = wrap_index(l1, pb.n1) - r0;
-            int c = wrap_index(l2, pb.n2) - c0;
-            const int64_t src = pb.perm[p];
-            SpreadPoint<T, MB> sp;
-            sp.d1 = (T)d1;
-            sp.d2 = (T)d2;
-            sp.r = min(max(r, 0), kTile - 1);
-            sp.c = min(max(c, 0), kTile - 1);
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63, j = lane & 15;
+    const int p0 = pb.slot_off[slot], np = pb.slot_off[slot + 1] - p0;
+    double creg[W + 1];
 #pragma unroll
-            for (int b = 0; b < MB; ++b) sp.f[b] = vals[src * MB + b];
-            s_pt[t] = sp;
+    for (int k = 0; k <= W; ++k) creg[k] = coef && j < W ? coef[k * W + j] : 0.0;
+    d4 acc[MB][2][2];
+#pragma unroll
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[b][q >> 1][q & 1] = d4{0.0, 0.0, 0.0, 0.0};
+
+    const int nbatch = (np + NB - 1) / NB;
+    for (int batch = 0; batch < nbatch; ++batch) {
+        const int i = batch + t * nbatch;
+        int quad = -1, rc = 0;
+        double sv1 = 0.0, sv2 = 0.0, f[MB];
+        if (i < np) {
+            const int p = p0 + i;
+            double e1, e2;
+            const int l1 = first_tap(pb.sth[p], pb.s1, W, e1);
+            const int l2 = first_tap(pb.sph[p], pb.s2, W, e2);
+            const int64_t src = pb.perm[p];
+#pragma unroll
+            for (int b = 0; b < MB; ++b) f[b] = vals[src * MB + b];
+            const int r = min(max(wrap_index(l1, pb.n1) - r0, 0), kTile - 1);
+            const int c = min(max(wrap_index(l2, pb.n2) - c0, 0), kTile - 1);
+            sv1 = 2.0 * e1 - (double)(W - 1);
+            sv2 = 2.0 * e2 - (double)(W - 1);
+            quad = (r >> 4) * 2 + (c >> 4);
+            rc = (r & 15) | ((c & 15) << 8);
+        }
+        int pos = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const unsigned long long m = __ballot(quad == q);
+            if (quad == q) pos = __popcll(m & ((1ull << lane) - 1));
+            if (lane == 0) s_cnt[wave][q] = __popcll(m);
+        }
+        __syncthreads();  // also: the previous batch has been consumed
+        int first = 0, mine = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            int tot = 0, before = 0;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int n = s_cnt[v][q];
+                if (v < wave) before += n;
+                tot += n;
+            }
+            // this wave's list starts after those of the quadrants before it
+            if (q < wave) first += tot;
+            if (q == wave) mine = tot;
+            if (q < quad) pos += tot;
+            if (q == quad) pos += before;
+        }
+        if (quad >= 0) {
+            s_s1[pos] = sv1;
+            s_s2[pos] = sv2;
+            s_rc[pos] = rc;
+#pragma unroll
+            for (int b = 0; b < MB; ++b) s_f[pos][b] = f[b];
         }
         __syncthreads();
-        // lane group g takes the points g S + i of the row-sorted batch: the PPW points of one
-        // step lie S apart, in different rows, so no two lanes of an atomic add address the
-        // same cell (a point adds into rows r + a for the step's common a)
-        const int S = (nb + PPW - 1) / PPW;
-        for (int i = wave; i < S; i += 4) {
-            const int q = grp * S + i;
-            const bool live = q < nb;
-            const SpreadPoint<T, MB> sp = s_pt[live ? q : 0];
-            const bool act = live && col < W;
-            const T p2 = act ? es_value<T>((sp.d2 - T(col)) * cw, beta) : T(0);
-            p1row[col] = col < W ? es_value<T>((sp.d1 - T(col)) * cw, beta) : T(0);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            T pr[W];
+        first = __builtin_amdgcn_readfirstlane(first);
+        mine = __builtin_amdgcn_readfirstlane(mine);
+        for (int k = 0; k < mine; k += 4) {
+            const bool live = k + (lane >> 4) < mine;
+            const int at = first + (live ? k + (lane >> 4) : k);
+            const double x1 = s_s1[at], x2 = s_s2[at];
+            const int x = s_rc[at];
+            const int r = x & 15, c = x >> 8;
+            double a, b;
+            if (coef) {
+                a = es_tap_poly<double, W>(x1, creg);
+                b = es_tap_poly<double, W>(x2, creg);
+            } else {
+                // d - j of the tap, from s = 2 d - (W - 1) (exact but for the last bit)
+                a = j < W ? es_value<double>((x1 + (double)(W - 1 - 2 * j)) / W, beta) : 0.0;
+                b = j < W ? es_value<double>((x2 + (double)(W - 1 - 2 * j)) / W, beta) : 0.0;
+            }
+            // cell j of the window's first (second) block holds tap j - r (j + 16 - r)
+            a = __shfl(a, (lane & 48) | ((j - r) & 15));
+            b = __shfl(b, (lane & 48) | ((j - c) & 15));
+            if (!live) b = 0.0;
+            const double a0 = j >= r ? a : 0.0, a1 = j >= r ? 0.0 : a;
+            // the list is sorted by row: often no point of the step reaches the second row block
+            const bool low = __ballot(r + W > 16) != 0;
 #pragma unroll
-            for (int a = 0; a < W; ++a) pr[a] = p1row[a];
-            // the next step rewrites the row: every lane's reads come first
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (act) {
-                T fb[MB];
-#pragma unroll
-                for (int b = 0; b < MB; ++b) fb[b] = sp.f[b] * p2;
-                double* w0 = win + sp.r * P + sp.c + col;
-#pragma unroll
-                for (int a = 0; a < W; ++a)
-#pragma unroll
-                    for (int b = 0; b < MB; ++b)
-                        atomicAdd(w0 + (b * P + a) * P, (double)(fb[b] * pr[a]));
+            for (int m = 0; m < MB; ++m) {
+                const double v = b * s_f[at][m];
+                const double b0 = j >= c ? v : 0.0, b1 = j >= c ? 0.0 : v;
+                acc[m][0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[m][0][0], 0, 0, 0);
+                acc[m][0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[m][0][1], 0, 0, 0);
+                if (low) {
+                    acc[m][1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[m][1][0], 0, 0, 0);
+                    acc[m][1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[m][1][1], 0, 0, 0);
+                }
             }
         }
     }
-    __syncthreads();
-    T* dst = sub + (int64_t)slot * (P * P * MB);
-    for (int e = t; e < P * P; e += blockDim.x) {
+    // element v of a block is row 4 v + lane / 16, column lane % 16
+    double* dst = sub + (int64_t)slot * (P * kSubCols * MB);
+    double* mywin = win[wave] + (lane >> 4) * 32 + j;
 #pragma unroll
-        for (int b = 0; b < MB; ++b) dst[e * MB + b] = (T)win[b * P * P + e];
+    for (int m = 0; m < MB; ++m) {
+        if (m) __syncthreads();  // the previous map has been read
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                mywin[((q >> 1) * 16 + 4 * v) * 32 + (q & 1) * 16] = acc[m][q >> 1][q & 1][v];
+        __syncthreads();
+        // two columns per thread; quadrant (qr, qc) covers rows 16 qr + [0, 32), columns alike
+        for (int e = t; e < P * (kSubCols / 2); e += 256) {
+            const int r = e / (kSubCols / 2), c = 2 * (e - r * (kSubCols / 2));
+            double2 v = {0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int rq = r - 16 * (q >> 1), cq = c - 16 * (q & 1);
+                if ((unsigned)rq < 32u && (unsigned)cq < 32u) {
+                    const double2 u = *reinterpret_cast<const double2*>(&win[q][rq * 32 + cq]);
+                    v.x += u.x;
+                    v.y += u.y;
+                }
+            }
+            reinterpret_cast<double2*>(dst + m * (P * kSubCols))[e] = v;
+        }
     }
 }
 
-// fine[b][i][j] = sum of the subgrids of the windows covering cell (i, j); zero elsewhere
-template <typename T, int W, int MB>
-__global__ __launch_bounds__(256) void k_halo(const T* __restrict__ sub,
+// fine[b][i][j] = sum of the subgrids of the windows covering cell (i, j); zero elsewhere.
+// A thread owns two columns of kHaloRows rows (of one tile row): the four slots are looked up
+// once, its loads are 16 bytes wide and in flight together.  (A column past the window is one of
+// the zero columns that pad a subgrid row.)
+constexpr int kHaloRows = 4;
+template <int W, int MB>
+__global__ __launch_bounds__(256) void k_halo(const double* __restrict__ sub,
                                               const int* __restrict__ tile_slot, int nt1, int nt2,
                                               int n1, int n2, int ra, int rb,
-                                              T* __restrict__ fine, int64_t map_stride)
+                                              double* __restrict__ fine, int64_t map_stride)
 {
     constexpr int P = kTile + W - 1;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = 2 * (blockIdx.x * blockDim.x + threadIdx.x);
     // rows [0, ra) and [n1 - rb, n1): the only rows any window reaches
-    const int i = (int)blockIdx.y < ra ? (int)blockIdx.y : n1 - rb + ((int)blockIdx.y - ra);
+    const int na = (ra + kHaloRows - 1) / kHaloRows, y = blockIdx.y;
+    const int i0 = y < na ? y * kHaloRows : n1 - rb + (y - na) * kHaloRows;
+    const int i1 = min(i0 + kHaloRows, y < na ? ra : n1);
     if (j >= n2) return;
-    const int tr = i / kTile, rr = i - tr * kTile;
+    const int tr = i0 / kTile, rr = i0 - tr * kTile;
     const int tc = j / kTile, cc = j - tc * kTile;
     const int trp = tr == 0 ? nt1 - 1 : tr - 1;
     const int tcp = tc == 0 ? nt2 - 1 : tc - 1;
-    T acc[MB];
+    double2 acc[MB][kHaloRows];
 #pragma unroll
-    for (int b = 0; b < MB; ++b) acc[b] = T(0);
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+        for (int v = 0; v < kHaloRows; ++v) acc[b][v] = double2{0.0, 0.0};
     auto add = [&](int t_r, int t_c, int r, int c) {
         const int sl = tile_slot[t_r * nt2 + t_c];
         if (sl < 0) return;
-        const T* s = sub + (int64_t)sl * (P * P * MB) + (r * P + c) * MB;
+        const double* s = sub + (int64_t)sl * (P * kSubCols * MB) + r * kSubCols + c;
 #pragma unroll
-        for (int b = 0; b < MB; ++b) acc[b] += s[b];
+        for (int b = 0; b < MB; ++b)
+#pragma unroll
+            for (int v = 0; v < kHaloRows; ++v)
+                if (r + v < P) {
+                    const double2 u =
+                        *reinterpret_cast<const double2*>(s + (b * P + v) * kSubCols);
+                    acc[b][v].x += u.x;
+                    acc[b][v].y += u.y;
+                }
     };
     add(tr, tc, rr, cc);
     if (rr < W - 1) add(trp, tc, rr + kTile, cc);
     if (cc < W - 1) add(tr, tcp, rr, cc + kTile);
     if (rr < W - 1 && cc < W - 1) add(trp, tcp, rr + kTile, cc + kTile);
-    const int64_t off = (int64_t)i * n2 + j;
 #pragma unroll
-    for (int b = 0; b < MB; ++b) fine[b * map_stride + off] = acc[b];
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+        for (int v = 0; v < kHaloRows; ++v)
+            if (i0 + v < i1)
+                *reinterpret_cast<double2*>(fine + b * map_stride + (int64_t)(i0 + v) * n2 + j) =
+                    acc[b][v];
 }
 
 // Spreading (type 1, N^H of Eq. 6): u(l1, l2) = sum_i f_i psi(row taps) psi(column taps), the
@@ -969,6 +1048,20 @@ inline PointBins make_bins(const nusht_plan_s* p)
         default: set_last_error("nufft", "unsupported kernel width"); return NUSHT_EINVAL; \
     }
 
+// widths of the tile subgrids
+#define NUSHT_WIDE_SWITCH(width, BODY)                   \
+    switch (width) {                                     \
+        case 9: { constexpr int WV = 9; BODY; } break;   \
+        case 10: { constexpr int WV = 10; BODY; } break; \
+        case 11: { constexpr int WV = 11; BODY; } break; \
+        case 12: { constexpr int WV = 12; BODY; } break; \
+        case 13: { constexpr int WV = 13; BODY; } break; \
+        case 14: { constexpr int WV = 14; BODY; } break; \
+        case 15: { constexpr int WV = 15; BODY; } break; \
+        case 16: { constexpr int WV = 16; BODY; } break; \
+        default: set_last_error("nufft", "unsupported kernel width"); return NUSHT_EINVAL; \
+    }
+
 // Interpolation of maps [0, nmaps): groups of four write packed rows [point][4] into the plan's
 // point scratch (one 32-byte store per point instead of four scattered 8-byte ones), unpacked
 // into out afterwards; a single map writes straight to out.
@@ -1046,28 +1139,32 @@ int spread_group_impl(const nusht_plan_s* p, const double* vals, T* fine, int mb
                            packed);
     NUSHT_HIP(hipGetLastError());
     const int64_t ms = (int64_t)p->g.n1 * p->g.n2;
-    if (spread_uses_tiles(p)) {
-        if (p->nslots == 0) return NUSHT_OK;
-        const PointBins pb = make_bins(p);
-        T* sub = reinterpret_cast<T*>(p->Z);
-        dim3 hgrid((p->g.n2 + 255) / 256, p->fine_ra + p->fine_rb);
-        NUSHT_WIDTH_SWITCH(p->g.width, {
-            if (mb == 4) {
-                hipLaunchKernelGGL((k_spread_lds<T, WV, 4>), dim3(p->nslots), dim3(256), 0, s,
-                                   packed, pb, beta, sub);
-                hipLaunchKernelGGL((k_halo<T, WV, 4>), hgrid, dim3(256), 0, s, sub, p->tile_slot,
-                                   p->nt1, p->nt2, p->g.n1, p->g.n2, p->fine_ra, p->fine_rb,
-                                   fine, ms);
-            } else {
-                hipLaunchKernelGGL((k_spread_lds<T, WV, 1>), dim3(p->nslots), dim3(256), 0, s,
-                                   packed, pb, beta, sub);
-                hipLaunchKernelGGL((k_halo<T, WV, 1>), hgrid, dim3(256), 0, s, sub, p->tile_slot,
-                                   p->nt1, p->nt2, p->g.n1, p->g.n2, p->fine_ra, p->fine_rb,
-                                   fine, ms);
-            }
-        });
-        NUSHT_HIP(hipGetLastError());
-        return NUSHT_OK;
+    if constexpr (sizeof(T) == 8) {
+        if (spread_uses_tiles(p)) {
+            if (p->nslots == 0) return NUSHT_OK;
+            const PointBins pb = make_bins(p);
+            const double* coef = es_coef_of<double>(p);
+            double* sub = reinterpret_cast<double*>(p->Z);
+            const int ha = (p->fine_ra + kHaloRows - 1) / kHaloRows;
+            const dim3 hgrid((p->g.n2 + 511) / 512, ha + p->fine_rb / kHaloRows);
+            NUSHT_WIDE_SWITCH(p->g.width, {
+                if (mb == 4) {
+                    hipLaunchKernelGGL((k_spread_tile<WV, 4>), dim3(p->nslots), dim3(256), 0, s,
+                                       packed, pb, beta, coef, sub);
+                    hipLaunchKernelGGL((k_halo<WV, 4>), hgrid, dim3(256), 0, s, sub, p->tile_slot,
+                                       p->nt1, p->nt2, p->g.n1, p->g.n2, p->fine_ra, p->fine_rb,
+                                       fine, ms);
+                } else {
+                    hipLaunchKernelGGL((k_spread_tile<WV, 1>), dim3(p->nslots), dim3(256), 0, s,
+                                       packed, pb, beta, coef, sub);
+                    hipLaunchKernelGGL((k_halo<WV, 1>), hgrid, dim3(256), 0, s, sub, p->tile_slot,
+                                       p->nt1, p->nt2, p->g.n1, p->g.n2, p->fine_ra, p->fine_rb,
+                                       fine, ms);
+                }
+            });
+            NUSHT_HIP(hipGetLastError());
+            return NUSHT_OK;
+        }
     }
     const BandBins bb = make_band_bins(p);
     const T* coef = es_coef_of<T>(p);

@@ -449,8 +449,8 @@ int ensure_capacity(nusht_plan_s* p, int nmaps)
     if (!p->V) NUSHT_TRY(dmalloc(&p->V, (size_t)g.npts * 4));
     // tile subgrids of the wide-kernel spreading: one group of up to four maps at a time
     if (spread_uses_tiles(p) && !p->Z) {
-        const int P = kTile + g.width - 1;
-        const size_t zb = (size_t)std::max(p->nslots, 1) * P * P * 4 * e;
+        const size_t sub = (size_t)(kTile + g.width - 1) * kSubCols;
+        const size_t zb = (size_t)std::max(p->nslots, 1) * sub * 4 * e;
         NUSHT_TRY(dmalloc((char**)&p->Z, zb));
         p->Zbytes = zb;
     }

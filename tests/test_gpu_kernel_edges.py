@@ -126,3 +126,27 @@ def test_general_lengths(P, oracle_mod, lmax, mmax, B, dtype, mode):
     d = rng.standard_normal((B, th.size))
     c = p.adjoint(dev(d)).cpu().numpy()
     assert mrel(c, oracle_mod.adjoint(lmax, mmax, th, ph, d), lmax, mmax) <= tol
+
+
+@pytest.mark.parametrize("width,n,B,taps", [
+    (9, 1, 1, "poly"), (9, 777, 4, "poly"), (10, 5000, 2, "poly"), (11, 5000, 3, "exact"),
+    (12, 255, 1, "poly"), (12, 257, 5, "poly"), (13, 5000, 1, "exact"), (14, 20000, 7, "poly"),
+    (15, 3, 4, "poly"), (15, 5000, 1, "poly"), (16, 5000, 4, "exact"), (16, 20000, 1, "poly")])
+def test_tile_spreading(P, width, n, B, taps):
+    """The tile kernel of the wide FP64 spreading against the band sweep (a deterministic plan's
+    kernel: the same taps, another split and order): one point, fewer and more points than a batch
+    of 256 in a tile, all of a tile's points in one quadrant, both poles, the phi wrap, every batch
+    remainder.  Bound 1e-12: the sums have at most a few thousand terms of rounding 1e-16."""
+    print(f"[tile spreading w={width} n={n} B={B} {taps}]", flush=True)
+    rng = np.random.default_rng(width * 1000 + n)
+    th, ph = inputs.uniform_points(rng, n)
+    k = n // 3
+    th[:k] = 1.3 + 0.02 * rng.random(k)
+    ph[:k] = 2.0 + 0.02 * rng.random(k)
+    if n > 100:
+        th[k:k + 4] = [0.0, np.pi, 1e-5, np.pi - 1e-5]
+        ph[k + 4:k + 8] = [0.0, 2 * np.pi - 1e-9, 1e-9, np.pi]
+    d = dev(rng.standard_normal((B, n)))
+    c = [P.Plan(90, 77, dev(th), dev(ph), 1e-8, width=width, kernel_eval=taps, deterministic=det).adjoint(d)
+         .cpu().numpy() for det in (False, True)]
+    assert mrel(c[0], c[1], 90, 77) <= 1e-12
