@@ -210,6 +210,8 @@ __global__ __launch_bounds__(256) void k_band_to_rows(const C* __restrict__ band
     const int q0 = blockIdx.y * kT, mu0 = blockIdx.x * kT;
     const int nq = ra + rb;
     const int tx = threadIdx.x, ty = threadIdx.y;
+    band += (int64_t)blockIdx.z * ncol * n1;  // map of the launch
+    rows += (int64_t)blockIdx.z * n1 * fw;
     const bool live = mu0 < ncol;
     if (live) {
         // read along i (contiguous in the band spectrum)
@@ -248,6 +250,8 @@ __global__ __launch_bounds__(256) void k_rows_to_band(const C* __restrict__ rows
     const int i0 = blockIdx.y * kT, mu0 = blockIdx.x * kT;
     const int tx = threadIdx.x, ty = threadIdx.y;
     const int nrow = COMPACT ? ra + rb : n1;
+    band += (int64_t)blockIdx.z * ncol * n1;  // map of the launch
+    rows += (int64_t)blockIdx.z * n1 * fw;
     // read along mu (contiguous in the row spectrum)
     for (int r = ty; r < kT; r += blockDim.y) {
         const int q = i0 + r, mu = mu0 + tx;
@@ -281,12 +285,12 @@ int launch_zero_nyquist_rows(const nusht_plan_s* p, double* G, int nmaps, hipStr
     return NUSHT_OK;
 }
 
-int launch_band_to_rows(const nusht_plan_s* p, const void* band, void* rows, int rw,
+int launch_band_to_rows(const nusht_plan_s* p, const void* band, void* rows, int rw, int nb,
                         hipStream_t s)
 {
     const nusht_geometry& g = p->g;
     const int fw = rw, nq = p->fine_ra + p->fine_rb;
-    dim3 grid((fw + kT - 1) / kT, (nq + kT - 1) / kT);
+    dim3 grid((fw + kT - 1) / kT, (nq + kT - 1) / kT, nb);
     dim3 block(kT, 8);
     if (g.dtype == NUSHT_MIXED)
         hipLaunchKernelGGL(k_band_to_rows<float2>, grid, block, 0, s,
@@ -301,13 +305,13 @@ int launch_band_to_rows(const nusht_plan_s* p, const void* band, void* rows, int
     return NUSHT_OK;
 }
 
-int launch_rows_to_band(const nusht_plan_s* p, const void* rows, int rw, void* band,
+int launch_rows_to_band(const nusht_plan_s* p, const void* rows, int rw, void* band, int nb,
                         hipStream_t s, bool window_only)
 {
     const nusht_geometry& g = p->g;
     const int fw = rw;
     const int nrow = window_only ? p->fine_ra + p->fine_rb : g.n1;
-    dim3 grid((g.mmax + 1 + kT - 1) / kT, (nrow + kT - 1) / kT);
+    dim3 grid((g.mmax + 1 + kT - 1) / kT, (nrow + kT - 1) / kT, nb);
     dim3 block(kT, 8);
 #define NUSHT_R2B(C, COMPACT)                                                                  \
     hipLaunchKernelGGL((k_rows_to_band<C, COMPACT>), grid, block, 0, s,                        \

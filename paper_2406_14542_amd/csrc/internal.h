@@ -144,7 +144,7 @@ struct nusht_plan_s {
     size_t Xbytes = 0;
     void* Y = nullptr;
     size_t Ybytes = 0;
-    void* W = nullptr;           // one map's fine row spectrum [n1][n2/2+1]
+    void* W = nullptr;           // fine row spectra [n1][n2/2+1] of one or more maps
     size_t Wbytes = 0;
     double* V = nullptr;         // point scratch [npts][4]: packed point values of one group
     void* Z = nullptr;           // tile subgrids of the wide-kernel spreading [nslots][P][P][4]
@@ -223,6 +223,10 @@ struct BandRec {
 // Maps are processed by the point kernels in groups of four, the remainder one by one.
 inline int group_width(int nmaps, int b) { return (nmaps - b) >= 4 ? 4 : 1; }
 
+// Row spectra of small maps are transformed together, up to this much scratch: one launch for
+// the batch where a launch per map would leave the chip idle.  (Larger maps fill it alone.)
+constexpr size_t kRowBatchBytes = 64u << 20;
+
 // Spreading strategy: the band sweep for every FP32 (mixed-precision) kernel, for FP64 kernels
 // of width <= 8 and for deterministic plans; tile subgrids (matrix cores) and a halo pass for
 // wider FP64 kernels (whose band sweep runs one map per pass).
@@ -275,20 +279,22 @@ int launch_deconv_pad(const nusht_plan_s* p, const void* tspec, void* fspec, int
                       int f32, hipStream_t s);
 int launch_deconv_trunc(const nusht_plan_s* p, const void* fspec, void* tspec, int nmaps,
                         int fused, int f32, hipStream_t s);
-// band spectrum [mmax+1][n1] <-> row spectrum [n1][rw] of one map, rows [0, fine_ra) and
+// band spectrum [mmax+1][n1] <-> row spectrum [n1][rw] of nb maps, rows [0, fine_ra) and
 // [n1 - fine_rb, n1) only (rw = n2/2+1 for the rocFFT row plans, mmax+1 for the row kernels).
 // band_to_rows zero-fills the columns mmax+1 .. rw-1; rows_to_band writes zeros for the rows
 // no window reaches, unless window_only (the fused theta pass reads the window rows only).
-int launch_band_to_rows(const nusht_plan_s* p, const void* band, void* rows, int rw,
+int launch_band_to_rows(const nusht_plan_s* p, const void* band, void* rows, int rw, int nb,
                         hipStream_t s);
-int launch_rows_to_band(const nusht_plan_s* p, const void* rows, int rw, void* band,
+int launch_rows_to_band(const nusht_plan_s* p, const void* rows, int rw, void* band, int nb,
                         hipStream_t s, bool window_only = false);
 
 // ---- fine-grid row transforms (rowfft.hip: 2^K and 5 2^K, mixfft.hip: other lengths) ----
 bool rowfft_supported(const nusht_geometry& g);
-// window rows of one map: rows [n1][rw] (columns 0 .. mmax) <-> real fine grid [n1][n2]
-int launch_row_c2r(const nusht_plan_s* p, const void* rows, int64_t rw, void* fine, hipStream_t s);
-int launch_row_r2c(const nusht_plan_s* p, const void* fine, void* rows, int64_t rw, hipStream_t s);
+// window rows of nb maps: rows [nb][n1][rw] (columns 0 .. mmax) <-> real fine grids [nb][n1][n2]
+int launch_row_c2r(const nusht_plan_s* p, const void* rows, int64_t rw, void* fine, int nb,
+                   hipStream_t s);
+int launch_row_r2c(const nusht_plan_s* p, const void* fine, void* rows, int64_t rw, int nb,
+                   hipStream_t s);
 // theta pass fused with the deconvolution, maps [0, nmaps): torus spectrum cs [b][mmax+1][N_t]
 // <-> band spectrum [b][mmax+1][n1] (window rows only)
 bool thetafft_supported(const nusht_geometry& g);
@@ -302,8 +308,8 @@ struct MixLen {
 bool thetafft_with_torus(const nusht_geometry& g);
 bool mixrow_supported(const nusht_geometry& g);
 bool mixtheta_supported(const nusht_geometry& g);
-int launch_mix_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, bool c2r,
-                   hipStream_t s);
+int launch_mix_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, int nb,
+                   bool c2r, hipStream_t s);
 int launch_mix_theta(const nusht_plan_s* p, const void* in, void* out, int nmaps, bool inv,
                      hipStream_t s);
 int launch_theta_inv(const nusht_plan_s* p, const void* cs, void* band, int nmaps, hipStream_t s);

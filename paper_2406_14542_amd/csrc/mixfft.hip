@@ -5,11 +5,11 @@
 namespace nusht {
 
 int mix_row_f32(const nusht_plan_s* p, const MixLen& m, const void* in, void* out, int64_t rw,
-                bool c2r, hipStream_t s);
+                int nb, bool c2r, hipStream_t s);
 int mix_theta_f32(const nusht_plan_s* p, const MixLen& mt, const MixLen& mn, const void* in, void* out,
                   int nmaps, bool inv, hipStream_t s);
 int mix_row_f64(const nusht_plan_s* p, const MixLen& m, const void* in, void* out, int64_t rw,
-                bool c2r, hipStream_t s);
+                int nb, bool c2r, hipStream_t s);
 int mix_theta_f64(const nusht_plan_s* p, const MixLen& mt, const MixLen& mn, const void* in, void* out,
                   int nmaps, bool inv, hipStream_t s);
 
@@ -74,13 +74,13 @@ bool mixtheta_supported(const nusht_geometry& g)
            mix_len(g.n1, &m) && mix_len(g.ntorus, &m);
 }
 
-int launch_mix_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, bool c2r,
-                   hipStream_t s)
+int launch_mix_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, int nb,
+                   bool c2r, hipStream_t s)
 {
     MixLen m;
     if (!mix_len(p->g.n2 / 2, &m)) return NUSHT_EINVAL;
-    return p->g.dtype == NUSHT_MIXED ? mix_row_f32(p, m, in, out, rw, c2r, s)
-                                     : mix_row_f64(p, m, in, out, rw, c2r, s);
+    return p->g.dtype == NUSHT_MIXED ? mix_row_f32(p, m, in, out, rw, nb, c2r, s)
+                                     : mix_row_f64(p, m, in, out, rw, nb, c2r, s);
 }
 
 int launch_mix_theta(const nusht_plan_s* p, const void* in, void* out, int nmaps, bool inv,

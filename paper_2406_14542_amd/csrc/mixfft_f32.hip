@@ -4,9 +4,9 @@
 namespace nusht {
 
 int mix_row_f32(const nusht_plan_s* p, const MixLen& m, const void* in, void* out, int64_t rw,
-                bool c2r, hipStream_t s)
+                int nb, bool c2r, hipStream_t s)
 {
-    return mix_row<float>(p, m, in, out, rw, c2r, s);
+    return mix_row<float>(p, m, in, out, rw, nb, c2r, s);
 }
 
 int mix_theta_f32(const nusht_plan_s* p, const MixLen& mt, const MixLen& mn, const void* in, void* out,

@@ -143,6 +143,8 @@ __global__ __launch_bounds__(1024) void k_mix_c2r(MixLen m, const typename Cx<T>
     C* buf = mix_lds<C>();
     const int q = blockIdx.x, N = m.n, M = ncol - 1;
     const int i = q < ra ? q : n1 - rb + (q - ra);
+    rows += (int64_t)blockIdx.y * n1 * rw;  // map of the launch
+    fine += (int64_t)blockIdx.y * n1 * (2 * N);
     const C* X = rows + (int64_t)i * rw;
     C* z = reinterpret_cast<C*>(fine + (int64_t)i * (2 * N));
     // Z[k] from X[k] and conj X[N - k]; band columns only (clamped loads, so no branch)
@@ -171,6 +173,8 @@ __global__ __launch_bounds__(1024) void k_mix_r2c(MixLen m, const T* __restrict_
     C* buf = mix_lds<C>();
     const int q = blockIdx.x, N = m.n;
     const int i = q < ra ? q : n1 - rb + (q - ra);
+    rows += (int64_t)blockIdx.y * n1 * rw;  // map of the launch
+    fine += (int64_t)blockIdx.y * n1 * (2 * N);
     const C* z = reinterpret_cast<const C*>(fine + (int64_t)i * (2 * N));
     mix_fft<-1, V, false, true>(m, buf, threadIdx.x, blockDim.x, tw, [z](int k) { return z[k]; },
                                 [buf](int k, C v) { buf[pad16(k)] = v; });
@@ -277,11 +281,11 @@ int threads_for(int n) { return std::min(1024, (n + 511) / 512 * 64); }
 
 template <typename T>
 int mix_row(const nusht_plan_s* p, const MixLen& m, const void* in, void* out, int64_t rw,
-            bool c2r, hipStream_t s)
+            int nb, bool c2r, hipStream_t s)
 {
     using C = typename Cx<T>::type;
     const nusht_geometry& g = p->g;
-    const dim3 grid(p->fine_ra + p->fine_rb);
+    const dim3 grid(p->fine_ra + p->fine_rb, nb);
     const C* tw = reinterpret_cast<const C*>(p->rowtw);
     if (c2r)
         NUSHT_MIX_LAUNCH(k_mix_c2r, T, m.n, grid, m, reinterpret_cast<const C*>(in), rw, g.mmax + 1,

@@ -187,6 +187,8 @@ __global__ __launch_bounds__(256) void k_interp(const T* __restrict__ fine, int6
     const int tile = pb.slot_tile[slot];
     const int r0 = (tile / pb.nt2) * kTile;
     const int c0 = (tile % pb.nt2) * kTile;
+    fine += blockIdx.y * map_stride;  // map of the launch (MB = 1)
+    out += blockIdx.y * npts;
     // the first point's coordinates and destination, then the whole window: every load of
     // the thread is in flight before the first one is waited for
     const int p0 = pb.slot_off[slot], p1 = pb.slot_off[slot + 1];
@@ -387,13 +389,13 @@ __global__ __launch_bounds__(256) void k_interp_deriv(const double* __restrict__
 // are used) and FP64 vector work (2 (w + 1) FMAs of taps and the shifts), which share the FP64
 // units: 226 and 290 us of the 620 us at 8.4 M points, w = 12, one map.  One FP64 LDS atomic add
 // per tap and point, with taps from exp and sqrt, took 765 us there; with four maps of 2.1 M
-// points, w = 14, 562 -> 448 us.  The subgrids' sum 242 -> 153 us.  Tiles of a few points
+// points, w = 14, 562 -> 448 us.  The subgrids' sum 242 -> 141 us.  Tiles of a few points
 // (26, w = 14) are bound by the subgrid's write and no faster than before (149 -> 186 us for
-// four maps, the sum 157 -> 200 us).
+// four maps, the sum 157 -> 170 us, the packing pass of single maps gone).
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 template <int W, int MB>
-__global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const double* __restrict__ vals, PointBins pb,
+__global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const double* __restrict__ vals, int64_t vstride, PointBins pb,
                                                      double beta, const double* __restrict__ coef,
                                                      double* __restrict__ sub)
 {
@@ -409,6 +411,7 @@ __global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const doub
     const int c0 = (tile % pb.nt2) * kTile;
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63, j = lane & 15;
     const int p0 = pb.slot_off[slot], np = pb.slot_off[slot + 1] - p0;
+    vals += blockIdx.y * vstride;  // map of the launch (MB = 1)
     double creg[W + 1];
 #pragma unroll
     for (int k = 0; k <= W; ++k) creg[k] = coef && j < W ? coef[k * W + j] : 0.0;
@@ -508,7 +511,7 @@ __global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const doub
         }
     }
     // element v of a block is row 4 v + lane / 16, column lane % 16
-    double* dst = sub + (int64_t)slot * (P * kSubCols * MB);
+    double* dst = sub + ((int64_t)blockIdx.y * gridDim.x + slot) * (P * kSubCols * MB);
     double* mywin = win[wave] + (lane >> 4) * 32 + j;
 #pragma unroll
     for (int m = 0; m < MB; ++m) {
@@ -538,17 +541,19 @@ __global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const doub
 }
 
 // fine[b][i][j] = sum of the subgrids of the windows covering cell (i, j); zero elsewhere.
-// A thread owns two columns of kHaloRows rows (of one tile row): the four slots are looked up
+// A thread owns two columns of one or two rows (of one tile row): the four slots are looked up
 // once, its loads are 16 bytes wide and in flight together.  (A column past the window is one of
 // the zero columns that pad a subgrid row.)
-constexpr int kHaloRows = 4;
 template <int W, int MB>
-__global__ __launch_bounds__(256) void k_halo(const double* __restrict__ sub,
+__global__ __launch_bounds__(256) void k_halo(const double* __restrict__ sub, int nslots,
                                               const int* __restrict__ tile_slot, int nt1, int nt2,
                                               int n1, int n2, int ra, int rb,
                                               double* __restrict__ fine, int64_t map_stride)
 {
     constexpr int P = kTile + W - 1;
+    constexpr int kHaloRows = MB == 4 ? 1 : 2;
+    sub += (int64_t)blockIdx.z * nslots * (P * kSubCols * MB);  // map of the launch (MB = 1)
+    fine += blockIdx.z * map_stride;
     const int j = 2 * (blockIdx.x * blockDim.x + threadIdx.x);
     // rows [0, ra) and [n1 - rb, n1): the only rows any window reaches
     const int na = (ra + kHaloRows - 1) / kHaloRows, y = blockIdx.y;
@@ -1094,12 +1099,13 @@ int dispatch_interp_impl(const nusht_plan_s* p, const T* fine, double* out, int 
                 hipLaunchKernelGGL((k_unpack_points<4, sizeof(T) == 4>), dim3(pblocks), dim3(256),
                                    0, s, p->V, p->iperm, npts, out + b * npts);
             } else {
-                hipLaunchKernelGGL((k_interp<T, WV, 1, false>), dim3(p->nslots), dim3(256), 0,
-                                   s, fine + b * ms, ms, pb, beta, coef, out + b * npts, npts);
+                hipLaunchKernelGGL((k_interp<T, WV, 1, false>), dim3(p->nslots, nmaps - b),
+                                   dim3(256), 0, s, fine + b * ms, ms, pb, beta, coef,
+                                   out + b * npts, npts);
             }
         });
         NUSHT_HIP(hipGetLastError());
-        b += mb;
+        b += mb == 4 ? 4 : nmaps - b;  // the last one to three maps are one launch
     }
     return NUSHT_OK;
 }
@@ -1134,7 +1140,7 @@ int spread_group_impl(const nusht_plan_s* p, const double* vals, T* fine, int mb
     if (mb == 4)
         hipLaunchKernelGGL((k_pack_values<T, 4>), dim3(pblocks), dim3(256), 0, s, vals, npts,
                            packed);
-    else
+    else if (!spread_uses_tiles(p))  // (the tile kernels read single maps as they are)
         hipLaunchKernelGGL((k_pack_values<T, 1>), dim3(pblocks), dim3(256), 0, s, vals, npts,
                            packed);
     NUSHT_HIP(hipGetLastError());
@@ -1145,21 +1151,21 @@ int spread_group_impl(const nusht_plan_s* p, const double* vals, T* fine, int mb
             const PointBins pb = make_bins(p);
             const double* coef = es_coef_of<double>(p);
             double* sub = reinterpret_cast<double*>(p->Z);
-            const int ha = (p->fine_ra + kHaloRows - 1) / kHaloRows;
-            const dim3 hgrid((p->g.n2 + 511) / 512, ha + p->fine_rb / kHaloRows);
+            const unsigned hx = (p->g.n2 + 511) / 512;
+            const auto ha = [p](int r) { return (unsigned)((p->fine_ra + r - 1) / r + p->fine_rb / r); };
             NUSHT_WIDE_SWITCH(p->g.width, {
                 if (mb == 4) {
                     hipLaunchKernelGGL((k_spread_tile<WV, 4>), dim3(p->nslots), dim3(256), 0, s,
-                                       packed, pb, beta, coef, sub);
-                    hipLaunchKernelGGL((k_halo<WV, 4>), hgrid, dim3(256), 0, s, sub, p->tile_slot,
-                                       p->nt1, p->nt2, p->g.n1, p->g.n2, p->fine_ra, p->fine_rb,
-                                       fine, ms);
+                                       packed, 0, pb, beta, coef, sub);
+                    hipLaunchKernelGGL((k_halo<WV, 4>), dim3(hx, ha(1)), dim3(256), 0, s, sub,
+                                       p->nslots, p->tile_slot, p->nt1, p->nt2, p->g.n1, p->g.n2,
+                                       p->fine_ra, p->fine_rb, fine, ms);
                 } else {
-                    hipLaunchKernelGGL((k_spread_tile<WV, 1>), dim3(p->nslots), dim3(256), 0, s,
-                                       packed, pb, beta, coef, sub);
-                    hipLaunchKernelGGL((k_halo<WV, 1>), hgrid, dim3(256), 0, s, sub, p->tile_slot,
-                                       p->nt1, p->nt2, p->g.n1, p->g.n2, p->fine_ra, p->fine_rb,
-                                       fine, ms);
+                    hipLaunchKernelGGL((k_spread_tile<WV, 1>), dim3(p->nslots, mb), dim3(256), 0, s,
+                                       vals, npts, pb, beta, coef, sub);
+                    hipLaunchKernelGGL((k_halo<WV, 1>), dim3(hx, ha(2), mb), dim3(256), 0, s, sub,
+                                       p->nslots, p->tile_slot, p->nt1, p->nt2, p->g.n1, p->g.n2,
+                                       p->fine_ra, p->fine_rb, fine, ms);
                 }
             });
             NUSHT_HIP(hipGetLastError());

@@ -442,9 +442,15 @@ int ensure_capacity(nusht_plan_s* p, int nmaps)
     NUSHT_TRY(dmalloc((char**)&p->X, per * nmaps));
     NUSHT_TRY(dmalloc((char**)&p->Y, per * nmaps));
     p->Xbytes = p->Ybytes = per * nmaps;
-    if (!p->W) {
-        NUSHT_TRY(dmalloc((char**)&p->W, fine_spec));
-        p->Wbytes = fine_spec;
+    const size_t wb =
+        p->row_custom ? fine_spec * std::max<size_t>(1, std::min<size_t>(nmaps, kRowBatchBytes / fine_spec))
+                      : fine_spec;
+    if (wb > p->Wbytes) {
+        if (p->W) hipFree(p->W);
+        p->W = nullptr;
+        p->Wbytes = 0;
+        NUSHT_TRY(dmalloc((char**)&p->W, wb));
+        p->Wbytes = wb;
     }
     if (!p->V) NUSHT_TRY(dmalloc(&p->V, (size_t)g.npts * 4));
     // tile subgrids of the wide-kernel spreading: one group of up to four maps at a time

@@ -160,6 +160,8 @@ __global__ __launch_bounds__((RowShape<K, F>::NT)) void k_row_c2r(
     __shared__ C buf[N + N / 16];
     const int q = blockIdx.x, t = threadIdx.x;
     const int i = q < ra ? q : n1 - rb + (q - ra);
+    rows += (int64_t)blockIdx.y * n1 * rw;  // map of the launch
+    fine += (int64_t)blockIdx.y * n1 * (2 * N);
     const C* X = rows + (int64_t)i * rw;
     const int M = ncol - 1;
     // first pass (span 1) from HBM: Z[k] built from X[k] and X[N - k].  All of the thread's
@@ -230,6 +232,8 @@ __global__ __launch_bounds__((RowShape<K, F>::NT)) void k_row_r2c(
     __shared__ C buf[N + N / 16];
     const int q = blockIdx.x, t = threadIdx.x;
     const int i = q < ra ? q : n1 - rb + (q - ra);
+    rows += (int64_t)blockIdx.y * n1 * rw;  // map of the launch
+    fine += (int64_t)blockIdx.y * n1 * (2 * N);
     const C* z = reinterpret_cast<const C*>(fine + (int64_t)i * (2 * N));
     constexpr int NU = (N / R0 + S::NT - 1) / S::NT;
     C za[NU][R0];
@@ -627,7 +631,7 @@ bool rowfft_supported(const nusht_geometry& g) { return row_pow2(g) || mixrow_su
     }
 
 template <typename T, int KV, int FV, bool C2R>
-int launch_row_k(const nusht_plan_s* p, const void* in, void* out, int64_t rw, hipStream_t s)
+int launch_row_k(const nusht_plan_s* p, const void* in, void* out, int64_t rw, int nb, hipStream_t s)
 {
     using C = typename Cx<T>::type;
     const nusht_geometry& g = p->g;
@@ -635,11 +639,11 @@ int launch_row_k(const nusht_plan_s* p, const void* in, void* out, int64_t rw, h
     const C* tw = reinterpret_cast<const C*>(p->rowtw);
     if constexpr ((KV <= 13 || FV == 5) && lds_fits<T>(RowShape<KV, FV>::N)) {
         if (C2R)
-            hipLaunchKernelGGL((k_row_c2r<T, KV, FV>), dim3(nq), dim3(RowShape<KV, FV>::NT), 0, s,
+            hipLaunchKernelGGL((k_row_c2r<T, KV, FV>), dim3(nq, nb), dim3(RowShape<KV, FV>::NT), 0, s,
                                reinterpret_cast<const C*>(in), rw, g.mmax + 1,
                                reinterpret_cast<T*>(out), g.n1, p->fine_ra, p->fine_rb, tw);
         else
-            hipLaunchKernelGGL((k_row_r2c<T, KV, FV>), dim3(nq), dim3(RowShape<KV, FV>::NT), 0, s,
+            hipLaunchKernelGGL((k_row_r2c<T, KV, FV>), dim3(nq, nb), dim3(RowShape<KV, FV>::NT), 0, s,
                                reinterpret_cast<const T*>(in), g.n1, p->fine_ra, p->fine_rb,
                                reinterpret_cast<C*>(out), rw, g.mmax + 1, tw);
     } else {
@@ -651,27 +655,29 @@ int launch_row_k(const nusht_plan_s* p, const void* in, void* out, int64_t rw, h
 }
 
 template <bool C2R>
-int launch_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, hipStream_t s)
+int launch_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, int nb, hipStream_t s)
 {
     int K = 0, F = 1;
     split_len(p->g.n2 / 2, K, F);
     NUSHT_FK_SWITCH(F, K, {
-        if (p->g.dtype == NUSHT_MIXED) return launch_row_k<float, KV, FV, C2R>(p, in, out, rw, s);
-        return launch_row_k<double, KV, FV, C2R>(p, in, out, rw, s);
+        if (p->g.dtype == NUSHT_MIXED) return launch_row_k<float, KV, FV, C2R>(p, in, out, rw, nb, s);
+        return launch_row_k<double, KV, FV, C2R>(p, in, out, rw, nb, s);
     });
     return NUSHT_OK;
 }
 
-int launch_row_c2r(const nusht_plan_s* p, const void* rows, int64_t rw, void* fine, hipStream_t s)
+int launch_row_c2r(const nusht_plan_s* p, const void* rows, int64_t rw, void* fine, int nb,
+                   hipStream_t s)
 {
-    if (!row_pow2(p->g)) return launch_mix_row(p, rows, fine, rw, true, s);
-    return launch_row<true>(p, rows, fine, rw, s);
+    if (!row_pow2(p->g)) return launch_mix_row(p, rows, fine, rw, nb, true, s);
+    return launch_row<true>(p, rows, fine, rw, nb, s);
 }
 
-int launch_row_r2c(const nusht_plan_s* p, const void* fine, void* rows, int64_t rw, hipStream_t s)
+int launch_row_r2c(const nusht_plan_s* p, const void* fine, void* rows, int64_t rw, int nb,
+                   hipStream_t s)
 {
-    if (!row_pow2(p->g)) return launch_mix_row(p, fine, rows, rw, false, s);
-    return launch_row<false>(p, fine, rows, rw, s);
+    if (!row_pow2(p->g)) return launch_mix_row(p, fine, rows, rw, nb, false, s);
+    return launch_row<false>(p, fine, rows, rw, nb, s);
 }
 
 bool thetafft_supported(const nusht_geometry& g)
@@ -685,9 +691,13 @@ bool thetafft_supported(const nusht_geometry& g)
     return lds_fits<double>(n1) || (F == 1 && K == 14);
 }
 
+// The kernels that hold the DFT over the doubled circle take the lengths the kernels of this file
+// do not, and short columns of any length, where a call is bound by its launches (n1 <= 1024);
+// from there on the passes of this file with rocFFT's torus transform are the faster pair
+// (117 + 56 us against about 215 us scaled from n1 = 6048, at n1 = 8192).
 bool thetafft_with_torus(const nusht_geometry& g)
 {
-    return rowfft_supported(g) && !thetafft_supported(g) && mixtheta_supported(g);
+    return rowfft_supported(g) && (!thetafft_supported(g) || g.n1 <= 1024) && mixtheta_supported(g);
 }
 
 // columns whose complex values exceed the LDS (FP64, 16384) take the register-resident kernels

@@ -309,53 +309,75 @@ size_t fine_band_bytes(const nusht_plan_s* p)
     return (size_t)(p->g.mmax + 1) * p->g.n1 * 2 * fine_elem_bytes(p);
 }
 
-// Band spectrum -> fine grid of one map (N(ii)): theta pass in place over the band (unless the
+// maps whose row spectra fit in the row scratch together
+int row_batch(const nusht_plan_s* p, int nmaps)
+{
+    if (!p->row_custom) return 1;
+    const size_t per = (size_t)p->g.n1 * (p->g.mmax + 1) * 2 * fine_elem_bytes(p);
+    return (int)std::max<size_t>(1, std::min<size_t>(nmaps, p->Wbytes / per));
+}
+
+// Band spectra -> fine grids of nmaps maps (N(ii)): theta pass in place over the band (unless the
 // fused theta pass has already written the band's window rows), transpose into the row
 // spectrum of the window rows (p->W), phi pass into those rows of the grid.  Other rows of the
 // grid are left untouched (no window reads them).
-int fine_c2r(nusht_plan_s* p, char* band, char* real, hipStream_t s)
+int fine_c2r(nusht_plan_s* p, char* bands, char* reals, int nmaps, hipStream_t s)
 {
     const nusht_geometry& g = p->g;
     const size_t e = fine_elem_bytes(p);
     const size_t fw = (size_t)g.n2 / 2 + 1;
     char* rows = bytes(p->W);
-    if (!p->theta_custom) NUSHT_TRY(fft_exec(p, p->fine_col_inv, band, nullptr, s));
-    if (p->row_custom) {
-        NUSHT_TRY(launch_band_to_rows(p, band, rows, g.mmax + 1, s));
-        return launch_row_c2r(p, rows, g.mmax + 1, real, s);
-    }
-    NUSHT_TRY(launch_band_to_rows(p, band, rows, (int)fw, s));
-    NUSHT_TRY(fft_exec(p, p->fine_rowa_c2r, rows, real, s));
-    if (p->fine_rb > 0) {
-        const size_t r0 = (size_t)g.n1 - p->fine_rb;
-        NUSHT_TRY(fft_exec(p, p->fine_rowb_c2r, rows + r0 * fw * 2 * e, real + r0 * g.n2 * e, s));
+    const int step = row_batch(p, nmaps);
+    for (int b = 0; b < nmaps; b += step) {
+        const int nb = std::min(step, nmaps - b);
+        char* band = bands + b * fine_band_bytes(p);
+        char* real = reals + b * fine_real_bytes(p);
+        for (int i = 0; i < nb && !p->theta_custom; ++i)
+            NUSHT_TRY(fft_exec(p, p->fine_col_inv, band + i * fine_band_bytes(p), nullptr, s));
+        if (p->row_custom) {
+            NUSHT_TRY(launch_band_to_rows(p, band, rows, g.mmax + 1, nb, s));
+            NUSHT_TRY(launch_row_c2r(p, rows, g.mmax + 1, real, nb, s));
+            continue;
+        }
+        NUSHT_TRY(launch_band_to_rows(p, band, rows, (int)fw, 1, s));
+        NUSHT_TRY(fft_exec(p, p->fine_rowa_c2r, rows, real, s));
+        if (p->fine_rb > 0) {
+            const size_t r0 = (size_t)g.n1 - p->fine_rb;
+            NUSHT_TRY(fft_exec(p, p->fine_rowb_c2r, rows + r0 * fw * 2 * e, real + r0 * g.n2 * e, s));
+        }
     }
     return NUSHT_OK;
 }
 
-// Fine grid -> band spectrum of one map (N^H(ii)), reading only the window rows: phi pass
+// Fine grids -> band spectra of nmaps maps (N^H(ii)), reading only the window rows: phi pass
 // over those rows into p->W, transpose into the band (zeros for the other rows), theta pass
 // in place.  With the fused theta pass only the window rows of the band are written and its
 // theta pass runs later, with the deconvolution.
-int fine_r2c(nusht_plan_s* p, char* real, char* band, hipStream_t s)
+int fine_r2c(nusht_plan_s* p, char* reals, char* bands, int nmaps, hipStream_t s)
 {
     const nusht_geometry& g = p->g;
     const size_t e = fine_elem_bytes(p);
     const size_t fw = (size_t)g.n2 / 2 + 1;
     char* rows = bytes(p->W);
-    if (p->row_custom) {
-        NUSHT_TRY(launch_row_r2c(p, real, rows, g.mmax + 1, s));
-        NUSHT_TRY(launch_rows_to_band(p, rows, g.mmax + 1, band, s, p->theta_custom));
-        if (p->theta_custom) return NUSHT_OK;
-        return fft_exec(p, p->fine_col_fwd, band, nullptr, s);
+    const int step = row_batch(p, nmaps);
+    for (int b = 0; b < nmaps; b += step) {
+        const int nb = std::min(step, nmaps - b);
+        char* band = bands + b * fine_band_bytes(p);
+        char* real = reals + b * fine_real_bytes(p);
+        if (p->row_custom) {
+            NUSHT_TRY(launch_row_r2c(p, real, rows, g.mmax + 1, nb, s));
+            NUSHT_TRY(launch_rows_to_band(p, rows, g.mmax + 1, band, nb, s, p->theta_custom));
+        } else {
+            NUSHT_TRY(fft_exec(p, p->fine_rowa_r2c, real, rows, s));
+            if (p->fine_rb > 0) {
+                const size_t r0 = (size_t)g.n1 - p->fine_rb;
+                NUSHT_TRY(fft_exec(p, p->fine_rowb_r2c, real + r0 * g.n2 * e, rows + r0 * fw * 2 * e, s));
+            }
+            NUSHT_TRY(launch_rows_to_band(p, rows, (int)fw, band, 1, s));
+        }
+        for (int i = 0; i < nb && !p->theta_custom; ++i)
+            NUSHT_TRY(fft_exec(p, p->fine_col_fwd, band + i * fine_band_bytes(p), nullptr, s));
     }
-    NUSHT_TRY(fft_exec(p, p->fine_rowa_r2c, real, rows, s));
-    if (p->fine_rb > 0) {
-        const size_t r0 = (size_t)g.n1 - p->fine_rb;
-        NUSHT_TRY(fft_exec(p, p->fine_rowb_r2c, real + r0 * g.n2 * e, rows + r0 * fw * 2 * e, s));
-    }
-    NUSHT_TRY(launch_rows_to_band(p, rows, (int)fw, band, s));
-    NUSHT_TRY(fft_exec(p, p->fine_col_fwd, band, nullptr, s));
     return NUSHT_OK;
 }
 
@@ -410,9 +432,7 @@ int synthesis_to_fine(nusht_plan_s* p, const double* alm, int nmaps, hipStream_t
             NUSHT_TRY(launch_deconv_pad(p, p->X, p->Y, nmaps, 1, f32, s));
         stage_end(p, ST_DECONV, s);
         stage_begin(p, ST_FINE_FFT, s);
-        for (int b = 0; b < nmaps; ++b)
-            NUSHT_TRY(fine_c2r(p, bytes(p->Y) + b * fine_band_bytes(p),
-                               bytes(p->X) + b * fine_real_bytes(p), s));
+        NUSHT_TRY(fine_c2r(p, bytes(p->Y), bytes(p->X), nmaps, s));
         stage_end(p, ST_FINE_FFT, s);
         *fine_out = p->X;
     } else {
@@ -433,9 +453,7 @@ int synthesis_to_fine(nusht_plan_s* p, const double* alm, int nmaps, hipStream_t
         NUSHT_TRY(launch_deconv_pad(p, p->Y, p->X, nmaps, 0, f32, s));
         stage_end(p, ST_DECONV, s);
         stage_begin(p, ST_FINE_FFT, s);
-        for (int b = 0; b < nmaps; ++b)
-            NUSHT_TRY(fine_c2r(p, bytes(p->X) + b * fine_band_bytes(p),
-                               bytes(p->Y) + b * fine_real_bytes(p), s));
+        NUSHT_TRY(fine_c2r(p, bytes(p->X), bytes(p->Y), nmaps, s));
         stage_end(p, ST_FINE_FFT, s);
         *fine_out = p->Y;
     }
@@ -562,7 +580,8 @@ int adjoint_impl(nusht_plan_s* p, const double* map, double* alm, int nmaps, hip
     // N^H (i): spreading of each group of maps straight onto their fine grids (window rows)
     stage_begin(p, ST_POINTS, s);
     for (int b = 0; b < nmaps;) {
-        const int mb = group_width(nmaps, b);
+        // the tile kernels take the last one to three maps of a batch in one launch
+        const int mb = spread_uses_tiles(p) ? std::min(nmaps - b, 4) : group_width(nmaps, b);
         char* fine = bytes(p->X) + b * fine_real_bytes(p);
         if (f32)
             NUSHT_TRY(spread_group_f32(p, map + b * g.npts, reinterpret_cast<float*>(fine), mb, s));
@@ -573,9 +592,7 @@ int adjoint_impl(nusht_plan_s* p, const double* map, double* alm, int nmaps, hip
     stage_end(p, ST_POINTS, s);
     // N^H (ii): fine-grid R2C
     stage_begin(p, ST_FINE_FFT, s);
-    for (int b = 0; b < nmaps; ++b)
-        NUSHT_TRY(fine_r2c(p, bytes(p->X) + b * fine_real_bytes(p),
-                           bytes(p->Y) + b * fine_band_bytes(p), s));
+    NUSHT_TRY(fine_r2c(p, bytes(p->X), bytes(p->Y), nmaps, s));
     stage_end(p, ST_FINE_FFT, s);
     if (g.dfs_mode == NUSHT_DFS_FUSED) {
         stage_begin(p, ST_DECONV, s);
