@@ -18,6 +18,7 @@
 //    below 2^-200 (below 2^-144 where the test is made once per eight steps) are dropped: they
 //    cannot reach the FP64 result.
 #include "internal.h"
+#include "wave_sum.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -864,32 +865,6 @@ __global__ __launch_bounds__(kAdjWaves * 64, DET ? 3 : 4) void k_legendre_adj(
 // lmax 1023 / 2047 / 4095: 0.13 / 0.60 / 3.75 ms against 0.20 / 1.13 / 7.2 ms of the kernel above.  (The
 // same for two maps, 7 R instructions and four MFMAs per l, was slower than that kernel.)
 // ------------------------------------------------------------------------------------
-
-// the double of the lane that DPP control CTRL names (within rows of 16 lanes)
-template <int CTRL>
-__device__ inline double dpp_f64(double v)
-{
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-
-constexpr int kDppXor1 = 0xB1;  // quad_perm [1, 0, 3, 2]
-constexpr int kDppXor2 = 0x4E;  // quad_perm [2, 3, 0, 1]
-constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;
-
-// the sum of q[x & 3] over the row's 16 lanes, in lane x of each row
-__device__ inline double wave_rows(const double (&q)[4], int x)
-{
-    const bool o1 = x & 1, o2 = x & 2;
-    const double a = (o1 ? q[1] : q[0]) + dpp_f64<kDppXor1>(o1 ? q[0] : q[1]);
-    const double b = (o1 ? q[3] : q[2]) + dpp_f64<kDppXor1>(o1 ? q[2] : q[3]);
-    double v = (o2 ? b : a) + dpp_f64<kDppXor2>(o2 ? a : b);
-    v += dpp_f64<kDppRor4>(v);
-    v += dpp_f64<kDppRor8>(v);
-    return v;
-}
 
 template <int R, bool FUSED, typename InT>
 __global__ __launch_bounds__(64 * kSubWaves) void k_legendre_adj_one(

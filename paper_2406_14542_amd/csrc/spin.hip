@@ -26,6 +26,7 @@
 // W- the opposite, and even/odd-l accumulators serve both rings; the lanes of a block share m,
 // so the coefficient stream is wave-uniform (scalar loads); blocks of one m sit on one XCD.
 #include "internal.h"
+#include "wave_sum.h"
 
 #include <algorithm>
 #include <cmath>
@@ -176,12 +177,10 @@ __device__ inline void spin_step(const double4 c, double y, double& p, double& q
     q = qn;
 }
 
-// the scaled variant: rescales the lane's pair when it reaches kSpBig while k > 0; returns
-// whether the new values are live (k == 0)
-__device__ inline bool spin_step_scaled(const double4 c, double y, double& p, double& q,
-                                        double& pp, double& qp, int& k)
+// rescales the lane's pair when it has reached kSpBig while k > 0; returns whether it is live
+// (k == 0)
+__device__ inline bool spin_rescale(double& p, double& q, double& pp, double& qp, int& k)
 {
-    spin_step(c, y, p, q, pp, qp);
     const bool big = (k > 0) && fmax(fabs(p), fabs(q)) >= kSpBig;
     const double sc = big ? kSpUnit : 1.0;
     p *= sc;
@@ -190,6 +189,14 @@ __device__ inline bool spin_step_scaled(const double4 c, double y, double& p, do
     qp *= sc;
     k -= big ? 1 : 0;
     return k == 0;
+}
+
+// a step with the test: whether the new values are live
+__device__ inline bool spin_step_scaled(const double4 c, double y, double& p, double& q,
+                                        double& pp, double& qp, int& k)
+{
+    spin_step(c, y, p, q, pp, qp);
+    return spin_rescale(p, q, pp, qp, k);
 }
 
 template <typename OutT>
@@ -382,13 +389,17 @@ __device__ inline double2 folded(const InT* col, int j, int nr, int nt, double s
 }
 
 // Adjoint.  Each lane holds kSpAdjR ring pairs (j, j + 64, ...) and multiplies W+- of each
-// with its folded ring data, summing them in registers; the sums over the wave's ring pairs
-// are then formed per chunk of kSpLC values of l: every lane parks its 4 MB products per l in
-// LDS, the wave reads them back transposed (a row per lane group) and sums, and each wave adds
-// its sums into the zeroed output with FP64 atomics, with no barrier between the waves (the
-// blocks of one m run on one XCD: the atomics resolve in its L2; the order of those additions
-// is not fixed, see DET for the fixed-order variant).
-constexpr int kSpAdjR = 3;  // ring pairs per lane of the adjoint
+// with its folded ring data, summing them in registers; the sums over the wave's lanes are
+// matrix products with selector rows (wave_sum.h), four values of l per register, and DPP steps
+// within 16 lanes once per chunk of kSpLC = 4 values of l.  Each wave adds its sums into the
+// zeroed output with FP64 atomics, with no LDS and no barrier (the blocks of one m run on one
+// XCD: the atomics resolve in its L2; the order of those additions is not fixed, see DET for
+// the fixed-order variant).  A chunk's coefficients are fetched while the chunk before runs.
+// Bound by the FP64 VALU and the FP64 MFMAs, which share its units, and by latency at four waves
+// per SIMD: lmax 2047, one field 2.24 ms, two fields 3.68 ms, against 2.98 and 4.98 ms with sums
+// through LDS, three pairs per lane and the rescale test at every step.  One or three pairs per
+// lane (one field): 2.60 and 2.50 ms.
+constexpr int kSpAdjR = 2;  // ring pairs per lane of the adjoint
 
 // DET: instead of the atomic adds, wave w of the m's waves writes its sums (unscaled) to
 // alm + w * part_stride, a zeroed per-wave partial array that k_spin_adj_reduce then adds in
@@ -401,14 +412,7 @@ __global__ __launch_bounds__(256) void k_spin_adj(
     const int* __restrict__ jlive, int nr, int nt, int64_t part_stride)
 {
     constexpr int R = kSpAdjR;
-    constexpr int NV = 4 * MB;          // products per l per lane
-    constexpr int ROWS = kSpLC * NV;    // rows of one chunk
-    constexpr int LPR = 64 / ROWS;      // lanes per row in the transposed read
-    constexpr int PER = 64 / LPR;       // entries summed per lane
-    static_assert(ROWS * LPR == 64, "chunk shape");
-    // rows of 64 lane entries, the upper half shifted by one slot (entry e at e + e / 32):
-    // the transposed read's two lanes of a row then fall on different banks
-    __shared__ double buf[4][ROWS][66];
+    static_assert(kSpLC == 4, "four values of l per selector MFMA");
     __shared__ float pf_sink[4][64];
 
     int m, rb;
@@ -476,8 +480,9 @@ __global__ __launch_bounds__(256) void k_spin_adj(
             Y1[r][b] = even_plus ? umi : upl;
             Y2[r][b] = even_plus ? upl : umi;
         }
-        spin_start(j, nr, m, spin, km[m], ke[m], y[r], p[r], q[r], k[r]);
-        pp[r] = qp[r] = 0.0;
+        // the recurrence starts one step early: the step (0, 0, 0, -1) into l0 gives the start
+        spin_start(j, nr, m, spin, km[m], ke[m], y[r], pp[r], qp[r], k[r]);
+        p[r] = q[r] = 0.0;
         live[r] = k[r] == 0;
         any_scaled |= k[r] > 0;
     }
@@ -486,7 +491,9 @@ __global__ __launch_bounds__(256) void k_spin_adj(
     // with (A, B, C, D) = (X1, Y1, Y2, X2) for the even class and (X2, Y2, Y1, X1) for the odd
     //   cG.re += W+ A.x - W- B.y,  cG.im += W+ A.y + W- B.x
     //   cC.re += W+ C.x + W- D.y,  cC.im += W+ C.y - W- D.x
-    const int slot = lane + (lane >> 5);
+    double sel[4], d[MB][4];  // selector rows; sums of the chunk, component by component
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sel[i] = (lane & 3) == i ? 1.0 : 0.0;
     auto put = [&](int li, bool odd, bool gated, const bool (&on)[R]) {
         double v[MB][4];
 #pragma unroll
@@ -514,55 +521,42 @@ __global__ __launch_bounds__(256) void k_spin_adj(
 #pragma unroll
         for (int b = 0; b < MB; ++b)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) buf[wave][li * NV + 4 * b + t][slot] = v[b][t];
+            for (int t = 0; t < 4; ++t)
+                d[b][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(sel[li], v[b][t], d[b][t], 0, 0, 0);
     };
 
     int pf_at = l0 + 1;
     unsigned pf_keep = 0;
     const unsigned sink = __builtin_amdgcn_readfirstlane(
         (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)pf_sink[wave]);
+    const __attribute__((address_space(4))) double* crec =
+        (const __attribute__((address_space(4))) double*)rec;
+    double4 cn[kSpLC];
+    auto fetch = [&](int lf) {
+#pragma unroll
+        for (int li = 0; li < kSpLC; ++li) {
+            const int64_t at = 4 * (moff + min(lf + li, lmax));
+            cn[li] = make_double4(crec[at], crec[at + 1], crec[at + 2], crec[at + 3]);
+        }
+    };
+    fetch(l0);
+    cn[0] = make_double4(0.0, 0.0, 0.0, -1.0);
     for (int lc = l0; lc <= lmax; lc += kSpLC) {
         if (lc + 1 >= pf_at) {
             pf_keep ^= spin_touch<0>(rec, nullptr, 0, moff, lmax, lc + 1 + kSpPf, lane, sink);
             pf_at = lc + 1 + kSpPf;
         }
-        const bool sc = __any(any_scaled);
-        // the chunk's coefficients in one go: a scalar load waits on the same counter as
-        // the LDS writes of the steps, so none is issued between them
         double4 cc[kSpLC];
 #pragma unroll
-        for (int li = 0; li < kSpLC; ++li) cc[li] = rec[moff + min(lc + li, lmax)];
-        if (sc || lc + kSpLC - 1 > lmax || lc == l0) {
-            // some lane still scaled, the last chunk or the first: every step tested
+        for (int li = 0; li < kSpLC; ++li) cc[li] = cn[li];
+        fetch(lc + kSpLC);
 #pragma unroll
-            for (int li = 0; li < kSpLC; ++li) {
-                const int l = lc + li;
-                bool on[R];
+        for (int b = 0; b < MB; ++b)
 #pragma unroll
-                for (int r = 0; r < R; ++r) on[r] = false;
-                if (l <= lmax) {
-                    if (l > l0) {
-                        const double4 c = cc[li];
-                        if (sc) {
-                            any_scaled = false;
-#pragma unroll
-                            for (int r = 0; r < R; ++r) {
-                                live[r] = spin_step_scaled(c, y[r], p[r], q[r], pp[r], qp[r], k[r]);
-                                any_scaled |= !live[r];
-                            }
-                        } else {
-#pragma unroll
-                            for (int r = 0; r < R; ++r)
-                                spin_step(c, y[r], p[r], q[r], pp[r], qp[r]);
-                        }
-                    }
-#pragma unroll
-                    for (int r = 0; r < R; ++r) on[r] = live[r];
-                }
-                put(li, (li & 1) != 0, true, on);
-            }
-        } else {
-            // every lane live, every step in range
+            for (int t = 0; t < 4; ++t) d[b][t] = 0.0;
+        const bool sc = __any(any_scaled);
+        bool some = true;
+        if (!sc) {
             const bool all_on[R] = {};
 #pragma unroll
             for (int li = 0; li < kSpLC; ++li) {
@@ -570,37 +564,49 @@ __global__ __launch_bounds__(256) void k_spin_adj(
                 for (int r = 0; r < R; ++r) spin_step(cc[li], y[r], p[r], q[r], pp[r], qp[r]);
                 put(li, (li & 1) != 0, false, all_on);
             }
-        }
-        // transposed read of this wave's chunk
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int rr = lane / LPR, h = lane % LPR;
-        double acc = 0.0;
-#pragma unroll 8
-        for (int i = 0; i < PER; ++i) {
-            const int e = h * PER + i;
-            acc += buf[wave][rr][e + (e >> 5)];
-        }
+        } else {
+            // some lane still scaled: the rescale test once per chunk (four steps grow a value by
+            // less than 2^40, so it stays in range and what a lane misses of the chunk in which it
+            // comes down is below 2^-160)
+            bool here = false;
 #pragma unroll
-        for (int o = 1; o < LPR; o <<= 1) acc += __shfl_xor(acc, o);
-        if (h == 0) {
-            const int li = rr / NV, v = rr % NV;
-            const int l = lc + li;
-            // (imaginary parts of m = 0 stay zero: that coefficient is real)
-            if (l <= lmax && !(m == 0 && (v & 1))) {
-                const int b = v >> 2, t = v & 3;
-                const int64_t o = ((int64_t)(2 * b + (t >> 1)) * nalm + moff + l) * 2 + (t & 1);
-                if (DET)
-                    alm[(int64_t)(rb * nw + wave) * part_stride + o] = acc;
-                else
-                    atomicAdd(alm + o, -0.5 * acc);
+            for (int r = 0; r < R; ++r) here |= live[r];
+            some = __any(here);
+            if (some) {
+#pragma unroll
+                for (int li = 0; li < kSpLC; ++li) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) spin_step(cc[li], y[r], p[r], q[r], pp[r], qp[r]);
+                    put(li, (li & 1) != 0, true, live);
+                }
+            } else {
+#pragma unroll
+                for (int li = 0; li < kSpLC; ++li)
+#pragma unroll
+                    for (int r = 0; r < R; ++r) spin_step(cc[li], y[r], p[r], q[r], pp[r], qp[r]);
+            }
+            any_scaled = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                live[r] = spin_rescale(p[r], q[r], pp[r], qp[r], k[r]);
+                any_scaled |= !live[r];
             }
         }
-        // this wave's reads of buf are done before its next writes
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (!some) continue;  // (a partial array is zero there already)
+        // lane x < 4 of row i holds component x of l = lc + i
+        const int t = lane & 15, l = lc + (lane >> 4);
+#pragma unroll
+        for (int b = 0; b < MB; ++b) {
+            const double v = wave_rows(d[b], t);
+            // (imaginary parts of m = 0 stay zero: that coefficient is real)
+            if (t < 4 && l <= lmax && !(m == 0 && (t & 1))) {
+                const int64_t o = ((int64_t)(2 * b + (t >> 1)) * nalm + moff + l) * 2 + (t & 1);
+                if (DET)
+                    alm[(int64_t)(rb * nw + wave) * part_stride + o] = v;
+                else
+                    unsafeAtomicAdd(alm + o, -0.5 * v);
+            }
+        }
     }
     // no LDS-DMA write may be in flight when the workgroup's LDS is released
     asm volatile("s_waitcnt vmcnt(0)" ::"v"(pf_keep) : "memory");

@@ -171,3 +171,25 @@ def test_batches_in_one_launch(P, lmax, B, dtype, mode):
     for b in range(B):
         assert rel(f[b], p.synthesis(alm[b:b + 1].contiguous()).cpu().numpy()[0]) <= tol
         assert mrel(c[b], p.adjoint(d[b:b + 1].contiguous()).cpu().numpy()[0], lmax, lmax) <= tol
+
+
+@pytest.mark.parametrize("lmax,mmax,s,F,det,mode", [
+    (1, 1, 1, 1, False, "fused"), (2, 2, 2, 3, True, "fused"), (6, 5, 3, 2, False, "paper"),
+    (125, 125, 2, 1, False, "fused"), (126, 126, 1, 2, True, "paper"), (254, 200, 2, 1, True, "fused"),
+    (255, 255, 2, 2, False, "fused"), (509, 509, 30, 1, False, "fused"), (1023, 1000, 2, 1, False, "fused"),
+    (1500, 300, 1, 2, False, "fused")])
+def test_spin_adjoint_edges(P, oracle_mod, lmax, mmax, s, F, det, mode):
+    """The Wigner-d adjoint where its split can go wrong: fewer degrees than a chunk of four and
+    every remainder, 64 and 128 ring pairs per wave and one more, columns that stay scaled for
+    long (m near mmax), one and two fields, partial arrays.  Bound as in the spin tests (1e-11)."""
+    print(f"[spin adjoint lmax={lmax} mmax={mmax} s={s} F={F} det={det} {mode}]", flush=True)
+    rng = np.random.default_rng(3 * lmax + s)
+    th, ph = inputs.uniform_points(rng, 59)
+    d = rng.standard_normal((F, 2, th.size))
+    p = P.Plan(lmax, mmax, dev(th), dev(ph), 1e-12, deterministic=det, dfs_mode=mode)
+    c = p.adjoint_spin(s, dev(d)).cpu().numpy()
+    ref = oracle_mod.spin_adjoint(lmax, mmax, s, th, ph, d)
+    assert mrel(c, ref, lmax, mmax) <= 1e-11
+    if det:
+        assert np.array_equal(p.adjoint_spin(s, dev(d)).cpu().numpy(), c)
+    p.status()
