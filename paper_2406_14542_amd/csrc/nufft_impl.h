@@ -152,10 +152,14 @@ __device__ inline void es_taps_d(double d, double beta, double (&psi)[W], double
         const double z = (d - a) * c;
         const double q = (1.0 - z) * (1.0 + z);
         if (q > 0.0) {
-            const double sq = sqrt(q);
+            // sqrt(q) from 1 / sqrt(q) with one correction (as exact as sqrt), the division
+            // becomes a product (w = 14, eight maps of 2.1 M points: 1105 -> 1035 us)
+            const double rs = rsqrt(q);
+            const double s0 = q * rs;
+            const double sq = fma(0.5 * rs, fma(-s0, s0, q), s0);
             const double v = exp(beta * (sq - 1.0));
             psi[a] = v;
-            dpsi[a] = q > kDerivEdgeQ ? -v * beta * z / sq * c : 0.0;
+            dpsi[a] = q > kDerivEdgeQ ? -v * beta * z * rs * c : 0.0;
         } else {
             psi[a] = 0.0;
             dpsi[a] = 0.0;
