@@ -73,7 +73,7 @@ typedef struct {
     int deterministic;   /* nonzero: the adjoint adds in a fixed order, so repeated calls give
                             identical bits (the Legendre adjoint then writes per-pair-chunk
                             partial sums, nmaps * nalm * 16 bytes per 256 ring pairs, and adds
-                            them in order; spreading is fixed-order in every plan) */
+                            them in order, and every kernel is spread in a fixed order) */
     int kernel_eval;     /* NUSHT_KERNEL_POLY (default): interpolation and spreading form the ES
                             taps from per-tap polynomials of degree w fitted at plan time (used
                             when the fit deviates from the kernel by at most eps / 20);

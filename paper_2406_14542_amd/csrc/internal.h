@@ -228,11 +228,26 @@ inline int group_width(int nmaps, int b) { return (nmaps - b) >= 4 ? 4 : 1; }
 constexpr size_t kRowBatchBytes = 64u << 20;
 
 // Spreading strategy: the band sweep for every FP32 (mixed-precision) kernel, for FP64 kernels
-// of width <= 8 and for deterministic plans; tile subgrids (matrix cores) and a halo pass for
-// wider FP64 kernels (whose band sweep runs one map per pass).
+// of width <= 8 and for deterministic plans; tile subgrids and a halo pass for wider FP64 kernels
+// (whose band sweep runs one map per pass).
 inline bool spread_uses_tiles(const nusht_plan_s* p)
 {
     return p->g.dtype == NUSHT_F64 && p->g.width > 8 && !p->deterministic;
+}
+
+// Tile subgrids on the matrix cores, or with LDS atomics.  The matrix cores cost more per tile and
+// less per point, the less the wider the kernel (they use (w / 32)^2 of their products), and need the
+// tap polynomials (with taps from sqrt and exp they are slower at every density).  LDS / matrix
+// cores, with the sum, in us, lmax 1023, one map and four: w = 10 at 60 points per occupied tile
+// 80 / 97 and 313 / 402, at 300 190 / 199 and 622 / 665; w = 12 at 60 86 / 102 and 343 / 407, at 200
+// 163 / 166 and 546 / 568, at 300 219 / 212 and 706 / 688; w = 14 at 140 144 / 144 and 491 / 514, at 200
+// 179 / 174 and 603 / 593; w = 16 at 140 157 / 156 and 541 / 539.  The lines lie within 15 % of
+// these between lmax 255 and 1500.
+inline bool spread_on_mfma(const nusht_plan_s* p)
+{
+    if (!p->es_coef) return false;
+    const double per_tile = (double)p->g.npts / (p->nslots > 0 ? p->nslots : 1);
+    return per_tile >= 60.0 + 650.0 / (p->g.width - 8);
 }
 
 // ---- geometry (plan.hip) ----

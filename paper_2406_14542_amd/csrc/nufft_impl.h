@@ -14,7 +14,7 @@
 //    (k_spread_band): every fine cell is written once, with its points summed in a fixed
 //    order, and no atomics or partial grids are involved;
 //  * spreading, FP64 windows of w > 8: tile subgrids formed on the matrix cores
-//    (k_spread_tile) and a halo pass that sums, for every fine cell, the subgrids of the
+//    (k_spread_tile) or with LDS atomics (k_spread_lds) and a halo pass that sums, for every fine cell, the subgrids of the
 //    windows covering it (k_halo).
 // Offsets are formed in FP64 from FP64 coordinates before any cast to the kernel's type T.
 #pragma once
@@ -403,8 +403,8 @@ __global__ __launch_bounds__(256) void k_interp_deriv(const double* __restrict__
     }
 }
 
-// Spreading of wide FP64 kernels (w > 8), not deterministic: tile subgrids on the matrix cores
-// and a halo pass.
+// Spreading of wide FP64 kernels (w > 8), not deterministic, where spread_on_mfma says yes: tile
+// subgrids on the matrix cores and a halo pass.
 //
 // A subgrid is sum_p f_p psi1_p psi2_p^T, a product contracted over points: K = 4 points per
 // v_mfma_f64_16x16x4.  The tile's points are dealt to the block's four waves by the 16 x 16
@@ -420,15 +420,15 @@ __global__ __launch_bounds__(256) void k_interp_deriv(const double* __restrict__
 // are used) and FP64 vector work (2 (w + 1) FMAs of taps and the shifts), which share the FP64
 // units: 226 and 290 us of the 620 us at 8.4 M points, w = 12, one map.  One FP64 LDS atomic add
 // per tap and point, with taps from exp and sqrt, took 765 us there; with four maps of 2.1 M
-// points, w = 14, 562 -> 448 us.  The subgrids' sum 242 -> 141 us.  Tiles of a few points
-// (26, w = 14) are bound by the subgrid's write and no faster than before (149 -> 186 us for
-// four maps, the sum 157 -> 170 us, the packing pass of single maps gone).
+// points, w = 14, 562 -> 448 us.  The subgrids' sum 242 -> 141 us.  Tiles of a few points are
+// bound by the subgrid's write and slower here than with LDS atomics (w = 14, 26 points, four maps:
+// 186 against 149 us, the sum 170 against 157 us).
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 template <int W, int MB>
-__global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const double* __restrict__ vals, int64_t vstride, PointBins pb,
-                                                     double beta, const double* __restrict__ coef,
-                                                     double* __restrict__ sub)
+__global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(
+    const double* __restrict__ vals, int64_t vstride, PointBins pb,
+    const double* __restrict__ coef, double* __restrict__ sub)
 {
     constexpr int P = kTile + W - 1;
     constexpr int NB = 256;  // points per batch, one per thread
@@ -445,7 +445,7 @@ __global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const doub
     vals += blockIdx.y * vstride;  // map of the launch (MB = 1)
     double creg[W + 1];
 #pragma unroll
-    for (int k = 0; k <= W; ++k) creg[k] = coef && j < W ? coef[k * W + j] : 0.0;
+    for (int k = 0; k <= W; ++k) creg[k] = j < W ? coef[k * W + j] : 0.0;
     d4 acc[MB][2][2];
 #pragma unroll
     for (int b = 0; b < MB; ++b)
@@ -512,15 +512,8 @@ __global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const doub
             const double x1 = s_s1[at], x2 = s_s2[at];
             const int x = s_rc[at];
             const int r = x & 15, c = x >> 8;
-            double a, b;
-            if (coef) {
-                a = es_tap_poly<double, W>(x1, creg);
-                b = es_tap_poly<double, W>(x2, creg);
-            } else {
-                // d - j of the tap, from s = 2 d - (W - 1) (exact but for the last bit)
-                a = j < W ? es_value<double>((x1 + (double)(W - 1 - 2 * j)) / W, beta) : 0.0;
-                b = j < W ? es_value<double>((x2 + (double)(W - 1 - 2 * j)) / W, beta) : 0.0;
-            }
+            double a = es_tap_poly<double, W>(x1, creg);
+            double b = es_tap_poly<double, W>(x2, creg);
             // cell j of the window's first (second) block holds tap j - r (j + 16 - r)
             a = __shfl(a, (lane & 48) | ((j - r) & 15));
             b = __shfl(b, (lane & 48) | ((j - c) & 15));
@@ -568,6 +561,133 @@ __global__ __launch_bounds__(256, MB == 4 ? 2 : 4) void k_spread_tile(const doub
             }
             reinterpret_cast<double2*>(dst + m * (P * kSubCols))[e] = v;
         }
+    }
+}
+
+// Spreading of wide FP64 kernels (w > 8), not deterministic, where spread_on_mfma says no (few
+// points per tile, or taps from sqrt and exp): tile subgrids with LDS atomics.
+//
+// The block stages up to NB of the slot's points (tap offsets, first cells relative to the tile,
+// values) in LDS, then every wave takes four points at a time with 16 lanes per point, lane =
+// column tap: each lane forms its column tap psi2[col] and the row tap psi1[col] (POLY: from its
+// polynomial, whose coefficients it holds in registers; else from sqrt and exp), the row taps of the point are exchanged through a per-wave LDS row, and lane (point, col) adds
+// f psi1[a] psi2[col] into window rows r + a, a < W, of its column.  The window is planar
+// (map-major), so the lanes of one point add into consecutive words of one row.  The order of the
+// additions into a cell is not fixed: results can differ between runs by FP64 rounding.
+//
+// Tiles of a few points are bound by the write of the subgrid and its sum.  Single maps use the
+// layout of k_spread_tile; four maps are interleaved, [P][P][4] (k_halo4), which sums faster than
+// planar maps in rows of 48 (lmax 1023, w = 12, 20 points a tile: 294 us against 313).  Taps from
+// polynomials instead of sqrt and exp: lmax 1023, w = 12, 160 points a tile, 160 -> 143 us.
+template <int MB>
+struct SpreadPoint {
+    double d1, d2;  // offsets of the first taps, grid units (POLY: the polynomials' s)
+    int r, c;       // first tap cell relative to the tile
+    double f[MB];
+};
+
+template <int W, int MB, bool POLY>
+__global__ __launch_bounds__(256) void k_spread_lds(const double* __restrict__ vals,
+                                                    int64_t vstride, PointBins pb, double beta,
+                                                    const double* __restrict__ coef,
+                                                    double* __restrict__ sub)
+{
+    constexpr int P = kTile + W - 1;
+    constexpr int LPP = 16, PPW = 64 / LPP;
+    constexpr int NB = 128;  // points staged per batch
+    static_assert(W <= LPP && P < kSubCols, "one lane per column tap");
+    __shared__ double win[MB * P * P];
+    __shared__ SpreadPoint<MB> s_pt[NB];
+    __shared__ double s_p1[4][PPW][LPP];
+    const int slot = blockIdx.x;
+    const int tile = pb.slot_tile[slot];
+    const int r0 = (tile / pb.nt2) * kTile;
+    const int c0 = (tile % pb.nt2) * kTile;
+    const int t = threadIdx.x;
+    vals += blockIdx.y * vstride;  // map of the launch (MB = 1)
+    for (int e = t; e < MB * P * P; e += 256) win[e] = 0.0;
+    const int wave = t >> 6, lane = t & 63;
+    const int grp = lane / LPP, col = lane - grp * LPP;
+    const int p0 = pb.slot_off[slot], p1 = pb.slot_off[slot + 1];
+    double creg[W + 1];
+    if (POLY) {
+#pragma unroll
+        for (int k = 0; k <= W; ++k) creg[k] = col < W ? coef[k * W + col] : 0.0;
+    }
+    const auto tap = [&](double d) {
+        if (POLY) return es_tap_poly<double, W>(d, creg);
+        return col < W ? es_value<double>((d - col) * (2.0 / W), beta) : 0.0;
+    };
+    double* p1row = s_p1[wave][grp];
+    for (int base = p0; base < p1; base += NB) {
+        const int nb = min(NB, p1 - base);
+        __syncthreads();  // window cleared, or the previous batch consumed
+        if (t < nb) {
+            const int p = base + t;
+            SpreadPoint<MB> sp;
+            const int l1 = first_tap(pb.sth[p], pb.s1, W, sp.d1);
+            const int l2 = first_tap(pb.sph[p], pb.s2, W, sp.d2);
+            if (POLY) {
+                sp.d1 = 2.0 * sp.d1 - (double)(W - 1);
+                sp.d2 = 2.0 * sp.d2 - (double)(W - 1);
+            }
+            sp.r = min(max(wrap_index(l1, pb.n1) - r0, 0), kTile - 1);
+            sp.c = min(max(wrap_index(l2, pb.n2) - c0, 0), kTile - 1);
+            const int64_t src = pb.perm[p];
+#pragma unroll
+            for (int b = 0; b < MB; ++b) sp.f[b] = vals[src * MB + b];
+            s_pt[t] = sp;
+        }
+        __syncthreads();
+        // lane group g takes the points g S + i of the row-sorted batch: the PPW points of one
+        // step lie S apart, mostly in different rows, so that few lanes of an atomic add address
+        // the same cell (a point adds into rows r + a for the step's common a)
+        const int S = (nb + PPW - 1) / PPW;
+        for (int i = wave; i < S; i += 4) {
+            const int q = grp * S + i;
+            const bool live = q < nb;
+            const SpreadPoint<MB> sp = s_pt[live ? q : 0];
+            const bool act = live && col < W;
+            const double p2 = tap(sp.d2);
+            p1row[col] = tap(sp.d1);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            double pr[W];
+#pragma unroll
+            for (int a = 0; a < W; ++a) pr[a] = p1row[a];
+            // the next step rewrites the row: every lane's reads come first
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (act) {
+                double fb[MB];
+#pragma unroll
+                for (int b = 0; b < MB; ++b) fb[b] = sp.f[b] * p2;
+                double* w0 = win + sp.r * P + sp.c + col;
+#pragma unroll
+                for (int a = 0; a < W; ++a)
+#pragma unroll
+                    for (int b = 0; b < MB; ++b) atomicAdd(w0 + (b * P + a) * P, fb[b] * pr[a]);
+            }
+        }
+    }
+    __syncthreads();
+    double* dst = sub + ((int64_t)blockIdx.y * gridDim.x + slot) * (P * (MB == 4 ? P : kSubCols) * MB);
+    if (MB == 4) {
+        for (int e = t; e < P * P; e += 256) {
+#pragma unroll
+            for (int b = 0; b < MB; ++b) dst[e * MB + b] = win[b * P * P + e];
+        }
+        return;
+    }
+    // two columns per thread; the columns past the window are zero
+    for (int e = t; e < P * (kSubCols / 2); e += 256) {
+        const int r = e / (kSubCols / 2), c = 2 * (e - r * (kSubCols / 2));
+        double2 v;
+        v.x = c < P ? win[r * P + c] : 0.0;
+        v.y = c + 1 < P ? win[r * P + c + 1] : 0.0;
+        reinterpret_cast<double2*>(dst)[e] = v;
     }
 }
 
@@ -626,6 +746,41 @@ __global__ __launch_bounds__(256) void k_halo(const double* __restrict__ sub, in
             if (i0 + v < i1)
                 *reinterpret_cast<double2*>(fine + b * map_stride + (int64_t)(i0 + v) * n2 + j) =
                     acc[b][v];
+}
+
+// the sum of the subgrids of four interleaved maps (k_spread_lds): a cell of all four per thread
+template <int W>
+__global__ __launch_bounds__(256) void k_halo4(const double* __restrict__ sub,
+                                               const int* __restrict__ tile_slot, int nt1, int nt2,
+                                               int n1, int n2, int ra, int rb,
+                                               double* __restrict__ fine, int64_t map_stride)
+{
+    constexpr int P = kTile + W - 1, MB = 4;
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    // rows [0, ra) and [n1 - rb, n1): the only rows any window reaches
+    const int i = (int)blockIdx.y < ra ? (int)blockIdx.y : n1 - rb + ((int)blockIdx.y - ra);
+    if (j >= n2) return;
+    const int tr = i / kTile, rr = i - tr * kTile;
+    const int tc = j / kTile, cc = j - tc * kTile;
+    const int trp = tr == 0 ? nt1 - 1 : tr - 1;
+    const int tcp = tc == 0 ? nt2 - 1 : tc - 1;
+    double acc[MB];
+#pragma unroll
+    for (int b = 0; b < MB; ++b) acc[b] = 0.0;
+    auto add = [&](int t_r, int t_c, int r, int c) {
+        const int sl = tile_slot[t_r * nt2 + t_c];
+        if (sl < 0) return;
+        const double* s = sub + (int64_t)sl * (P * P * MB) + (r * P + c) * MB;
+#pragma unroll
+        for (int b = 0; b < MB; ++b) acc[b] += s[b];
+    };
+    add(tr, tc, rr, cc);
+    if (rr < W - 1) add(trp, tc, rr + kTile, cc);
+    if (cc < W - 1) add(tr, tcp, rr, cc + kTile);
+    if (rr < W - 1 && cc < W - 1) add(trp, tcp, rr + kTile, cc + kTile);
+    const int64_t off = (int64_t)i * n2 + j;
+#pragma unroll
+    for (int b = 0; b < MB; ++b) fine[b * map_stride + off] = acc[b];
 }
 
 // Spreading (type 1, N^H of Eq. 6): u(l1, l2) = sum_i f_i psi(row taps) psi(column taps), the
@@ -1181,24 +1336,44 @@ int spread_group_impl(const nusht_plan_s* p, const double* vals, T* fine, int mb
             if (p->nslots == 0) return NUSHT_OK;
             const PointBins pb = make_bins(p);
             const double* coef = es_coef_of<double>(p);
+            const bool mfma = spread_on_mfma(p);
             double* sub = reinterpret_cast<double*>(p->Z);
             const unsigned hx = (p->g.n2 + 511) / 512;
             const auto ha = [p](int r) { return (unsigned)((p->fine_ra + r - 1) / r + p->fine_rb / r); };
+#define NUSHT_SPREAD_LDS(MBV, grid, v, stride)                                                    \
+    do {                                                                                          \
+        if (coef)                                                                                 \
+            hipLaunchKernelGGL((k_spread_lds<WV, MBV, true>), grid, dim3(256), 0, s, v, stride, pb, \
+                               beta, coef, sub);                                                  \
+        else                                                                                      \
+            hipLaunchKernelGGL((k_spread_lds<WV, MBV, false>), grid, dim3(256), 0, s, v, stride, pb, \
+                               beta, coef, sub);                                                  \
+    } while (0)
             NUSHT_WIDE_SWITCH(p->g.width, {
-                if (mb == 4) {
+                if (mb == 4 && mfma) {
                     hipLaunchKernelGGL((k_spread_tile<WV, 4>), dim3(p->nslots), dim3(256), 0, s,
-                                       packed, 0, pb, beta, coef, sub);
+                                       packed, 0, pb, coef, sub);
                     hipLaunchKernelGGL((k_halo<WV, 4>), dim3(hx, ha(1)), dim3(256), 0, s, sub,
                                        p->nslots, p->tile_slot, p->nt1, p->nt2, p->g.n1, p->g.n2,
                                        p->fine_ra, p->fine_rb, fine, ms);
+                } else if (mb == 4) {
+                    NUSHT_SPREAD_LDS(4, dim3(p->nslots), packed, 0);
+                    hipLaunchKernelGGL((k_halo4<WV>),
+                                       dim3((p->g.n2 + 255) / 256, p->fine_ra + p->fine_rb),
+                                       dim3(256), 0, s, sub, p->tile_slot, p->nt1, p->nt2, p->g.n1,
+                                       p->g.n2, p->fine_ra, p->fine_rb, fine, ms);
                 } else {
-                    hipLaunchKernelGGL((k_spread_tile<WV, 1>), dim3(p->nslots, mb), dim3(256), 0, s,
-                                       vals, npts, pb, beta, coef, sub);
+                    if (mfma)
+                        hipLaunchKernelGGL((k_spread_tile<WV, 1>), dim3(p->nslots, mb), dim3(256),
+                                           0, s, vals, npts, pb, coef, sub);
+                    else
+                        NUSHT_SPREAD_LDS(1, dim3(p->nslots, mb), vals, npts);
                     hipLaunchKernelGGL((k_halo<WV, 1>), dim3(hx, ha(2), mb), dim3(256), 0, s, sub,
                                        p->nslots, p->tile_slot, p->nt1, p->nt2, p->g.n1, p->g.n2,
                                        p->fine_ra, p->fine_rb, fine, ms);
                 }
             });
+#undef NUSHT_SPREAD_LDS
             NUSHT_HIP(hipGetLastError());
             return NUSHT_OK;
         }

@@ -193,3 +193,30 @@ def test_spin_adjoint_edges(P, oracle_mod, lmax, mmax, s, F, det, mode):
     if det:
         assert np.array_equal(p.adjoint_spin(s, dev(d)).cpu().numpy(), c)
     p.status()
+
+
+@pytest.mark.parametrize("width,n,B,eps", [
+    (9, 1, 4, 1e-6), (9, 710, 1, 1e-6), (9, 711, 2, 1e-6), (9, 711, 5, 1e-6), (10, 127, 3, 1e-7),
+    (10, 384, 4, 1e-7), (10, 385, 4, 1e-7), (11, 129, 1, 1e-8), (11, 276, 3, 1e-8), (11, 277, 3, 1e-8),
+    (12, 222, 4, 1e-9), (12, 223, 7, 1e-9), (13, 255, 1, 1e-10), (13, 256, 1, 1e-10), (13, 257, 6, 1e-10),
+    (14, 168, 4, 1e-11), (14, 169, 4, 1e-11), (15, 512, 1, 1e-11), (15, 513, 4, 1e-11),
+    (16, 128, 5, 1e-11), (16, 141, 1, 1e-11), (16, 142, 1, 1e-11), (16, 3000, 2, 1e-11)])
+def test_spreading_kernels(P, width, n, B, eps):
+    """Both tile kernels of the wide FP64 spreading at the line between them (60 + 650 / (w - 8)
+    points a tile; one tile holds all points here), one point fewer and more than their batches of
+    128 and 256 points, every remainder of a batch of maps: against the band sweep of
+    a deterministic plan, which has the same taps.  Sums of at most 3000 terms agree to 1e-12."""
+    print(f"[spreading w={width} n={n} B={B}]", flush=True)
+    rng = np.random.default_rng(width * 1000 + n)
+    # the first taps of all points within one tile: 20 cells around its middle
+    g = P.geometry(90, 77, eps, width=width)
+    at = [int(0.4 * m / 64) * 32 + 16 + 0.5 * width for m in (g["n1"], g["n2"])]
+    th = (at[0] + 10.0 * (2 * rng.random(n) - 1)) * 2 * np.pi / g["n1"]
+    ph = (at[1] + 10.0 * (2 * rng.random(n) - 1)) * 2 * np.pi / g["n2"]
+    d = dev(rng.standard_normal((B, n)))
+    plans = [P.Plan(90, 77, dev(th), dev(ph), eps, width=width, deterministic=det)
+             for det in (False, True)]
+    g = plans[0].geometry
+    assert g["ntiles_used"] == 1 and g["kernel_eval"] == 0
+    c = [p.adjoint(d).cpu().numpy() for p in plans]
+    assert mrel(c[0], c[1], 90, 77) <= 1e-12

@@ -1,0 +1,49 @@
+"""Times of a stage against another call of the same process, where a kernel or a work split was
+once chosen that cost a class of calls more than it gained elsewhere.  The bounds lie midway between
+the two measured ratios; times are the smallest of many calls."""
+
+import math
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2406_14542_amd as P
+    P.lib()
+    return P
+
+
+def points(n, seed=5):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    u = torch.rand(2, n, generator=g, device="cuda", dtype=torch.float64)
+    return torch.acos(1 - 2 * u[0]), 2 * math.pi * u[1]
+
+
+def stage(p, call, name, repeats=25):
+    """smallest time of a stage over the calls, in us"""
+    call()
+    best = math.inf
+    for _ in range(repeats):
+        call()
+        best = min(best, 1e3 * p.stage_times()[name])
+    return best
+
+
+def test_spreading_with_exact_taps(P):
+    """Spreading 300 points a tile at w = 9 with taps from sqrt and exp against polynomial taps: 1.2
+    with LDS atomics, 1.8 where the matrix kernel formed the former too."""
+    n = 300 * 8192
+    th, ph = points(n)
+    d = torch.randn(1, n, device="cuda", dtype=torch.float64)
+    t = []
+    for taps in ("exact", "poly"):
+        p = P.Plan(1023, 1023, th, ph, 1e-7, width=9, kernel_eval=taps, timing=True)
+        assert p.geometry["kernel_eval"] == (1 if taps == "exact" else 0)
+        t.append(stage(p, lambda: p.adjoint(d), "points"))
+        print(f"[{taps}: {t[-1]:.1f} us]", flush=True)
+    assert t[0] <= 1.5 * t[1], t
