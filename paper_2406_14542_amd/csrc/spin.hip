@@ -388,30 +388,36 @@ __device__ inline double2 folded(const InT* col, int j, int nr, int nt, double s
     return v;
 }
 
-// Adjoint.  Each lane holds kSpAdjR ring pairs (j, j + 64, ...) and multiplies W+- of each
+// Adjoint.  Each lane holds R ring pairs (64 apart) and multiplies W+- of each
 // with its folded ring data, summing them in registers; the sums over the wave's lanes are
 // matrix products with selector rows (wave_sum.h), four values of l per register, and DPP steps
 // within 16 lanes once per chunk of kSpLC = 4 values of l.  Each wave adds its sums into the
 // zeroed output with FP64 atomics, with no LDS and no barrier (the blocks of one m run on one
 // XCD: the atomics resolve in its L2; the order of those additions is not fixed, see DET for
 // the fixed-order variant).  A chunk's coefficients are fetched while the chunk before runs.
+// Wave w of an m has the w-th span of pairs counted from the equator, so that 2^k + 1 pairs
+// (lmax = 2^k' - 1) leave the pole's pair alone to a wave, which then ends at once for every m but s.
 // Bound by the FP64 VALU and the FP64 MFMAs, which share its units, and by latency at four waves
-// per SIMD: lmax 2047, one field 2.24 ms, two fields 3.68 ms, against 2.98 and 4.98 ms with sums
-// through LDS, three pairs per lane and the rescale test at every step.  One or three pairs per
-// lane (one field): 2.60 and 2.50 ms.
-constexpr int kSpAdjR = 2;  // ring pairs per lane of the adjoint
+// per SIMD: lmax 1023 / 2047, one field 0.40 / 1.86 ms, two fields 0.59 / 2.94 ms, against 0.49 / 3.02
+// and 0.75 / 4.98 ms with sums through LDS, three pairs per lane and the rescale test at every step.
+// With spans counted from the pole, in blocks of four waves, a fifth wave of one pair took every m of
+// lmax 1023 through all of l in a block of its own: 0.55 and 0.83 ms.
+//
+// R = 2.  Deterministic plans take R = 3 above 512 pairs: as fast there (lmax 1023 one field 451
+// against 415 us, two 581 / 637, lmax 1535 953 / 1063 and 1626 / 1810 us), with a third fewer
+// partial arrays; below, R = 2 is the faster (lmax 511 132 / 152 us).
+inline int spin_adj_pairs_per_lane(int npairs, bool det) { return det && npairs > 512 ? 3 : 2; }
 
 // DET: instead of the atomic adds, wave w of the m's waves writes its sums (unscaled) to
 // alm + w * part_stride, a zeroed per-wave partial array that k_spin_adj_reduce then adds in
 // wave order (bit-identical results from run to run).
-template <int MB, typename InT, bool DET, bool FUSED>
+template <int R, int MB, typename InT, bool DET, bool FUSED>
 __global__ __launch_bounds__(256) void k_spin_adj(
     const InT* __restrict__ in, int64_t in_map_stride, int64_t in_row_stride,
     double* __restrict__ alm, int64_t nalm, int lmax, int mmax, int spin, int nbx,
     const double4* __restrict__ rec, const double* __restrict__ km, const int* __restrict__ ke,
     const int* __restrict__ jlive, int nr, int nt, int64_t part_stride)
 {
-    constexpr int R = kSpAdjR;
     static_assert(kSpLC == 4, "four values of l per selector MFMA");
     __shared__ float pf_sink[4][64];
 
@@ -420,10 +426,10 @@ __global__ __launch_bounds__(256) void k_spin_adj(
     if (m > mmax) return;  // uniform over the block
     const int npairs = (nr + 1) / 2;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int nw = blockDim.x >> 6;
-    const int wbase = (rb * nw + wave) * 64 * R;
-    // a wave below the first live pair of this m, or past the last pair, adds nothing
-    if (wbase + 64 * R <= jlive[m] || wbase >= npairs) return;
+    // wave pc of the m has the pairs [top - 64 R, top); one below the first live pair, or past the
+    // pole, adds nothing
+    const int pc = wave * nbx + rb, top = npairs - 64 * R * pc;
+    if (top <= jlive[m] || top <= 0) return;
     in += (int64_t)blockIdx.y * MB * 2 * in_map_stride;
     alm += (int64_t)blockIdx.y * MB * 2 * nalm * 2;
     const int64_t moff = (int64_t)m * (2 * lmax + 1 - m) / 2;
@@ -444,10 +450,10 @@ __global__ __launch_bounds__(256) void k_spin_adj(
     bool any_scaled = false;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int jraw = wbase + lane + 64 * r;
-        const int j = min(jraw, npairs - 1);
+        const int jraw = top - 1 - lane - 64 * r;
+        const int j = max(jraw, 0);
         const int js = nr - 1 - j;
-        const bool ok = jraw < npairs;
+        const bool ok = jraw >= 0;
 #pragma unroll
         for (int b = 0; b < MB; ++b) {
             double2 qn = make_double2(0.0, 0.0), un = qn, qs = qn, us = qn;
@@ -602,7 +608,7 @@ __global__ __launch_bounds__(256) void k_spin_adj(
             if (t < 4 && l <= lmax && !(m == 0 && (t & 1))) {
                 const int64_t o = ((int64_t)(2 * b + (t >> 1)) * nalm + moff + l) * 2 + (t & 1);
                 if (DET)
-                    alm[(int64_t)(rb * nw + wave) * part_stride + o] = v;
+                    alm[(int64_t)pc * part_stride + o] = v;
                 else
                     unsafeAtomicAdd(alm + o, -0.5 * v);
             }
@@ -816,14 +822,15 @@ int launch_spin_adjoint(nusht_plan_s* p, int spin, const void* in, double* alm, 
     NUSHT_TRY(ensure_spin_tables(p, spin));
     const nusht_geometry& g = p->g;
     const int npairs = (g.nrings + 1) / 2;
-    // four independent waves per block, kSpAdjR ring pairs per lane
-    const int nbx = (npairs + 256 * kSpAdjR - 1) / (256 * kSpAdjR);
+    const bool det = p->deterministic != 0;
+    // waves of one m, dealt to the fewest blocks of at most four, all of one size
+    const int R = spin_adj_pairs_per_lane(npairs, det), span = 64 * R;
+    const int nwm = (npairs + span - 1) / span;
+    const int nbx = (nwm + 3) / 4, wpb = (nwm + nbx - 1) / nbx;
     const int mpad = (g.mmax + 1 + 7) / 8 * 8;
     const int64_t row_stride = fused ? g.ntorus : g.nphi / 2 + 1;
     const int64_t map_stride = fused ? (int64_t)(g.mmax + 1) * g.ntorus : (int64_t)g.nrings * row_stride;
     const int64_t nz = (int64_t)nfields * 2 * g.nalm * 2;  // doubles of the output
-    const int nwm = 4 * nbx;                                // waves per m
-    const bool det = p->deterministic != 0;
     double* target = alm;
     if (det) {
         // per-wave partial sums, zeroed (waves below the first live pair write nothing)
@@ -849,30 +856,29 @@ int launch_spin_adjoint(nusht_plan_s* p, int spin, const void* in, double* alm, 
         const int mb = nfields - f >= 2 ? 2 : 1;
         const int groups = (nfields - f) / mb;
         double* af = target + (int64_t)f * 2 * g.nalm * 2;
-#define SPA(MBV, IT, D, FU)                                                                      \
-    hipLaunchKernelGGL((k_spin_adj<MBV, IT, D, FU>), dim3(nbx * mpad, groups), dim3(256), 0, s,   \
+#define SPA(RV, MBV, IT, D, FU)                                                                  \
+    hipLaunchKernelGGL((k_spin_adj<RV, MBV, IT, D, FU>), dim3(nbx * mpad, groups), dim3(64 * wpb), \
+                       0, s,                                                                      \
                        reinterpret_cast<const IT*>(in) + (int64_t)f * 2 * map_stride, map_stride, \
                        row_stride, af, g.nalm, g.lmax, g.mmax, spin, nbx, p->spin_rec,           \
                        p->spin_km, p->spin_ke, p->spin_jlive, g.nrings, g.ntorus, nz)
-        if (!fused) {
-            if (det) {
-                if (mb == 2) SPA(2, double2, true, false); else SPA(1, double2, true, false);
-            } else {
-                if (mb == 2) SPA(2, double2, false, false); else SPA(1, double2, false, false);
-            }
-        } else if (det) {
-            if (in_f32) {
-                if (mb == 2) SPA(2, float2, true, true); else SPA(1, float2, true, true);
-            } else {
-                if (mb == 2) SPA(2, double2, true, true); else SPA(1, double2, true, true);
-            }
-        } else {
-            if (in_f32) {
-                if (mb == 2) SPA(2, float2, false, true); else SPA(1, float2, false, true);
-            } else {
-                if (mb == 2) SPA(2, double2, false, true); else SPA(1, double2, false, true);
-            }
-        }
+#define SPA_MB(IT, FU)                                                            \
+    do {                                                                          \
+        if (det && R == 3) {                                                      \
+            if (mb == 2) SPA(3, 2, IT, true, FU); else SPA(3, 1, IT, true, FU);   \
+        } else if (det) {                                                         \
+            if (mb == 2) SPA(2, 2, IT, true, FU); else SPA(2, 1, IT, true, FU);   \
+        } else {                                                                  \
+            if (mb == 2) SPA(2, 2, IT, false, FU); else SPA(2, 1, IT, false, FU); \
+        }                                                                         \
+    } while (0)
+        if (!fused)
+            SPA_MB(double2, false);
+        else if (in_f32)
+            SPA_MB(float2, true);
+        else
+            SPA_MB(double2, true);
+#undef SPA_MB
 #undef SPA
         NUSHT_HIP(hipGetLastError());
         f += groups * mb;

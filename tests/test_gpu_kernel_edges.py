@@ -220,3 +220,28 @@ def test_spreading_kernels(P, width, n, B, eps):
     assert g["ntiles_used"] == 1 and g["kernel_eval"] == 0
     c = [p.adjoint(d).cpu().numpy() for p in plans]
     assert mrel(c[0], c[1], 90, 77) <= 1e-12
+
+
+@pytest.mark.parametrize("lmax,mmax,s,F,det", [
+    (126, 126, 2, 1, True), (255, 255, 2, 1, False), (255, 255, 1, 2, True), (511, 511, 3, 1, False),
+    (767, 200, 2, 1, True), (1022, 40, 2, 1, True), (1023, 40, 2, 2, False), (1023, 40, 2, 2, True),
+    (1151, 33, 1, 1, True)])
+def test_spin_adjoint_waves(P, oracle_mod, lmax, mmax, s, F, det):
+    """The Wigner-d adjoint's spans counted from the equator: a pole's pair alone in the last wave
+    (129, 257, 385, 513 and 577 pairs at two or three per lane), blocks of one to four waves, the
+    deterministic split on either side of 512 pairs; points next to the poles, so that column
+    m = s, to which alone the pole's pair contributes, is checked by itself.  Bound as in the spin
+    tests (1e-11)."""
+    print(f"[spin waves lmax={lmax} mmax={mmax} s={s} F={F} det={det}]", flush=True)
+    rng = np.random.default_rng(5 * lmax + s)
+    th, ph = inputs.uniform_points(rng, 41)
+    th[:4] = [0.0, 1e-3, np.pi - 1e-3, np.pi]
+    d = rng.standard_normal((F, 2, th.size))
+    p = P.Plan(lmax, mmax, dev(th), dev(ph), 1e-12, deterministic=det)
+    c = p.adjoint_spin(s, dev(d)).cpu().numpy()
+    ref = oracle_mod.spin_adjoint(lmax, mmax, s, th, ph, d)
+    assert mrel(c, ref, lmax, mmax) <= 1e-11
+    _, ms = inputs.ell_of_index(lmax, mmax)
+    assert rel(c[..., ms == s], ref[..., ms == s]) <= 1e-11
+    if det:
+        assert np.array_equal(p.adjoint_spin(s, dev(d)).cpu().numpy(), c)

@@ -47,3 +47,16 @@ def test_spreading_with_exact_taps(P):
         t.append(stage(p, lambda: p.adjoint(d), "points"))
         print(f"[{taps}: {t[-1]:.1f} us]", flush=True)
     assert t[0] <= 1.5 * t[1], t
+
+
+def test_spin_adjoint_past_a_power_of_two(P):
+    """The Wigner-d adjoint at 513 ring pairs (lmax 1023) against 451 (lmax 900): 1.3 with the pole's
+    pair in a wave of its own, 1.85 with an equator pair in one."""
+    t = []
+    for lmax in (900, 1023):
+        th, ph = points(500)
+        p = P.Plan(lmax, lmax, th, ph, 1e-5, timing=True)
+        d = torch.randn(1, 2, 500, device="cuda", dtype=torch.float64)
+        t.append(stage(p, lambda: p.adjoint_spin(2, d), "legendre"))
+        print(f"[lmax {lmax}: {t[-1]:.1f} us]", flush=True)
+    assert t[1] <= 1.55 * t[0], t
