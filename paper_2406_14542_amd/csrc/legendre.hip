@@ -1229,9 +1229,14 @@ int launch_legendre_adjoint(nusht_plan_s* p, const void* in, double* alm, int nm
         hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, s, alm,
                            nz);
     }
+    const int npairs = (g.nrings + 1) / 2;
     // one map left over after the groups of four has its own kernel; two or three fill a group of
-    // the other well enough
-    const int one = nmaps % 4 == 1 ? 1 : 0, many = nmaps - one;
+    // the other well enough.  Up to 256 pairs the other kernel has one block per m and leaves the chip
+    // idle: a group more costs it less than the launch (five maps at lmax 200 / 400: 25 / 50 us
+    // against 37 / 65), so only a lone map goes to its own kernel there (23 -> 19 us).  In a
+    // deterministic plan a map's bits do not depend on its batch: no map does.
+    const bool own = nmaps % 4 == 1 && (npairs > kAdjWaves * 64 || (nmaps == 1 && !p->deterministic));
+    const int one = own ? 1 : 0, many = nmaps - one;
     if (one) {
         const int64_t esz = in_f32 ? sizeof(float2) : sizeof(double2);
         const char* lin = reinterpret_cast<const char*>(in) + many * map_stride * esz;
@@ -1244,7 +1249,6 @@ int launch_legendre_adjoint(nusht_plan_s* p, const void* in, double* alm, int nm
             NUSHT_TRY((launch_adj_one<false, double2>(p, lin, lout, row_stride, s)));
     }
     if (!many) return NUSHT_OK;
-    const int npairs = (g.nrings + 1) / 2;
     const int npc = (npairs + kAdjWaves * 64 - 1) / (kAdjWaves * 64);
     int ppb = (npairs + npc - 1) / npc;
     ppb = ((ppb + 63) / 64) * 64;

@@ -245,3 +245,25 @@ def test_spin_adjoint_waves(P, oracle_mod, lmax, mmax, s, F, det):
     assert rel(c[..., ms == s], ref[..., ms == s]) <= 1e-11
     if det:
         assert np.array_equal(p.adjoint_spin(s, dev(d)).cpu().numpy(), c)
+
+
+@pytest.mark.parametrize("lmax,mmax,mode,det", [
+    (60, 60, "fused", False), (254, 200, "paper", True), (503, 503, "fused", False), (503, 90, "fused", True),
+    (511, 90, "fused", True), (511, 511, "paper", False), (629, 80, "fused", True), (639, 80, "fused", True),
+    (639, 639, "fused", False), (1259, 40, "fused", True), (1279, 40, "fused", True)])
+def test_left_over_map(P, oracle_mod, lmax, mmax, mode, det):
+    """One map by itself and as the fifth of a batch, at the lines between the adjoint's kernels and
+    splits: up to 256 ring pairs a map left over joins the group before it (253 and 257 pairs), one
+    to two pairs per lane after 320 (316, 321), two to four after 640 (631, 641).  A deterministic plan
+    gives the same bits for both.  Bound as in test_one_map_adjoint."""
+    print(f"[left over lmax={lmax} mmax={mmax} {mode} det={det}]", flush=True)
+    rng = np.random.default_rng(lmax + mmax)
+    th, ph = inputs.uniform_points(rng, 47)
+    d = rng.standard_normal((5, th.size))
+    ref = oracle_mod.adjoint(lmax, mmax, th, ph, d)
+    p = P.Plan(lmax, mmax, dev(th), dev(ph), 1e-12, dfs_mode=mode, deterministic=det)
+    one, five = p.adjoint(dev(d[4:])).cpu().numpy(), p.adjoint(dev(d)).cpu().numpy()
+    assert mrel(one, ref[4:], lmax, mmax) <= 1e-11 and mrel(five, ref, lmax, mmax) <= 1e-11
+    if det:
+        assert np.array_equal(five[4], one[0])
+    p.status()

@@ -60,3 +60,16 @@ def test_spin_adjoint_past_a_power_of_two(P):
         t.append(stage(p, lambda: p.adjoint_spin(2, d), "legendre"))
         print(f"[lmax {lmax}: {t[-1]:.1f} us]", flush=True)
     assert t[1] <= 1.55 * t[0], t
+
+
+def test_left_over_map_of_a_small_batch(P):
+    """The Legendre adjoint of five maps against four at lmax 200: 1.05 where the fifth joins the
+    launch, 1.5 with one of its own."""
+    th, ph = points(500)
+    p = P.Plan(200, 200, th, ph, 1e-5, timing=True)
+    t = []
+    for nmaps in (4, 5):
+        d = torch.randn(nmaps, 500, device="cuda", dtype=torch.float64)
+        t.append(stage(p, lambda: p.adjoint(d), "legendre"))
+        print(f"[{nmaps} maps: {t[-1]:.1f} us]", flush=True)
+    assert t[1] <= 1.28 * t[0], t
