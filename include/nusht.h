@@ -72,7 +72,7 @@ typedef struct {
     int timing;          /* nonzero: record one hipEvent pair per stage (nusht_stage_times) */
     int deterministic;   /* nonzero: the adjoint adds in a fixed order, so repeated calls give
                             identical bits (the Legendre adjoint then writes per-pair-chunk
-                            partial sums, nmaps * nalm * 16 bytes per 256 ring pairs, and adds
+                            partial sums, nmaps * nalm * 16 bytes per 128 to 256 ring pairs, and adds
                             them in order, and every kernel is spread in a fixed order) */
     int kernel_eval;     /* NUSHT_KERNEL_POLY (default): interpolation and spreading form the ES
                             taps from per-tap polynomials of degree w fitted at plan time (used

@@ -144,11 +144,9 @@ struct nusht_plan_s {
     size_t Xbytes = 0;
     void* Y = nullptr;
     size_t Ybytes = 0;
-    void* W = nullptr;           // fine row spectra [n1][n2/2+1] of one or more maps
+    void* W = nullptr;           // one map's fine row spectrum, where it has no room behind the bands
     size_t Wbytes = 0;
-    double* V = nullptr;         // point scratch [npts][4]: packed point values of one group
-    void* Z = nullptr;           // tile subgrids of the wide-kernel spreading [nslots][P][P][4]
-    size_t Zbytes = 0;
+    double* V = nullptr;         // point scratch: packed point values of one group of maps
     void* fftwork = nullptr;
     size_t fftwork_bytes = 0;
     double* red = nullptr;       // small reduction scratch for the CG solve
@@ -255,6 +253,8 @@ int compute_geometry(int lmax, int mmax, double eps, int dtype, const nusht_plan
                      nusht_geometry* g);
 int ensure_capacity(nusht_plan_s* p, int nmaps);
 size_t fine_elem_bytes(const nusht_plan_s* p);
+size_t fine_spec_bytes(const nusht_plan_s* p);  // full row spectra [n1][n2/2+1] of one map
+size_t fine_band_bytes(const nusht_plan_s* p);  // band spectrum [mmax+1][n1] of one map
 
 // ---- FFT helpers (transform.hip) ----
 int fft_exec(nusht_plan_s* p, FftPlan& f, void* in, void* out, hipStream_t s);

@@ -1315,7 +1315,7 @@ inline BandBins make_band_bins(const nusht_plan_s* p)
 // fine grids of those maps: the values are first packed [point][mb] in the caller's order into
 // the plan's point scratch, so that the kernels fetch a point's mb values with one load through
 // the caller's index.  Kernels of width <= 8 (and every kernel of a deterministic plan) use the
-// band sweep; wider ones the tile subgrids (into the plan's scratch Z) and the halo pass.
+// band sweep; wider ones the tile subgrids (into the plan's scratch Y) and the halo pass.
 template <typename T>
 int spread_group_impl(const nusht_plan_s* p, const double* vals, T* fine, int mb, T beta,
                       hipStream_t s)
@@ -1337,7 +1337,7 @@ int spread_group_impl(const nusht_plan_s* p, const double* vals, T* fine, int mb
             const PointBins pb = make_bins(p);
             const double* coef = es_coef_of<double>(p);
             const bool mfma = spread_on_mfma(p);
-            double* sub = reinterpret_cast<double*>(p->Z);
+            double* sub = reinterpret_cast<double*>(p->Y);  // (idle until the transforms)
             const unsigned hx = (p->g.n2 + 511) / 512;
             const auto ha = [p](int r) { return (unsigned)((p->fine_ra + r - 1) / r + p->fine_rb / r); };
 #define NUSHT_SPREAD_LDS(MBV, grid, v, stride)                                                    \

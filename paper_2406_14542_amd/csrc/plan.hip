@@ -418,15 +418,27 @@ size_t fine_elem_bytes(const nusht_plan_s* p)
     return p->g.dtype == NUSHT_MIXED ? sizeof(float) : sizeof(double);
 }
 
+size_t fine_spec_bytes(const nusht_plan_s* p)
+{
+    return (size_t)p->g.n1 * (p->g.n2 / 2 + 1) * 2 * fine_elem_bytes(p);
+}
+
+size_t fine_band_bytes(const nusht_plan_s* p)
+{
+    return (size_t)(p->g.mmax + 1) * p->g.n1 * 2 * fine_elem_bytes(p);
+}
+
 // Scratch for up to `nmaps` maps: X and Y each hold the largest per-map intermediate of
-// either mode times the batch.
+// either mode times the batch.  What is idle meanwhile serves twice: the subgrids of the tile
+// spreading lie in Y, which the adjoint uses only after it, and the row spectra of the library's own row
+// kernels lie behind the band spectra of the call, where those leave room (sigma >= 2: always).
 int ensure_capacity(nusht_plan_s* p, int nmaps)
 {
     if (nmaps <= p->bcap) return NUSHT_OK;
     const nusht_geometry& g = p->g;
     const size_t e = fine_elem_bytes(p);
     const size_t fine_real = (size_t)g.n1 * g.n2 * e;
-    const size_t fine_spec = (size_t)g.n1 * (g.n2 / 2 + 1) * 2 * e;
+    const size_t fine_spec = fine_spec_bytes(p);
     const size_t gpaper = (size_t)g.nrings * (g.nphi / 2 + 1) * 16;
     const size_t ring = (size_t)g.nrings * g.nphi * 8;
     const size_t torus = (size_t)g.ntorus * g.nphi * e;
@@ -434,32 +446,26 @@ int ensure_capacity(nusht_plan_s* p, int nmaps)
     const size_t gfused = (size_t)(g.mmax + 1) * g.ntorus * 2 * 8;  // doubled columns, <= c128
     size_t per = fine_real;
     for (size_t v : {fine_spec, gpaper, ring, torus, tspec, gfused}) per = v > per ? v : per;
+    // tile subgrids of one group of up to four maps
+    const size_t sub = (size_t)(kTile + g.width - 1) * kSubCols * e;
+    const size_t zb = spread_uses_tiles(p) ? (size_t)p->nslots * sub * std::min(nmaps, 4) : 0;
     NUSHT_HIP(hipDeviceSynchronize());
-    if (p->X) hipFree(p->X);
-    if (p->Y) hipFree(p->Y);
-    p->X = p->Y = nullptr;
+    for (void* b : {p->X, p->Y, p->W, (void*)p->V})
+        if (b) hipFree(b);
+    p->X = p->Y = p->W = nullptr;
+    p->V = nullptr;
+    p->Xbytes = p->Ybytes = p->Wbytes = 0;
     p->bcap = 0;
     NUSHT_TRY(dmalloc((char**)&p->X, per * nmaps));
-    NUSHT_TRY(dmalloc((char**)&p->Y, per * nmaps));
-    p->Xbytes = p->Ybytes = per * nmaps;
-    const size_t wb =
-        p->row_custom ? fine_spec * std::max<size_t>(1, std::min<size_t>(nmaps, kRowBatchBytes / fine_spec))
-                      : fine_spec;
-    if (wb > p->Wbytes) {
-        if (p->W) hipFree(p->W);
-        p->W = nullptr;
-        p->Wbytes = 0;
-        NUSHT_TRY(dmalloc((char**)&p->W, wb));
-        p->Wbytes = wb;
-    }
-    if (!p->V) NUSHT_TRY(dmalloc(&p->V, (size_t)g.npts * 4));
-    // tile subgrids of the wide-kernel spreading: one group of up to four maps at a time
-    if (spread_uses_tiles(p) && !p->Z) {
-        const size_t sub = (size_t)(kTile + g.width - 1) * kSubCols;
-        const size_t zb = (size_t)std::max(p->nslots, 1) * sub * 4 * e;
-        NUSHT_TRY(dmalloc((char**)&p->Z, zb));
-        p->Zbytes = zb;
-    }
+    p->Xbytes = per * nmaps;
+    NUSHT_TRY(dmalloc((char**)&p->Y, std::max(per * nmaps, zb)));
+    p->Ybytes = std::max(per * nmaps, zb);
+    // row spectra: of rocFFT's row plans, or where they do not fit behind the bands
+    const size_t band = fine_band_bytes(p);
+    const size_t wb = !p->row_custom ? fine_spec : (per - band) * nmaps < band ? band : 0;
+    NUSHT_TRY(dmalloc((char**)&p->W, wb));
+    p->Wbytes = wb;
+    NUSHT_TRY(dmalloc(&p->V, (size_t)g.npts * (nmaps >= 4 ? 4 : 1)));
     p->bcap = nmaps;
     return NUSHT_OK;
 }
@@ -848,7 +854,7 @@ void nusht_destroy(nusht_plan_t p)
     void* bufs[] = {p->rec,  p->cm_mant, p->cm_exp,   p->dec1,      p->dec2,      p->dec1f,
                     p->dec2f, p->sth,    p->sph,      p->perm,      p->iperm,     p->V,
                     p->slot_off,  p->slot_tile,
-                    p->tile_slot, p->boff, p->brec, p->dflag, p->dstatus, p->X,     p->Y,         p->W,   p->Z,
+                    p->tile_slot, p->boff, p->brec, p->dflag, p->dstatus, p->X,     p->Y,         p->W,
                     p->fftwork,   p->rowtw, p->thetatw, p->torustw,
                     p->red,      p->jlive,  p->adj_part, p->es_coef, p->es_coeff,
                     p->spin_rec, p->spin_km, p->spin_ke, p->spin_jlive};

@@ -303,31 +303,31 @@ inline char* bytes(void* v) { return reinterpret_cast<char*>(v); }
 
 // fine grid (real) of map b and its half spectrum, in elements of the plan's precision
 size_t fine_real_bytes(const nusht_plan_s* p) { return (size_t)p->g.n1 * p->g.n2 * fine_elem_bytes(p); }
-// band spectrum [mmax+1][n1] of one map
-size_t fine_band_bytes(const nusht_plan_s* p)
+// Row spectra of the window rows: scratch (behind the band spectra, which start the buffer X or Y,
+// or W) and the number of maps transformed together.
+char* row_scratch(const nusht_plan_s* p, char* bands, int nmaps, int& step)
 {
-    return (size_t)(p->g.mmax + 1) * p->g.n1 * 2 * fine_elem_bytes(p);
-}
-
-// maps whose row spectra fit in the row scratch together
-int row_batch(const nusht_plan_s* p, int nmaps)
-{
-    if (!p->row_custom) return 1;
-    const size_t per = (size_t)p->g.n1 * (p->g.mmax + 1) * 2 * fine_elem_bytes(p);
-    return (int)std::max<size_t>(1, std::min<size_t>(nmaps, p->Wbytes / per));
+    step = 1;
+    if (!p->row_custom) return bytes(p->W);
+    const size_t per = fine_band_bytes(p), used = (size_t)nmaps * per;  // (rows are as large as a band)
+    const size_t room = (bands == bytes(p->X) ? p->Xbytes : p->Ybytes) - used;
+    if (room < per) return bytes(p->W);
+    const size_t most = std::max<size_t>(kRowBatchBytes, fine_spec_bytes(p)) / per;
+    step = (int)std::max<size_t>(1, std::min<size_t>({(size_t)nmaps, most, room / per}));
+    return bands + used;
 }
 
 // Band spectra -> fine grids of nmaps maps (N(ii)): theta pass in place over the band (unless the
 // fused theta pass has already written the band's window rows), transpose into the row
-// spectrum of the window rows (p->W), phi pass into those rows of the grid.  Other rows of the
+// spectrum of the window rows, phi pass into those rows of the grid.  Other rows of the
 // grid are left untouched (no window reads them).
 int fine_c2r(nusht_plan_s* p, char* bands, char* reals, int nmaps, hipStream_t s)
 {
     const nusht_geometry& g = p->g;
     const size_t e = fine_elem_bytes(p);
     const size_t fw = (size_t)g.n2 / 2 + 1;
-    char* rows = bytes(p->W);
-    const int step = row_batch(p, nmaps);
+    int step;
+    char* rows = row_scratch(p, bands, nmaps, step);
     for (int b = 0; b < nmaps; b += step) {
         const int nb = std::min(step, nmaps - b);
         char* band = bands + b * fine_band_bytes(p);
@@ -350,7 +350,7 @@ int fine_c2r(nusht_plan_s* p, char* bands, char* reals, int nmaps, hipStream_t s
 }
 
 // Fine grids -> band spectra of nmaps maps (N^H(ii)), reading only the window rows: phi pass
-// over those rows into p->W, transpose into the band (zeros for the other rows), theta pass
+// over those rows into the row spectrum, transpose into the band (zeros for the other rows), theta pass
 // in place.  With the fused theta pass only the window rows of the band are written and its
 // theta pass runs later, with the deconvolution.
 int fine_r2c(nusht_plan_s* p, char* reals, char* bands, int nmaps, hipStream_t s)
@@ -358,8 +358,8 @@ int fine_r2c(nusht_plan_s* p, char* reals, char* bands, int nmaps, hipStream_t s
     const nusht_geometry& g = p->g;
     const size_t e = fine_elem_bytes(p);
     const size_t fw = (size_t)g.n2 / 2 + 1;
-    char* rows = bytes(p->W);
-    const int step = row_batch(p, nmaps);
+    int step;
+    char* rows = row_scratch(p, bands, nmaps, step);
     for (int b = 0; b < nmaps; b += step) {
         const int nb = std::min(step, nmaps - b);
         char* band = bands + b * fine_band_bytes(p);

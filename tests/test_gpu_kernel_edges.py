@@ -267,3 +267,66 @@ def test_left_over_map(P, oracle_mod, lmax, mmax, mode, det):
     if det:
         assert np.array_equal(five[4], one[0])
     p.status()
+
+
+def plan_scratch(p, B):
+    """bytes of one of a plan's two work buffers for B maps (the largest intermediate of either mode),
+    of the tile subgrids of wide FP64 kernels, and of the row spectrum that rocFFT's row plans need"""
+    g = p.geometry
+    e = 8 if p.dtype == "f64" else 4
+    per = max(g["n1"] * (g["n2"] // 2 + 1) * 2 * e, g["n1"] * g["n2"] * e,
+              g["nrings"] * (g["nphi"] // 2 + 1) * 16, (g["mmax"] + 1) * g["ntorus"] * 16)
+    wide = e == 8 and g["width"] > 8
+    sub = g["ntiles_used"] * (g["width"] + 31) * 48 * e * min(B, 4) if wide else 0
+    h = g["n2"] // 2
+    while h % 2 == 0:
+        h //= 2
+    rows = g["n1"] * (g["n2"] // 2 + 1) * 2 * e if e == 4 and h not in (1, 5) else 0
+    return B * per, sub, rows
+
+
+@pytest.mark.parametrize("lmax,n,B,dtype,eps", [
+    (511, 2000000, 1, "f64", 1e-10), (255, 400000, 8, "f64", 1e-12), (500, 300000, 3, "f64", 1e-12),
+    (383, 100000, 8, "mixed", 1e-5)])
+def test_scratch_of_first_calls(P, lmax, n, B, dtype, eps):
+    """Device memory that a plan takes in its first calls: two work buffers, the second at least as
+    large as the subgrids of the maps spread together, and the packed point values of a group.  (Row
+    spectra and subgrids lie in the work buffers, but for those of mixed plans of general length,
+    which rocFFT transforms.)  Slack: the allocator's granules."""
+    print(f"[scratch lmax={lmax} n={n} B={B} {dtype}]", flush=True)
+    rng = np.random.default_rng(lmax)
+    th, ph = (dev(x) for x in inputs.uniform_points(rng, n))
+    d = torch.randn(B, n, device="cuda", dtype=torch.float64)
+    for _ in range(2):  # the first plan loads the kernels and fills torch's cache
+        p = P.Plan(lmax, lmax, th, ph, eps, dtype=dtype)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        c = p.adjoint(d)
+        f = p.synthesis(c)
+        torch.cuda.synchronize()
+        used = free - torch.cuda.mem_get_info()[0]
+        work, sub, rows = plan_scratch(p, B)
+        del p, c, f
+    most = work + max(work, sub) + rows + 8 * n * (4 if B >= 4 else 1)
+    assert used <= most + (12 << 20), (used, most)
+
+
+@pytest.mark.parametrize("lmax,mmax,dtype,mode,sigma", [
+    (63, 63, "f64", "fused", 2.0), (90, 77, "f64", "paper", 2.0), (100, 100, "f64", "fused", 1.25),
+    (127, 40, "f64", "paper", 1.25), (127, 127, "mixed", "fused", 2.0), (90, 90, "mixed", "paper", 2.0)])
+def test_growing_batches(P, lmax, mmax, dtype, mode, sigma):
+    """Batches of 1, 6, 2 and 9 maps through one plan (scratch that grows and is used in part) give
+    what new plans give, row spectra behind the bands or, at sigma = 1.25 and few maps, apart: the
+    same arithmetic but for the order of some sums (1e-13 FP64, 1e-6 mixed)."""
+    print(f"[growing lmax={lmax} mmax={mmax} {dtype} {mode} {sigma}]", flush=True)
+    rng = np.random.default_rng(lmax + mmax)
+    th, ph = (dev(x) for x in inputs.uniform_points(rng, 900))
+    eps, tol = (1e-8, 1e-13) if dtype == "f64" else (1e-4, 1e-6)
+    new = lambda: P.Plan(lmax, mmax, th, ph, eps, dtype=dtype, dfs_mode=mode, sigma=sigma)
+    p = new()
+    for B in (1, 6, 2, 9, 1):
+        alm, d = dev(inputs.red_alm(rng, lmax, mmax, B)), dev(rng.standard_normal((B, 900)))
+        q = new()
+        assert rel(p.synthesis(alm).cpu().numpy(), q.synthesis(alm).cpu().numpy()) <= tol
+        c = p.adjoint(d).cpu().numpy()
+        assert mrel(c, q.adjoint(d).cpu().numpy(), lmax, mmax) <= tol
