@@ -61,6 +61,13 @@ struct Err {
 
 void set_last_error(const char* what, const char* why);
 
+// A length and its radices, four bits each, first pass lowest.
+struct MixLen {
+    int n = 0, np = 0;
+    unsigned long long code = 0;
+    __host__ __device__ int radix(int p) const { return (int)(code >> (4 * p)) & 15; }
+};
+
 // One rocFFT transform with its execution info (stream and work buffer bound per call).
 struct FftPlan {
     rocfft_plan plan = nullptr;
@@ -181,12 +188,14 @@ struct nusht_plan_s {
     // on row spectra of width mmax + 1 (no zero columns), instead of the rocFFT row plans.
     bool row_custom = false;
     void* rowtw = nullptr;  // [n2] e^{2 pi i k / n2} in the plan's FFT precision
+    nusht::MixLen mix_row;  // n2 / 2, where mixfft.hip transforms the rows
     // Fused mode with n1 that fits in LDS (or 2^14): the theta pass and the deconvolution run
     // as one kernel per direction (rowfft.hip, mixfft.hip) instead of the rocFFT column plans and
     // the pad / truncate kernels.  theta_torus: that kernel holds the DFT over the doubled circle
     // (F) as well.
     bool theta_custom = false;
     bool theta_torus = false;
+    nusht::MixLen mix_torus, mix_theta;  // N_t and n1 (theta_torus)
     void* torustw = nullptr;  // [2 N_t] e^{2 pi i k / (2 N_t)} (theta_torus)
     void* thetatw = nullptr;  // [2 n1] e^{2 pi i k / (2 n1)} in the plan's FFT precision
 
@@ -305,6 +314,7 @@ int launch_rows_to_band(const nusht_plan_s* p, const void* rows, int rw, void* b
 
 // ---- fine-grid row transforms (rowfft.hip: 2^K and 5 2^K, mixfft.hip: other lengths) ----
 bool rowfft_supported(const nusht_geometry& g);
+bool row_pow2(const nusht_geometry& g);  // 2^K or 5 2^K: rowfft.hip
 // window rows of nb maps: rows [nb][n1][rw] (columns 0 .. mmax) <-> real fine grids [nb][n1][n2]
 int launch_row_c2r(const nusht_plan_s* p, const void* rows, int64_t rw, void* fine, int nb,
                    hipStream_t s);
@@ -313,16 +323,12 @@ int launch_row_r2c(const nusht_plan_s* p, const void* fine, void* rows, int64_t 
 // theta pass fused with the deconvolution, maps [0, nmaps): torus spectrum cs [b][mmax+1][N_t]
 // <-> band spectrum [b][mmax+1][n1] (window rows only)
 bool thetafft_supported(const nusht_geometry& g);
-// A length and its radices, four bits each, first pass lowest.
-struct MixLen {
-    int n, np;
-    unsigned long long code;
-    __host__ __device__ int radix(int p) const { return (int)(code >> (4 * p)) & 15; }
-};
 // the fused theta pass of this geometry also holds the DFT over the doubled circle
 bool thetafft_with_torus(const nusht_geometry& g);
 bool mixrow_supported(const nusht_geometry& g);
 bool mixtheta_supported(const nusht_geometry& g);
+// the radices of n; false if it has none or fits one pass
+bool mix_len(int n, MixLen* m);
 int launch_mix_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, int nb,
                    bool c2r, hipStream_t s);
 int launch_mix_theta(const nusht_plan_s* p, const void* in, void* out, int nmaps, bool inv,

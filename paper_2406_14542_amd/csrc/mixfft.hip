@@ -340,6 +340,8 @@ bool factor(int n, int maxr, int depth, int* cur, int* best, int& nbest, int& sb
     return any;
 }
 
+}  // namespace
+
 // Two passes at least (one reads HBM, one writes it).  Odd radices first: their stores of stride
 // R in the first pass fall on distinct banks.
 bool mix_len(int n, MixLen* m)
@@ -354,8 +356,6 @@ bool mix_len(int n, MixLen* m)
             if ((best[i] & 1) == odd) m->code |= (unsigned long long)best[i] << (4 * m->np++);
     return true;
 }
-
-}  // namespace
 
 // Both are decided on the geometry alone: every length of the geometry is 7-smooth, so the limit
 // is the LDS of one workgroup (N <= 9035: lmax about 2200 at sigma 2).
@@ -377,17 +377,13 @@ bool mixtheta_supported(const nusht_geometry& g)
 int launch_mix_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, int nb,
                    bool c2r, hipStream_t s)
 {
-    MixLen m;
-    if (!mix_len(p->g.n2 / 2, &m)) return NUSHT_EINVAL;
-    return mix_row<double>(p, m, in, out, rw, nb, c2r, s);
+    return mix_row<double>(p, p->mix_row, in, out, rw, nb, c2r, s);
 }
 
 int launch_mix_theta(const nusht_plan_s* p, const void* in, void* out, int nmaps, bool inv,
                      hipStream_t s)
 {
-    MixLen mt, mn;
-    if (!mix_len(p->g.ntorus, &mt) || !mix_len(p->g.n1, &mn)) return NUSHT_EINVAL;
-    return mix_theta<double>(p, mt, mn, in, out, nmaps, inv, s);
+    return mix_theta<double>(p, p->mix_torus, p->mix_theta, in, out, nmaps, inv, s);
 }
 
 }  // namespace nusht

@@ -601,7 +601,7 @@ static bool len_supported(int K, int F)
 }
 
 // rows of 2^K or 5 2^K: the kernels of this file; other lengths: mixfft.hip
-static bool row_pow2(const nusht_geometry& g)
+bool row_pow2(const nusht_geometry& g)
 {
     const int n2 = g.n2;
     int K, F;
@@ -669,14 +669,14 @@ int launch_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, int
 int launch_row_c2r(const nusht_plan_s* p, const void* rows, int64_t rw, void* fine, int nb,
                    hipStream_t s)
 {
-    if (!row_pow2(p->g)) return launch_mix_row(p, rows, fine, rw, nb, true, s);
+    if (p->mix_row.n) return launch_mix_row(p, rows, fine, rw, nb, true, s);
     return launch_row<true>(p, rows, fine, rw, nb, s);
 }
 
 int launch_row_r2c(const nusht_plan_s* p, const void* fine, void* rows, int64_t rw, int nb,
                    hipStream_t s)
 {
-    if (!row_pow2(p->g)) return launch_mix_row(p, fine, rows, rw, nb, false, s);
+    if (p->mix_row.n) return launch_mix_row(p, fine, rows, rw, nb, false, s);
     return launch_row<false>(p, fine, rows, rw, nb, s);
 }
 

@@ -158,12 +158,16 @@ int create_fft_plans(nusht_plan_s* p)
     const size_t fw = (size_t)g.n2 / 2 + 1;
     const size_t ncol = (size_t)g.mmax + 1;
     p->row_custom = rowfft_supported(g);
+    if (p->row_custom && !row_pow2(g)) mix_len(g.n2 / 2, &p->mix_row);
     p->theta_torus = thetafft_with_torus(g);
     p->theta_custom = p->theta_torus || thetafft_supported(g);
     if (p->theta_custom) {
         NUSHT_TRY(make_twiddles(2 * g.n1, g.dtype == NUSHT_MIXED, &p->thetatw));
-        if (p->theta_torus)
+        if (p->theta_torus) {
+            mix_len(g.ntorus, &p->mix_torus);
+            mix_len(g.n1, &p->mix_theta);
             NUSHT_TRY(make_twiddles(2 * g.ntorus, g.dtype == NUSHT_MIXED, &p->torustw));
+        }
     } else {
         NUSHT_TRY(make_fft_1d(p->fine_col_inv, rocfft_transform_type_complex_inverse, prec, g.n1,
                               ncol, 1, g.n1, 1, g.n1, rocfft_placement_inplace));

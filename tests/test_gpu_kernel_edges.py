@@ -330,3 +330,22 @@ def test_growing_batches(P, lmax, mmax, dtype, mode, sigma):
         assert rel(p.synthesis(alm).cpu().numpy(), q.synthesis(alm).cpu().numpy()) <= tol
         c = p.adjoint(d).cpu().numpy()
         assert mrel(c, q.adjoint(d).cpu().numpy(), lmax, mmax) <= tol
+
+
+@pytest.mark.parametrize("lmax,mmax,B,mode", [
+    (48, 48, 2, "fused"), (1890, 300, 1, "fused"), (2010, 200, 1, "fused"), (2010, 2010, 1, "paper"),
+    (2200, 2200, 1, "fused"), (4100, 4100, 1, "fused"), (4230, 4210, 1, "paper")])
+def test_general_lengths_fp64(P, oracle_mod, lmax, mmax, B, mode):
+    """The FP64 general-length kernels where the lists above do not reach: radix 2 (98 = 7 7 2), columns of
+    7680 and 8064 (1024 threads at 8 values each), rows of 8064, rows of 8400 and 8640 (9 values per thread
+    in the row kernels, above mmax 4096), columns of 8960.  Bound as there."""
+    print(f"[lengths lmax={lmax} mmax={mmax} B={B} {mode}]", flush=True)
+    rng = np.random.default_rng(13 * lmax + mmax)
+    th, ph = inputs.uniform_points(rng, 29)
+    p = P.Plan(lmax, mmax, dev(th), dev(ph), 1e-12, dfs_mode=mode)
+    alm = inputs.red_alm(rng, lmax, mmax, B)
+    f = p.synthesis(dev(alm)).cpu().numpy()
+    assert rel(f, oracle_mod.synthesis(lmax, mmax, th, ph, alm)) <= 1e-11
+    d = rng.standard_normal((B, th.size))
+    c = p.adjoint(dev(d)).cpu().numpy()
+    assert mrel(c, oracle_mod.adjoint(lmax, mmax, th, ph, d), lmax, mmax) <= 1e-11
