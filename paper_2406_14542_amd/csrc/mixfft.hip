@@ -26,6 +26,9 @@
 namespace nusht {
 namespace {
 
+using T = double;
+using C = double2;
+
 // One pass of radix R and span ns over N values: butterfly b reads ld(b + r N / R), output r goes
 // to st((b - j) R + j + r ns) with j = b mod ns.  tw[m] = e^{2 pi i m / (2 N)}.  V: values per
 // thread (N <= V nt).  BAR: loads and stores meet in the same LDS array.
@@ -126,7 +129,6 @@ __device__ __forceinline__ void mix_fft(const MixLen& m, C* buf, int t, int nt, 
     mix_any<DIR, V, false, LDSOUT>(m.radix(m.np - 1), t, nt, m.n, ns, tw, from, st);
 }
 
-template <typename C>
 __device__ inline C* mix_lds()
 {
     extern __shared__ char mix_lds_raw[];
@@ -134,14 +136,13 @@ __device__ inline C* mix_lds()
 }
 
 // C2R of window rows (the half-length route of rowfft.hip): blockIdx.x = compact window row
-template <typename T, int V>
-__global__ __launch_bounds__(1024) void k_mix_c2r(MixLen m, const typename Cx<T>::type* __restrict__ rows,
+template <int V>
+__global__ __launch_bounds__(1024) void k_mix_c2r(MixLen m, const C* __restrict__ rows,
                                                  int64_t rw, int ncol, T* __restrict__ fine, int n1,
                                                  int ra, int rb,
-                                                 const typename Cx<T>::type* __restrict__ tw)
+                                                 const C* __restrict__ tw)
 {
-    using C = typename Cx<T>::type;
-    C* buf = mix_lds<C>();
+    C* buf = mix_lds();
     const int q = blockIdx.x, N = m.n, M = ncol - 1;
     const int i = q < ra ? q : n1 - rb + (q - ra);
     rows += (int64_t)blockIdx.y * n1 * rw;  // map of the launch
@@ -164,14 +165,13 @@ __global__ __launch_bounds__(1024) void k_mix_c2r(MixLen m, const typename Cx<T>
 }
 
 // R2C of window rows, columns 0 .. ncol-1 of each row's spectrum
-template <typename T, int V>
+template <int V>
 __global__ __launch_bounds__(1024) void k_mix_r2c(MixLen m, const T* __restrict__ fine, int n1, int ra,
-                                                 int rb, typename Cx<T>::type* __restrict__ rows,
+                                                 int rb, C* __restrict__ rows,
                                                  int64_t rw, int ncol,
-                                                 const typename Cx<T>::type* __restrict__ tw)
+                                                 const C* __restrict__ tw)
 {
-    using C = typename Cx<T>::type;
-    C* buf = mix_lds<C>();
+    C* buf = mix_lds();
     const int q = blockIdx.x, N = m.n;
     const int i = q < ra ? q : n1 - rb + (q - ra);
     rows += (int64_t)blockIdx.y * n1 * rw;  // map of the launch
@@ -194,15 +194,14 @@ __global__ __launch_bounds__(1024) void k_mix_r2c(MixLen m, const T* __restrict_
 
 // synthesis: doubled Legendre columns cs[b][mu][t] (t < N_t) -> band[b][mu][i], window rows only:
 // DFT over t, entries |k| <= L times the deconvolution factors, zero-padded DFT back over n1
-template <typename T, int V>
+template <int V>
 __global__ __launch_bounds__(1024) void k_mix_theta_inv(
-    MixLen mt, MixLen mn, const typename Cx<T>::type* __restrict__ cs,
-    typename Cx<T>::type* __restrict__ band, int lmax, const T* __restrict__ d1,
-    const T* __restrict__ d2, int ra, int rb, const typename Cx<T>::type* __restrict__ twt,
-    const typename Cx<T>::type* __restrict__ twn)
+    MixLen mt, MixLen mn, const C* __restrict__ cs,
+    C* __restrict__ band, int lmax, const T* __restrict__ d1,
+    const T* __restrict__ d2, int ra, int rb, const C* __restrict__ twt,
+    const C* __restrict__ twn)
 {
-    using C = typename Cx<T>::type;
-    C* buf = mix_lds<C>();
+    C* buf = mix_lds();
     const int t = threadIdx.x, nt = blockDim.x;
     const int64_t col = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     const C* src = cs + col * mt.n;
@@ -229,15 +228,14 @@ __global__ __launch_bounds__(1024) void k_mix_theta_inv(
 }
 
 // adjoint: band[b][mu][i] (window rows; the others are zero) -> columns cs[b][mu][t]
-template <typename T, int V>
+template <int V>
 __global__ __launch_bounds__(1024) void k_mix_theta_fwd(
-    MixLen mt, MixLen mn, const typename Cx<T>::type* __restrict__ band,
-    typename Cx<T>::type* __restrict__ cs, int lmax, const T* __restrict__ d1,
-    const T* __restrict__ d2, int ra, int rb, const typename Cx<T>::type* __restrict__ twt,
-    const typename Cx<T>::type* __restrict__ twn)
+    MixLen mt, MixLen mn, const C* __restrict__ band,
+    C* __restrict__ cs, int lmax, const T* __restrict__ d1,
+    const T* __restrict__ d2, int ra, int rb, const C* __restrict__ twt,
+    const C* __restrict__ twn)
 {
-    using C = typename Cx<T>::type;
-    C* buf = mix_lds<C>();
+    C* buf = mix_lds();
     const int t = threadIdx.x, nt = blockDim.x;
     const int64_t col = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     const int N = mn.n, Nt = mt.n;
@@ -268,40 +266,36 @@ __global__ __launch_bounds__(1024) void k_mix_theta_fwd(
 // at most 8 values per thread up to 8192 (one butterfly of radix 8 to 12, two of 5 to 7), more above
 int threads_for(int n) { return std::min(1024, (n + 511) / 512 * 64); }
 
-// the instance of F for this precision and length, as F<T, V>
-#define NUSHT_MIX_LAUNCH(F, T_, N_, grid, ...)                                                      \
+// the instance of F for this length, as F<V>
+#define NUSHT_MIX_LAUNCH(F, N_, grid, ...)                                                      \
     do {                                                                                            \
         const int nt_ = threads_for(N_);                                                            \
-        const size_t lds_ = (size_t)((N_) + (N_) / 16 + 1) * 2 * sizeof(T_);                        \
+        const size_t lds_ = (size_t)((N_) + (N_) / 16 + 1) * sizeof(C);                        \
         if ((N_) <= 8192)                                                                           \
-            hipLaunchKernelGGL((F<T_, 8>), grid, dim3(nt_), lds_, s, __VA_ARGS__);                  \
+            hipLaunchKernelGGL(F<8>, grid, dim3(nt_), lds_, s, __VA_ARGS__);                  \
         else                                                                                        \
-            hipLaunchKernelGGL((F<T_, 9>), grid, dim3(nt_), lds_, s, __VA_ARGS__);                   \
+            hipLaunchKernelGGL(F<9>, grid, dim3(nt_), lds_, s, __VA_ARGS__);                   \
     } while (0)
 
-template <typename T>
 int mix_row(const nusht_plan_s* p, const MixLen& m, const void* in, void* out, int64_t rw,
             int nb, bool c2r, hipStream_t s)
 {
-    using C = typename Cx<T>::type;
     const nusht_geometry& g = p->g;
     const dim3 grid(p->fine_ra + p->fine_rb, nb);
     const C* tw = reinterpret_cast<const C*>(p->rowtw);
     if (c2r)
-        NUSHT_MIX_LAUNCH(k_mix_c2r, T, m.n, grid, m, reinterpret_cast<const C*>(in), rw, g.mmax + 1,
+        NUSHT_MIX_LAUNCH(k_mix_c2r, m.n, grid, m, reinterpret_cast<const C*>(in), rw, g.mmax + 1,
                          reinterpret_cast<T*>(out), g.n1, p->fine_ra, p->fine_rb, tw);
     else
-        NUSHT_MIX_LAUNCH(k_mix_r2c, T, m.n, grid, m, reinterpret_cast<const T*>(in), g.n1, p->fine_ra,
+        NUSHT_MIX_LAUNCH(k_mix_r2c, m.n, grid, m, reinterpret_cast<const T*>(in), g.n1, p->fine_ra,
                          p->fine_rb, reinterpret_cast<C*>(out), rw, g.mmax + 1, tw);
     NUSHT_HIP(hipGetLastError());
     return NUSHT_OK;
 }
 
-template <typename T>
 int mix_theta(const nusht_plan_s* p, const MixLen& mt, const MixLen& mn, const void* in, void* out,
               int nmaps, bool inv, hipStream_t s)
 {
-    using C = typename Cx<T>::type;
     const nusht_geometry& g = p->g;
     const dim3 grid(g.mmax + 1, nmaps);
     const T *d1 = p->dec1, *d2 = p->dec2;
@@ -310,10 +304,10 @@ int mix_theta(const nusht_plan_s* p, const MixLen& mt, const MixLen& mn, const v
     const C* src = reinterpret_cast<const C*>(in);
     C* dst = reinterpret_cast<C*>(out);
     if (inv)
-        NUSHT_MIX_LAUNCH(k_mix_theta_inv, T, mn.n, grid, mt, mn, src, dst, g.lmax, d1, d2, p->fine_ra,
+        NUSHT_MIX_LAUNCH(k_mix_theta_inv, mn.n, grid, mt, mn, src, dst, g.lmax, d1, d2, p->fine_ra,
                          p->fine_rb, twt, twn);
     else
-        NUSHT_MIX_LAUNCH(k_mix_theta_fwd, T, mn.n, grid, mt, mn, src, dst, g.lmax, d1, d2, p->fine_ra,
+        NUSHT_MIX_LAUNCH(k_mix_theta_fwd, mn.n, grid, mt, mn, src, dst, g.lmax, d1, d2, p->fine_ra,
                          p->fine_rb, twt, twn);
     NUSHT_HIP(hipGetLastError());
     return NUSHT_OK;
@@ -377,13 +371,13 @@ bool mixtheta_supported(const nusht_geometry& g)
 int launch_mix_row(const nusht_plan_s* p, const void* in, void* out, int64_t rw, int nb,
                    bool c2r, hipStream_t s)
 {
-    return mix_row<double>(p, p->mix_row, in, out, rw, nb, c2r, s);
+    return mix_row(p, p->mix_row, in, out, rw, nb, c2r, s);
 }
 
 int launch_mix_theta(const nusht_plan_s* p, const void* in, void* out, int nmaps, bool inv,
                      hipStream_t s)
 {
-    return mix_theta<double>(p, p->mix_torus, p->mix_theta, in, out, nmaps, inv, s);
+    return mix_theta(p, p->mix_torus, p->mix_theta, in, out, nmaps, inv, s);
 }
 
 }  // namespace nusht

@@ -693,8 +693,10 @@ bool thetafft_supported(const nusht_geometry& g)
 
 // The kernels that hold the DFT over the doubled circle take the lengths the kernels of this file
 // do not, and short columns of any length, where a call is bound by its launches (n1 <= 1024);
-// from there on the passes of this file with rocFFT's torus transform are the faster pair
-// (117 + 56 us against about 215 us scaled from n1 = 6048, at n1 = 8192).
+// from there on the passes of this file with rocFFT's torus transform are the faster pair for a
+// single map.  One kernel / the pair, adjoint, in us: one map at n1 = 512 14 / 14, 1024 16 / 15, 2048
+// 25 / 20, 4096 48 / 44, 8192 224 / 169; eight maps 18 / 35, 26 / 47, 82 / 97, 277 / 305, 1655 / 1343
+// (one rocFFT launch per map; 5 2^K, n1 = 1280 / 2560 / 5120: one map 20 / 27 / 90 against 19 / 36 / 92).
 bool thetafft_with_torus(const nusht_geometry& g)
 {
     return rowfft_supported(g) && (!thetafft_supported(g) || g.n1 <= 1024) && mixtheta_supported(g);
