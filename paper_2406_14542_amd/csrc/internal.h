@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <rocfft/rocfft.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <string>
@@ -151,7 +152,7 @@ struct nusht_plan_s {
     size_t Xbytes = 0;
     void* Y = nullptr;
     size_t Ybytes = 0;
-    void* W = nullptr;           // one map's fine row spectrum, where it has no room behind the bands
+    void* W = nullptr;           // fine row spectra, where they have no room behind the bands
     size_t Wbytes = 0;
     double* V = nullptr;         // point scratch: packed point values of one group of maps
     void* fftwork = nullptr;
@@ -230,9 +231,17 @@ struct BandRec {
 // Maps are processed by the point kernels in groups of four, the remainder one by one.
 inline int group_width(int nmaps, int b) { return (nmaps - b) >= 4 ? 4 : 1; }
 
+size_t fine_spec_bytes(const nusht_plan_s* p);  // full row spectra [n1][n2/2+1] of one map
+size_t fine_band_bytes(const nusht_plan_s* p);  // band spectrum [mmax+1][n1] of one map
+
 // Row spectra of small maps are transformed together, up to this much scratch: one launch for
 // the batch where a launch per map would leave the chip idle.  (Larger maps fill it alone.)
 constexpr size_t kRowBatchBytes = 64u << 20;
+inline int row_batch_most(const nusht_plan_s* p)
+{
+    const size_t n = std::max(kRowBatchBytes, fine_spec_bytes(p)) / fine_band_bytes(p);
+    return (int)std::min<size_t>(n, 1 << 20);
+}
 
 // Spreading strategy: the band sweep for every FP32 (mixed-precision) kernel, for FP64 kernels
 // of width <= 8 and for deterministic plans; tile subgrids and a halo pass for wider FP64 kernels
@@ -262,8 +271,6 @@ int compute_geometry(int lmax, int mmax, double eps, int dtype, const nusht_plan
                      nusht_geometry* g);
 int ensure_capacity(nusht_plan_s* p, int nmaps);
 size_t fine_elem_bytes(const nusht_plan_s* p);
-size_t fine_spec_bytes(const nusht_plan_s* p);  // full row spectra [n1][n2/2+1] of one map
-size_t fine_band_bytes(const nusht_plan_s* p);  // band spectrum [mmax+1][n1] of one map
 
 // ---- FFT helpers (transform.hip) ----
 int fft_exec(nusht_plan_s* p, FftPlan& f, void* in, void* out, hipStream_t s);

@@ -431,7 +431,8 @@ size_t fine_band_bytes(const nusht_plan_s* p)
 // Scratch for up to `nmaps` maps: X and Y each hold the largest per-map intermediate of
 // either mode times the batch.  What is idle meanwhile serves twice: the subgrids of the tile
 // spreading lie in Y, which the adjoint uses only after it, and the row spectra of the library's own row
-// kernels lie behind the band spectra of the call, where those leave room (sigma >= 2: always).
+// kernels lie behind the band spectra of the call, where those leave room for all that are
+// transformed together (sigma >= 2: always).
 int ensure_capacity(nusht_plan_s* p, int nmaps)
 {
     if (nmaps <= p->bcap) return NUSHT_OK;
@@ -461,8 +462,8 @@ int ensure_capacity(nusht_plan_s* p, int nmaps)
     NUSHT_TRY(dmalloc((char**)&p->Y, std::max(per * nmaps, zb)));
     p->Ybytes = std::max(per * nmaps, zb);
     // row spectra: of rocFFT's row plans, or where they do not fit behind the bands
-    const size_t band = fine_band_bytes(p);
-    const size_t wb = !p->row_custom ? fine_spec : (per - band) * nmaps < band ? band : 0;
+    const size_t band = fine_band_bytes(p), rows = band * std::min(nmaps, row_batch_most(p));
+    const size_t wb = !p->row_custom ? fine_spec : (per - band) * nmaps < rows ? rows : 0;
     NUSHT_TRY(dmalloc((char**)&p->W, wb));
     p->Wbytes = wb;
     NUSHT_TRY(dmalloc(&p->V, (size_t)g.npts * (nmaps >= 4 ? 4 : 1)));

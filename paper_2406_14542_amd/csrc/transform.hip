@@ -315,9 +315,9 @@ char* row_scratch(const nusht_plan_s* p, char* bands, int nmaps, int& step)
     if (!p->row_custom) return bytes(p->W);
     const size_t per = fine_band_bytes(p), used = (size_t)nmaps * per;  // (rows are as large as a band)
     const size_t room = (bands == bytes(p->X) ? p->Xbytes : p->Ybytes) - used;
-    if (room < per) return bytes(p->W);
-    const size_t most = std::max<size_t>(kRowBatchBytes, fine_spec_bytes(p)) / per;
-    step = (int)std::max<size_t>(1, std::min<size_t>({(size_t)nmaps, most, room / per}));
+    const bool behind = room >= p->Wbytes;
+    step = std::max(1, std::min({nmaps, row_batch_most(p), (int)((behind ? room : p->Wbytes) / per)}));
+    if (!behind) return bytes(p->W);
     return bands + used;
 }
 
