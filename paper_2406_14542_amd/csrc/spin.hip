@@ -395,17 +395,18 @@ __device__ inline double2 folded(const InT* col, int j, int nr, int nt, double s
 // zeroed output with FP64 atomics, with no LDS and no barrier (the blocks of one m run on one
 // XCD: the atomics resolve in its L2; the order of those additions is not fixed, see DET for
 // the fixed-order variant).  A chunk's coefficients are fetched while the chunk before runs.
-// Wave w of an m has the w-th span of pairs counted from the equator, so that 2^k + 1 pairs
-// (lmax = 2^k' - 1) leave the pole's pair alone to a wave, which then ends at once for every m but s.
+// Wave w of an m has the w-th span of pairs counted from the equator, so that of 2^k + 1 pairs
+// (lmax = 2^k' - 1) the pole's is left, which only column m = s needs (see launch_spin_adjoint).
 // Bound by the FP64 VALU and the FP64 MFMAs, which share its units, and by latency at four waves
-// per SIMD: lmax 1023 / 2047, one field 0.40 / 1.86 ms, two fields 0.59 / 2.94 ms, against 0.49 / 3.02
-// and 0.75 / 4.98 ms with sums through LDS, three pairs per lane and the rescale test at every step.
+// per SIMD: lmax 1023 / 2047 / 4095, one field 0.37 / 1.84 / 12.3 ms, two fields 0.54 / 2.79 / 19.5 ms,
+// against 0.49 / 3.02 / 15.2 and 0.75 / 4.98 / 25.0 ms with sums through LDS, three pairs per lane and
+// the rescale test at every step.
 // With spans counted from the pole, in blocks of four waves, a fifth wave of one pair took every m of
 // lmax 1023 through all of l in a block of its own: 0.55 and 0.83 ms.
 //
-// R = 2.  Deterministic plans take R = 3 above 512 pairs: as fast there (lmax 1023 one field 451
-// against 415 us, two 581 / 637, lmax 1535 953 / 1063 and 1626 / 1810 us), with a third fewer
-// partial arrays; below, R = 2 is the faster (lmax 511 132 / 152 us).
+// R = 2.  Deterministic plans take R = 3 above 512 pairs: about as fast there (lmax 1023 one field
+// 460 / 415 us, two 597 / 637) with a third fewer partial arrays; below, R = 2 is the faster (lmax 511
+// 152 / 122 us).
 inline int spin_adj_pairs_per_lane(int npairs, bool det) { return det && npairs > 512 ? 3 : 2; }
 
 // DET: instead of the atomic adds, wave w of the m's waves writes its sums (unscaled) to
@@ -414,21 +415,28 @@ inline int spin_adj_pairs_per_lane(int npairs, bool det) { return det && npairs 
 template <int R, int MB, typename InT, bool DET, bool FUSED>
 __global__ __launch_bounds__(256) void k_spin_adj(
     const InT* __restrict__ in, int64_t in_map_stride, int64_t in_row_stride,
-    double* __restrict__ alm, int64_t nalm, int lmax, int mmax, int spin, int nbx,
+    double* __restrict__ alm, int64_t nalm, int lmax, int mmax, int spin, int nbx, int extra,
     const double4* __restrict__ rec, const double* __restrict__ km, const int* __restrict__ ke,
     const int* __restrict__ jlive, int nr, int nt, int64_t part_stride)
 {
     static_assert(kSpLC == 4, "four values of l per selector MFMA");
     __shared__ float pf_sink[4][64];
 
-    int m, rb;
-    xcd_place(blockIdx.x, nbx, m, rb);
-    if (m > mmax) return;  // uniform over the block
     const int npairs = (nr + 1) / 2;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, wpb = blockDim.x >> 6;
+    int m, pc;
+    if ((int)blockIdx.x < extra) {
+        m = blockIdx.x == 0 ? spin : mmax + 1;
+        pc = nbx * wpb + wave;
+    } else {
+        int rb;
+        xcd_place(blockIdx.x - extra, nbx, m, rb);
+        pc = rb * wpb + wave;
+    }
+    if (m > mmax) return;  // uniform over the block
     // wave pc of the m has the pairs [top - 64 R, top); one below the first live pair, or past the
     // pole, adds nothing
-    const int pc = wave * nbx + rb, top = npairs - 64 * R * pc;
+    const int top = npairs - 64 * R * pc;
     if (top <= jlive[m] || top <= 0) return;
     in += (int64_t)blockIdx.y * MB * 2 * in_map_stride;
     alm += (int64_t)blockIdx.y * MB * 2 * nalm * 2;
@@ -823,10 +831,16 @@ int launch_spin_adjoint(nusht_plan_s* p, int spin, const void* in, double* alm, 
     const nusht_geometry& g = p->g;
     const int npairs = (g.nrings + 1) / 2;
     const bool det = p->deterministic != 0;
-    // waves of one m, dealt to the fewest blocks of at most four, all of one size
+    // waves of one m without the pole's pair, in an odd number of blocks of at most four, all of one
+    // size; where the pole's pair has no place in them, column m = spin gets one more block, in front
+    // (8 ids, of which one is used, so that the others keep their XCD).  Blocks near the equator are
+    // the long ones and go to an XCD's shader engines in turn: an even count gives them to the same
+    // engines for every m (two fields at lmax 4095 / 3500 with four blocks 23.8 / 17.2 ms, with five
+    // 19.5 / 12.9).
     const int R = spin_adj_pairs_per_lane(npairs, det), span = 64 * R;
-    const int nwm = (npairs + span - 1) / span;
-    const int nbx = (nwm + 3) / 4, wpb = (nwm + nbx - 1) / nbx;
+    const int nwm = (npairs + span - 1) / span, n = std::max(1, (npairs + span - 2) / span);
+    const int nbx = (n + 3) / 4 | 1, wpb = (n + nbx - 1) / nbx;
+    const int extra = nwm > nbx * wpb ? 8 : 0;
     const int mpad = (g.mmax + 1 + 7) / 8 * 8;
     const int64_t row_stride = fused ? g.ntorus : g.nphi / 2 + 1;
     const int64_t map_stride = fused ? (int64_t)(g.mmax + 1) * g.ntorus : (int64_t)g.nrings * row_stride;
@@ -857,10 +871,10 @@ int launch_spin_adjoint(nusht_plan_s* p, int spin, const void* in, double* alm, 
         const int groups = (nfields - f) / mb;
         double* af = target + (int64_t)f * 2 * g.nalm * 2;
 #define SPA(RV, MBV, IT, D, FU)                                                                  \
-    hipLaunchKernelGGL((k_spin_adj<RV, MBV, IT, D, FU>), dim3(nbx * mpad, groups), dim3(64 * wpb), \
-                       0, s,                                                                      \
+    hipLaunchKernelGGL((k_spin_adj<RV, MBV, IT, D, FU>), dim3(extra + nbx * mpad, groups),       \
+                       dim3(64 * wpb), 0, s,                                                                      \
                        reinterpret_cast<const IT*>(in) + (int64_t)f * 2 * map_stride, map_stride, \
-                       row_stride, af, g.nalm, g.lmax, g.mmax, spin, nbx, p->spin_rec,           \
+                       row_stride, af, g.nalm, g.lmax, g.mmax, spin, nbx, extra, p->spin_rec,    \
                        p->spin_km, p->spin_ke, p->spin_jlive, g.nrings, g.ntorus, nz)
 #define SPA_MB(IT, FU)                                                            \
     do {                                                                          \
