@@ -188,11 +188,14 @@ __device__ inline void xcd_block(int b, int nbx, int& m, int& rb)
 // Bound by the FP64 VALU: (3 + 2 MB) R instructions per l and wave, and by the coefficients' scalar
 // loads.  One map at lmax 127 / 1023 / 1535 / 2047 / 4095: 12 / 84 / 225 / 432 / 2573 us against 43 / 149 /
 // 522 / 603 / 3132 us of two kernels (scaled and unscaled rings) on forked streams with contiguous rings
-// per wave and coefficients loaded when used; four maps 18 / 173 / 488 / 937 / 6401 against 42 / 250 / 878 /
-// 1162 / 7035 us.
+// per wave and coefficients loaded when used; four maps at 127 / 1023 / 2047 / 4095 18 / 165 / 857 / 6270
+// against 42 / 250 / 1162 / 7035 us.
 constexpr int kSynLC = 8;               // l values per chunk of the synthesis
 
-constexpr int kSubWaves = 8;  // most waves per block
+// Most waves per block.  Four maps: blocks of four are faster up to lmax 3700 (8 / 4 waves in us, lmax
+// 2047 915 / 864, 3000 3171 / 2754, 4095 6395 / 6339); one map and its adjoint are slower in blocks
+// of four above lmax 3100 (1451 / 1525 and 2139 / 2399 at 3200).
+constexpr int sub_waves(int mb) { return mb == 4 ? 4 : 8; }
 
 // Blocks of the kernels that split one m's live pairs over waves of R sub-blocks.  For m > 0 the
 // pole's pair is never live, so that 2^k + 1 pairs (lmax = 2^k' - 1) leave no sub-block of one pair: the
@@ -201,11 +204,11 @@ constexpr int kSubWaves = 8;  // most waves per block
 // the m's wave w nbx + rb: blocks of equal weight.
 struct SubGrid {
     int nbx, wpb, extra;
-    __host__ __device__ SubGrid(int npairs, int R)
+    __host__ __device__ SubGrid(int npairs, int R, int most)
     {
         const int nw = (npairs + 64 * R - 2) / (64 * R), nw0 = (npairs + 64 * R - 1) / (64 * R);
         const int n = nw > 0 ? nw : 1;
-        nbx = (n + kSubWaves - 1) / kSubWaves;
+        nbx = (n + most - 1) / most;
         wpb = (n + nbx - 1) / nbx;
         extra = nw0 > nbx * wpb ? 8 : 0;
     }
@@ -266,17 +269,17 @@ __device__ inline void run_states(int& st, F&& f)
 }
 
 template <int MB, int R, bool FUSED, typename OutT>
-__global__ __launch_bounds__(64 * kSubWaves) void k_legendre_synth(
+__global__ __launch_bounds__(64 * sub_waves(MB)) void k_legendre_synth(
     const double2* __restrict__ alm, int64_t nalm, int lmax, int mmax,
     const double2* __restrict__ rec, const double* __restrict__ cm_mant,
     const int* __restrict__ cm_exp, const int* __restrict__ jlive, int nr, int nt,
     OutT* __restrict__ out, int64_t out_map_stride, int64_t out_row_stride)
 {
     constexpr int LC = kSynLC;
-    __shared__ float pf_sink[kSubWaves][64];
+    __shared__ float pf_sink[sub_waves(MB)][64];
     const int npairs = (nr + 1) / 2;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const SubGrid sg(npairs, R);
+    const SubGrid sg(npairs, R, sub_waves(MB));
     int m, pc;
     sg.place(blockIdx.x, wave, mmax, m, pc);
     if (m > mmax) return;
@@ -867,17 +870,17 @@ __global__ __launch_bounds__(kAdjWaves * 64, DET ? 3 : 4) void k_legendre_adj(
 // ------------------------------------------------------------------------------------
 
 template <int R, bool FUSED, typename InT>
-__global__ __launch_bounds__(64 * kSubWaves) void k_legendre_adj_one(
+__global__ __launch_bounds__(64 * sub_waves(1)) void k_legendre_adj_one(
     const InT* __restrict__ in, int64_t in_row_stride, double* __restrict__ alm, int64_t part_stride,
     int lmax, int mmax,
     const double2* __restrict__ rec, const double* __restrict__ cm_mant,
     const int* __restrict__ cm_exp, const int* __restrict__ jlive, int nr, int nt)
 {
     constexpr int LC = 8;  // l values between two flushes: 2 LC / 4 = 4 registers of sums
-    __shared__ float pf_sink[kSubWaves][64];
+    __shared__ float pf_sink[sub_waves(1)][64];
     const int npairs = (nr + 1) / 2;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const SubGrid sg(npairs, R);
+    const SubGrid sg(npairs, R, sub_waves(1));
     int m, pc;
     sg.place(blockIdx.x, wave, mmax, m, pc);
     if (m > mmax) return;
@@ -1078,7 +1081,7 @@ namespace {
 // the scalar registers to longer fetches.  R = 1 / 2 in us: four maps at 65 pairs (lmax 127) 18 / 25, at
 // 129 34 / 36, at 257 80 / 67, at 2049 7485 / 6401; one map at 257 31 / 36, at 513 84 / 85, at 1025
 // 470 / 432, at 2049 2950 / 2573; two maps at 513 108 / 128, at 1025 555 / 599, at 2049 3875 / 3934.
-// (More than two per wave: spilled scalar registers.)
+// (Four maps in blocks of eight waves.  More than two per wave: spilled scalar registers.)
 int synth_pairs_per_lane(int npairs, int mb)
 {
     if (mb == 2) return 1;
@@ -1091,7 +1094,7 @@ int launch_synth(const nusht_plan_s* p, const double2* alm, OutT* out, int group
 {
     const nusht_geometry& g = p->g;
     const int npairs = (g.nrings + 1) / 2;
-    const SubGrid sg(npairs, R);
+    const SubGrid sg(npairs, R, sub_waves(MB));
     const int mpad = (g.mmax + 1 + 7) / 8 * 8;
     hipLaunchKernelGGL((k_legendre_synth<MB, R, FUSED, OutT>), dim3(sg.extra + sg.nbx * mpad, groups),
                        dim3(64 * sg.wpb), 0, s, alm, g.nalm, g.lmax, g.mmax, p->rec, p->cm_mant,
@@ -1177,7 +1180,7 @@ int launch_adj_one(nusht_plan_s* p, const void* in, double* alm, int64_t row_str
     const int npairs = (g.nrings + 1) / 2;
     const int R = one_map_pairs_per_lane(npairs);
     const int nw = (npairs + 64 * R - 1) / (64 * R);  // most waves of one m
-    const SubGrid sg(npairs, R);
+    const SubGrid sg(npairs, R, sub_waves(1));
     const int mpad = (g.mmax + 1 + 7) / 8 * 8;
     double* target = alm;
     int64_t part_stride = 0;
