@@ -223,8 +223,9 @@ __global__ __launch_bounds__(512, 4) void k_mlp_forward(const float* __restrict_
 // columns 16 ub .. of W2 and W3 (32 registers) in the products over points.  A tile's gradient is
 // summed from zero and then added to the block's running sum, so that the sums' rounding grows
 // with the number of tiles, not of points.  Every block writes one partial vector, which
-// k_mlp_reduce sums in block order.  Bound by the FP32 MFMAs (208 kflop a point; 2.65 ms at their
-// peak for 2 M points) and the barriers between the layers: 6.03 ms against 85.4 ms on the VALU
+// k_mlp_reduce sums in block order.  The FP32 MFMAs (208 kflop a point; 2.65 ms at their peak for 2 M
+// points) are busy 44 % of its time; the rest are the barriers between the layers and 96 registers
+// per lane that spill at 16 waves per CU (12 GB at 2 TB/s): 5.95 ms against 85.4 ms on the VALU
 // (135 KB of LDS, one block of 4 waves per CU; strided scalar weight loads in the delta products).
 __global__ __launch_bounds__(1024) void k_mlp_backward(const float* __restrict__ params,
                                                        const float* __restrict__ feat,
